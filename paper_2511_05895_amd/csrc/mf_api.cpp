@@ -61,6 +61,8 @@ struct mf_handle {
     int32_t kc = 1;
     int32_t mode = MF_MODE_DATA;
     int32_t grid = 1;
+    int32_t xcd = 0;  // the solve kernel's team stays on one XCD
+    int64_t join_ticks = 0;
     int64_t max_iter = -1;
     int64_t deadline_ticks = 0;
     int64_t barrier_ticks = 0;
@@ -131,6 +133,11 @@ constexpr int32_t kLazyItems = 1024;
 // arcs not reached yet; back to top-down below n / beta frontier vertices.
 constexpr int32_t kBuAlpha = 14;
 constexpr int32_t kBuBeta = 24;
+// Arcs up to which the solve kernel's team stays on one XCD.  Static solves,
+// one XCD (32 workgroups) against workgroups all over the device: R-MAT 2^16
+// (1.8 M arcs) 1.52 against 1.82 ms, R-MAT 2^18 (7.6 M arcs) 3.87 against 2.73
+// ms; segmentation grid 512^2 (2.1 M arcs) 64 against 72 ms.
+constexpr int64_t kXcdMaxArcs = 1 << 22;
 // Rounds of local pulls into the deficits a batch leaves (the last one
 // without handing deficits on).
 constexpr int kPullRounds = 4;
@@ -234,6 +241,8 @@ mf::LoopParams loop_params(const mf_handle_t *h) {
     p.bu_alpha = h->bu_alpha;
     p.bu_beta = kBuBeta;
     p.walk = h->walk;
+    p.xcd = h->xcd;
+    p.join_ticks = h->join_ticks;
     p.combine = h->combine;
     p.policy_mode = h->policy_mode;
     p.policy_w = mf::policy_device_params(h->policy);
@@ -857,6 +866,7 @@ MF_API int mf_create(const mf_csr_t *g, const int32_t *cap, int32_t s, int32_t t
     h->deadline_ticks = budget_ms * (int64_t)clock_khz;
     h->tick_ms = 1.0 / clock_khz;
     h->barrier_ticks = 10000 * (int64_t)clock_khz;  // 10 s
+    h->join_ticks = clock_khz / 10;                 // 0.1 ms
     // workgroups of the persistent kernel
     int maxb = 0;
     if ((e = mf::loop_max_coresident(o.device, &maxb)) != hipSuccess)
@@ -871,6 +881,14 @@ MF_API int mf_create(const mf_csr_t *g, const int32_t *cap, int32_t s, int32_t t
         if ((int64_t)n <= 8192 && A <= (1 << 17)) grid = 1;
         else grid = (int)std::min<int64_t>(std::min(maxb, std::max(cus, 1)),
                                            std::max<int64_t>(8, (A + 65535) / 65536));
+        // Graphs of up to kXcdMaxArcs arcs run on the compute units of one XCD
+        // (see kXcd in the kernels): their steps are chains of dependent
+        // loads, and one L2 without invalidations answers those sooner than
+        // eight with.  Larger ones need every compute unit's bandwidth.
+        if (grid > 1 && A <= kXcdMaxArcs) {
+            h->xcd = 1;
+            grid = std::max(2, std::max(cus, 1) / mf::kXcds);
+        }
     }
     if (grid > 1 && grid > maxb)
         return bail(MF_EINVAL, "grid_blocks above the co-resident limit " + std::to_string(maxb));

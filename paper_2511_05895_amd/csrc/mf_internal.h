@@ -19,6 +19,8 @@ constexpr int kHugeDeg = 4096;
 // Arcs per BFS frontier item: a frontier vertex with a longer list is split
 // into several items so that hubs are expanded by many wavefronts at once.
 constexpr int kChunk = 256;
+// XCDs of the device; consecutive workgroups of a launch go to them in turn.
+constexpr int kXcds = 8;
 // Threads per workgroup of the persistent solve kernel.
 constexpr int kBlock = 1024;
 
@@ -99,6 +101,9 @@ struct alignas(32) ListCtr {
 struct Ctrl {
     PaddedU32 bar_count;  // monotonic barrier arrivals of the launch (groups, for large teams)
     PaddedU32 abort;
+    PaddedU32 join;       // workgroups that registered for the launch's team (top bit: closed)
+    PaddedU32 team_size;  // its size once closed
+    PaddedU32 xcd_pick;   // XCD of an XCD-local team, plus one
     PaddedU32 bar_group[kBarGroups];  // arrivals per group of workgroups (two-level barrier)
     int32_t qcount[4];  // frontier items per BFS level, triple-buffered
     int32_t qverts[4];  // vertices discovered per BFS level (direction rule), same buffering
@@ -211,6 +216,9 @@ struct LoopParams {
                                // exceed the arcs of the vertices not reached yet, and stays
                                // bottom-up while the frontier holds at least n / bu_beta vertices
     int32_t bu_beta;
+    int32_t team_want;         // workgroups the launch's team waits for (see join_team)
+    int32_t xcd;               // 1: the team stays on one XCD
+    int64_t join_ticks;        // wall-clock ticks it waits
     int32_t walk;              // 1: long arc lists are visited by a walk that pushes downhill in arc
                                // order and stops when the excess is gone (full scan only to relabel)
 };

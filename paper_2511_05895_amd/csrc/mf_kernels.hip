@@ -49,39 +49,78 @@ __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 // grid over eight XCDs with separate L2 caches.
 constexpr int kAgent = __HIP_MEMORY_SCOPE_AGENT;
 constexpr int kGroup = __HIP_MEMORY_SCOPE_WORKGROUP;
+// A team whose workgroups all run on one XCD (kXcd) shares that XCD's L2.  Its
+// stores reach the L2 once the storing wave has waited for them, its atomics
+// resolve there, and a load that skips the L1 (a relaxed agent-scope load)
+// reads it, so the team needs no L2 write-back and no invalidation at its
+// barriers.  Every load of data that the loop changes goes through get<SC>,
+// which skips the L1 for such a team (the L1 of another compute unit may hold
+// a stale line, and the only instruction that drops it drops the L2's lines
+// too) and is a plain load for the others.
+constexpr int kXcd = 100;
+template <int SC>
+constexpr int scope_of = SC == kXcd ? kAgent : SC;
 
 template <int SC>
 __device__ __forceinline__ int32_t ld(const int32_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, SC);
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, scope_of<SC>);
 }
 template <int SC>
 __device__ __forceinline__ int64_t ld(const int64_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, SC);
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, scope_of<SC>);
+}
+template <int SC>
+__device__ __forceinline__ int32_t get(const int32_t *p) {
+    if constexpr (SC == kXcd) return ld<SC>(p);
+    else return *p;
+}
+template <int SC>
+__device__ __forceinline__ int64_t get(const int64_t *p) {
+    if constexpr (SC == kXcd) return ld<SC>(p);
+    else return *p;
+}
+template <int SC>
+__device__ __forceinline__ int2 get(const int2 *p) {
+    if constexpr (SC == kXcd) {
+        const int64_t x = ld<SC>(reinterpret_cast<const int64_t *>(p));
+        return make_int2((int)(uint32_t)x, (int)((uint64_t)x >> 32));
+    } else {
+        return *p;
+    }
 }
 template <int SC>
 __device__ __forceinline__ void add(int32_t *p, int32_t v) {
-    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, SC);
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, scope_of<SC>);
 }
 template <int SC>
 __device__ __forceinline__ void add(int64_t *p, int64_t v) {
-    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, SC);
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, scope_of<SC>);
 }
 template <int SC>
 __device__ __forceinline__ int32_t fetch_add(int32_t *p, int32_t v) {
-    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, SC);
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, scope_of<SC>);
 }
 template <int SC>
 __device__ __forceinline__ int64_t fetch_add(int64_t *p, int64_t v) {
-    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, SC);
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, scope_of<SC>);
 }
 template <int SC>
 __device__ __forceinline__ int32_t xchg(int32_t *p, int32_t v) {
-    return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, SC);
+    return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, scope_of<SC>);
 }
 template <int SC>
 __device__ __forceinline__ bool cas(int32_t *p, int32_t expected, int32_t desired) {
     return __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED,
-                                                __ATOMIC_RELAXED, SC);
+                                                __ATOMIC_RELAXED, scope_of<SC>);
+}
+
+// Workgroup barrier after which every wave may read what the others stored.
+// With loads that skip the L1 (kXcd) each wave first waits until its own
+// stores and atomics have reached the L2.
+template <int SC>
+__device__ __forceinline__ void block_sync() {
+    if constexpr (SC == kXcd) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
 }
 
 // residual capacity field of arc a
@@ -164,7 +203,7 @@ __device__ __forceinline__ int64_t uniform(int64_t x) {
 }
 
 // The workgroups that run one solve loop together: ranks 0..size-1.  Either
-// the whole grid of a cooperative launch, or a single workgroup of a batched
+// the workgroups of a launch that joined (join_team), or a single workgroup of a batched
 // launch (then every barrier is a workgroup barrier).
 struct Team {
     int rank, size;
@@ -186,25 +225,23 @@ struct Team {
 // caller must then leave the kernel, so every workgroup ends even if
 // co-residency ever failed.  Every thread of every workgroup of the team calls
 // it with the same epoch, which it advances.
+template <int SC>
 __device__ bool grid_barrier(Ctrl *c, const Team &tm, uint32_t &epoch, int64_t limit) {
-    if (tm.size == 1) {
-        __syncthreads();
-        return true;
-    }
+    block_sync<SC>();
+    if (tm.size == 1) return true;
     __shared__ int s_ok;
-    __syncthreads();
     const uint32_t e1 = epoch + 1u;
     ++epoch;
     if (threadIdx.x == 0) {
         int ok = 1;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if constexpr (SC != kXcd) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         // Arrivals: a team of 2 * kBarGroups workgroups or more arrives in
         // kBarGroups groups (rank mod kBarGroups), each on a counter of its own
         // line, and the last arrival of a group (the one that completes its
         // count) acquires the group's writes and releases them on to the top
         // counter, which every workgroup polls.  Arrivals on one word
         // serialise; this way each word takes a group's share of them.
-        const int G = tm.size < 2 * kBarGroups ? 1 : kBarGroups;
+        const int G = SC == kXcd || tm.size < 2 * kBarGroups ? 1 : kBarGroups;
         uint32_t target, before;
         if (G == 1) {
             target = e1 * (uint32_t)tm.size;
@@ -225,7 +262,7 @@ __device__ bool grid_barrier(Ctrl *c, const Team &tm, uint32_t &epoch, int64_t l
             uint32_t spins = 0;
             while ((int32_t)(__hip_atomic_load(&c->bar_count.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
                              target) < 0) {
-                __builtin_amdgcn_s_sleep(1);
+                if constexpr (SC != kXcd) __builtin_amdgcn_s_sleep(1);
                 if ((++spins & 255u) == 0) {
                     if (__hip_atomic_load(&c->abort.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
                         ok = 0;
@@ -239,11 +276,64 @@ __device__ bool grid_barrier(Ctrl *c, const Team &tm, uint32_t &epoch, int64_t l
                 }
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if constexpr (SC != kXcd) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         s_ok = ok;
     }
     __syncthreads();
     return s_ok != 0;
+}
+
+// The team of a launch forms itself: the workgroups that arrive register in
+// Ctrl::join, the first of them closes the team once `want` have registered or
+// `limit` ticks have passed, and whoever arrives later leaves the kernel.  A
+// team is thus made of workgroups that are running already, whatever else
+// occupies the device, so its barriers need no co-residency promise (and no
+// cooperative launch, whose host call costs several times a plain one's).
+// With kXcd only workgroups on the XCD of the first arrival register.  Returns
+// size 0 to a workgroup that is not in the team.  Every thread calls it once,
+// before any grid barrier, on a cleared control block.
+constexpr uint32_t kTeamClosed = 0x80000000u;
+template <int SC>
+__device__ Team join_team(Ctrl *c, int want, int64_t limit) {
+    __shared__ int s_rank, s_size;
+    if (threadIdx.x == 0) {
+        int rank = -1, size = 0;
+        bool in = true;
+        if constexpr (SC == kXcd) {
+            // hardware register XCC_ID (id 20), low four bits: this wave's XCD
+            const uint32_t me = (__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u) + 1u;
+            uint32_t first = 0;
+            in = __hip_atomic_compare_exchange_strong(&c->xcd_pick.v, &first, me, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT) ||
+                 first == me;
+        }
+        if (in) {
+            const uint32_t old = __hip_atomic_fetch_add(&c->join.v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!(old & kTeamClosed)) {
+                rank = (int)old;
+                const uint64_t t0 = wall_clock64();
+                if (rank == 0) {
+                    while ((int)__hip_atomic_load(&c->join.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want &&
+                           (int64_t)(wall_clock64() - t0) < limit) {
+                    }
+                    size = (int)__hip_atomic_fetch_or(&c->join.v, kTeamClosed, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&c->team_size.v, (uint32_t)size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else {
+                    // the first arrival is running and closes after `limit`
+                    // ticks; it also does so if this wait ever ran out first
+                    while ((size = (int)__hip_atomic_load(&c->team_size.v, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT)) == 0) {
+                        __builtin_amdgcn_s_sleep(1);
+                    }
+                }
+            }
+        }
+        s_rank = rank;
+        s_size = size;
+    }
+    __syncthreads();
+    return Team{s_rank, s_size};
 }
 
 // Per-thread event counters (32-bit), summed into the 64-bit Ctrl::stat at the
@@ -292,7 +382,7 @@ __device__ void bfs_roots(const DevGraph &g, const Team &tm, bool counts, bool f
         if (i < g.n) {
             const bool mine = !g.part || g.part[v] == g.part_want;
             if (mine || !g.part_restrict) {
-                root = mine && ((v == g.t) || (v != g.s && g.e[v] < 0));
+                root = mine && ((v == g.t) || (v != g.s && get<SC>(&g.e[v]) < 0));
                 g.h[v] = root ? 0 : g.n;
             }
             if (root) {
@@ -510,7 +600,7 @@ __device__ void bfs_tally_flush(const DevGraph &g, int L, BfsStage *tst) {
 template <int SC>
 __device__ void bfs_level(const DevGraph &g, const Team &tm, int L, int cnt, bool feats, bool counts,
                           bool track, bool lazy, BfsStage *st, BfsStage *tst, Tally &tl) {
-    const int2 *__restrict__ qin = g.q[L & 1];
+    const int2 *qin = g.q[L & 1];
     int2 *qout = g.q[(L + 1) & 1];
     int32_t *qout_count = &g.ctrl->qcount[(L + 1) % 3];
     const int lane = lane_id();
@@ -525,7 +615,7 @@ __device__ void bfs_level(const DevGraph &g, const Team &tm, int L, int cnt, boo
         const int64_t idx = base + lane;
         int beg = 0, len = 0;
         if (lane < ipw && idx < cnt) {
-            const int2 it = qin[idx];  // arc range {first, end} of one item
+            const int2 it = get<SC>(&qin[idx]);  // arc range {first, end} of one item
             beg = it.x;
             len = it.y - it.x;
         }
@@ -553,20 +643,20 @@ __device__ void bfs_level(const DevGraph &g, const Team &tm, int L, int cnt, boo
                 // and the twin's residual in the next; on a large level the
                 // twin's residual (a gather from anywhere in the arc array) is
                 // read only for heads not reached yet
-                const int2 rec = g.arc[a];
+                const int2 rec = get<SC>(&g.arc[a]);
                 const int tw = g.twin[a];
                 v = rec.x;
-                const int hv = g.h[v];
+                const int hv = get<SC>(&g.h[v]);
                 const bool cand = v != g.s && hv == n;
                 int cft = 1;
-                if (!lazy || cand) cft = g.arc[tw].y;
+                if (!lazy || cand) cft = get<SC>(cf_ptr(g.arc, tw));
                 tl.bfs_a++;
                 if (cand && cft > 0 && (!g.part_restrict || g.part[v] == g.part_want)) {
                     // the candidate's row bounds and excess load alongside the
                     // compare-and-swap that decides the discovery
                     vbeg = g.row_ptr[v];
                     vend = g.row_ptr[v + 1];
-                    ev = g.e[v];
+                    ev = get<SC>(&g.e[v]);
                     disc = cas<SC>(&g.h[v], n, L + 1);
                 }
             }
@@ -606,7 +696,7 @@ __device__ void bfs_bottom_up(const DevGraph &g, const Team &tm, int L, bool fea
         int v = -1, beg = 0, len = 0;
         if (idx < nb) {
             const int4 it = g.bu_items[idx];
-            if (it.x != g.s && g.h[it.x] == n) {
+            if (it.x != g.s && get<SC>(&g.h[it.x]) == n) {
                 v = it.x;
                 beg = it.y;
                 len = it.z - it.y;
@@ -630,8 +720,8 @@ __device__ void bfs_bottom_up(const DevGraph &g, const Team &tm, int L, bool fea
             const int oexcl = __shfl(excl, o, 64);
             bool hit = false;
             if (lane < total) {
-                const int2 r = g.arc[obeg + (lane - oexcl)];
-                if (r.y > 0) hit = g.h[r.x] == L;
+                const int2 r = get<SC>(&g.arc[obeg + (lane - oexcl)]);
+                if (r.y > 0) hit = get<SC>(&g.h[r.x]) == L;
                 tl.bfs_a++;
             }
             const uint64_t hm = __ballot(hit);
@@ -652,7 +742,7 @@ __device__ void bfs_bottom_up(const DevGraph &g, const Team &tm, int L, bool fea
         if (disc) {
             vbeg = g.row_ptr[v];
             vend = g.row_ptr[v + 1];
-            ev = g.e[v];
+            ev = get<SC>(&g.e[v]);
         }
         bfs_emit<SC>(g, L, disc, v, vbeg, vend, ev, feats, counts, true, st, nullptr, qout, qout_count, tl);
     }
@@ -764,7 +854,7 @@ __device__ __forceinline__ int relabel_to(const DevGraph &g, int u, int ho, int 
         if (hn > gap) hn = g.n;
         if (hn < g.n) add<SC>(&g.hcount[hn], 1);
         if (fetch_add<SC>(&g.hcount[ho], -1) == 1 && ho > 0)
-            __hip_atomic_fetch_min(&g.ctrl->gap, ho, __ATOMIC_RELAXED, SC);
+            __hip_atomic_fetch_min(&g.ctrl->gap, ho, __ATOMIC_RELAXED, scope_of<SC>);
     }
     if (hn > g.n) hn = g.n;
     g.h[u] = hn;
@@ -803,16 +893,17 @@ __device__ __forceinline__ void push_arc(const DevGraph &g, const RoundCtx &rc, 
 // Lowest residual neighbour height over the arcs first, first + stride, ...
 // below last, and the residual capacity of the arcs at that height; four
 // arcs per lane in flight.
+template <int SC>
 __device__ __forceinline__ void scan_lowest(const DevGraph &g, int first, int last, int stride, int &hmin,
                                             int64_t &cmin) {
     int a = first;
     for (; a + 3 * stride < last; a += 4 * stride) {
         int2 r[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) r[k] = g.arc[a + k * stride];
+        for (int k = 0; k < 4; ++k) r[k] = get<SC>(&g.arc[a + k * stride]);
         int hv[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) hv[k] = r[k].y > 0 ? g.h[r[k].x] : INT32_MAX;
+        for (int k = 0; k < 4; ++k) hv[k] = r[k].y > 0 ? get<SC>(&g.h[r[k].x]) : INT32_MAX;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             if (hv[k] < hmin) {
@@ -824,8 +915,8 @@ __device__ __forceinline__ void scan_lowest(const DevGraph &g, int first, int la
         }
     }
     for (; a < last; a += stride) {
-        const int2 r = g.arc[a];
-        const int hv = r.y > 0 ? g.h[r.x] : INT32_MAX;
+        const int2 r = get<SC>(&g.arc[a]);
+        const int hv = r.y > 0 ? get<SC>(&g.h[r.x]) : INT32_MAX;
         if (hv < hmin) {
             hmin = hv;
             cmin = r.y;
@@ -849,8 +940,8 @@ __device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx 
     if (u < 0) return 0;
     const int n = g.n;
     const int beg = g.row_ptr[u], end = g.row_ptr[u + 1];
-    int hu = g.h[u];
-    int32_t stamp = g.rmark[u];  // phase of u's last first-relabel (read with the rest)
+    int hu = get<SC>(&g.h[u]);
+    int32_t stamp = get<SC>(&g.rmark[u]);  // phase of u's last first-relabel (read with the rest)
     int relabels = 0;
     if (rc.use_gap && hu < n && hu > ld<SC>(&g.ctrl->gap)) {  // above a gap: cut off
         if (gl == 0) {
@@ -869,7 +960,7 @@ __device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx 
         if (gl == 0) tl.pr_cyc++;
         int hmin = INT32_MAX;
         int64_t cmin = 0;  // not needed here
-        scan_lowest(g, beg + gl, end, G, hmin, cmin);
+        scan_lowest<SC>(g, beg + gl, end, G, hmin, cmin);
         if (gl == 0) tl.pr_a += end - beg;
 #pragma unroll
         for (int d = G / 2; d >= 1; d >>= 1) hmin = min(hmin, __shfl_xor(hmin, d, G));
@@ -881,9 +972,9 @@ __device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx 
                 int64_t c = 0;
                 int v = -1, tw = 0;
                 if (a < end) {
-                    const int2 r = g.arc[a];
+                    const int2 r = get<SC>(&g.arc[a]);
                     tw = g.twin[a];
-                    if (r.y > 0 && g.h[r.x] == hmin) {
+                    if (r.y > 0 && get<SC>(&g.h[r.x]) == hmin) {
                         c = cyc == 0 ? r.y : max(0, ld<SC>(cf_ptr(g.arc, a)));
                         v = r.x;
                     }
@@ -940,8 +1031,8 @@ __device__ int discharge_walk(const DevGraph &g, int u, int kc, const RoundCtx &
     if (u < 0) return 0;
     const int n = g.n;
     const int beg = g.row_ptr[u], end = g.row_ptr[u + 1];
-    int hu = g.h[u];
-    int32_t stamp = g.rmark[u];
+    int hu = get<SC>(&g.h[u]);
+    int32_t stamp = get<SC>(&g.rmark[u]);
     int relabels = 0;
     if (rc.use_gap && hu < n && hu > ld<SC>(&g.ctrl->gap)) {  // above a gap: cut off
         if (lane == 0) {
@@ -965,9 +1056,9 @@ __device__ int discharge_walk(const DevGraph &g, int u, int kc, const RoundCtx &
             int64_t c = 0;
             int v = -1, hv = INT32_MAX;
             if (a < end) {
-                const int2 r = g.arc[a];
+                const int2 r = get<SC>(&g.arc[a]);
                 if (r.y > 0) {
-                    hv = g.h[r.x];
+                    hv = get<SC>(&g.h[r.x]);
                     if (hv < hu) {
                         c = cyc == 0 ? r.y : max(0, ld<SC>(cf_ptr(g.arc, a)));
                         v = r.x;
@@ -1040,8 +1131,8 @@ __device__ int discharge_block(const DevGraph &g, int u, int kc, const RoundCtx 
     const int beg = g.row_ptr[u], end = g.row_ptr[u + 1];
     const int chunk = ((end - beg + nw - 1) / nw + 63) & ~63;
     const int cb = min(end, beg + w * chunk), ce = min(end, cb + chunk);
-    int hu = g.h[u];
-    int32_t stamp = g.rmark[u];
+    int hu = get<SC>(&g.h[u]);
+    int32_t stamp = get<SC>(&g.rmark[u]);
     int relabels = 0;
     if (rc.use_gap && hu < n && hu > ld<SC>(&g.ctrl->gap)) {  // above a gap: cut off
         if (t == 0) {
@@ -1061,7 +1152,7 @@ __device__ int discharge_block(const DevGraph &g, int u, int kc, const RoundCtx 
         }
         int hm = INT32_MAX;
         int64_t cm = 0;
-        scan_lowest(g, cb + lane, ce, 64, hm, cm);
+        scan_lowest<SC>(g, cb + lane, ce, 64, hm, cm);
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) {
             const int oh = __shfl_xor(hm, d, 64);
@@ -1095,9 +1186,9 @@ __device__ int discharge_block(const DevGraph &g, int u, int kc, const RoundCtx 
                 int64_t c = 0;
                 int v = -1, tw = 0;
                 if (a < ce) {
-                    const int2 r = g.arc[a];
+                    const int2 r = get<SC>(&g.arc[a]);
                     tw = g.twin[a];
-                    if (r.y > 0 && g.h[r.x] == hmin) {
+                    if (r.y > 0 && get<SC>(&g.h[r.x]) == hmin) {
                         c = cyc == 0 ? r.y : max(0, ld<SC>(cf_ptr(g.arc, a)));
                         v = r.x;
                     }
@@ -1150,8 +1241,8 @@ __device__ int discharge_block_walk(const DevGraph &g, int u, int kc, const Roun
     const int t = threadIdx.x, lane = lane_id(), w = t >> 6, nw = blockDim.x >> 6;
     const int n = g.n;
     const int beg = g.row_ptr[u], end = g.row_ptr[u + 1];
-    int hu = g.h[u];
-    int32_t stamp = g.rmark[u];
+    int hu = get<SC>(&g.h[u]);
+    int32_t stamp = get<SC>(&g.rmark[u]);
     int relabels = 0;
     if (rc.use_gap && hu < n && hu > ld<SC>(&g.ctrl->gap)) {  // above a gap: cut off
         if (t == 0) {
@@ -1175,9 +1266,9 @@ __device__ int discharge_block_walk(const DevGraph &g, int u, int kc, const Roun
             int64_t c = 0;
             int v = -1, hv = INT32_MAX;
             if (a < end) {
-                const int2 r = g.arc[a];
+                const int2 r = get<SC>(&g.arc[a]);
                 if (r.y > 0) {
-                    hv = g.h[r.x];
+                    hv = get<SC>(&g.h[r.x]);
                     if (hv < hu) {
                         c = cyc == 0 ? r.y : max(0, ld<SC>(cf_ptr(g.arc, a)));
                         v = r.x;
@@ -1335,7 +1426,7 @@ __device__ void pr_round(const DevGraph &g, const Team &tm, int rd, int nl, int 
         const int64_t grp = gtid / kLightGroup, ngrp = stride / kLightGroup;
         const int64_t trips = (nl + ngrp - 1) / ngrp;  // the same for every group
         for (int64_t k = 0, i = grp; k < trips; ++k, i += ngrp)
-            rl += discharge_group<SC, kLightGroup>(g, i < nl ? lst[i] : -1, kc, rc, tl, to_t);
+            rl += discharge_group<SC, kLightGroup>(g, i < nl ? get<SC>(&lst[i]) : -1, kc, rc, tl, to_t);
     }
     // huge arc lists: one workgroup per vertex, handed out by a counter
     if (nu > 0) {
@@ -1347,14 +1438,14 @@ __device__ void pr_round(const DevGraph &g, const Team &tm, int rd, int nl, int 
             const int idx = s_idx;
             __syncthreads();
             if (idx >= nu) break;
-            if constexpr (WALK) rl += discharge_block_walk<SC>(g, hl[idx], kc, rc, tl, to_t);
-            else rl += discharge_block<SC>(g, hl[idx], kc, rc, tl, to_t);
+            if constexpr (WALK) rl += discharge_block_walk<SC>(g, get<SC>(&hl[idx]), kc, rc, tl, to_t);
+            else rl += discharge_block<SC>(g, get<SC>(&hl[idx]), kc, rc, tl, to_t);
         }
     }
     // long arc lists: one wavefront per vertex, dealt out round-robin (no
     // shared counter for thousands of wavefronts to contend on)
     for (int64_t i = tm.wave(); i < nh; i += tm.nwaves()) {
-        const int u = lst[g.n - 1 - i];
+        const int u = get<SC>(&lst[g.n - 1 - i]);
         if constexpr (WALK) rl += discharge_walk<SC>(g, u, kc, rc, tl, to_t);
         else rl += discharge_group<SC, 64>(g, u, kc, rc, tl, to_t);
     }
@@ -1406,8 +1497,8 @@ __device__ void pr_round_topology(const DevGraph &g, const Team &tm, int kc, con
 
 template <int SC>
 __device__ __forceinline__ void rie_arc(const DevGraph &g, int u, int hu, int a, Tally &tl) {
-    const int2 r = g.arc[a];
-    if (r.y > 0 && hu > g.h[r.x] + 1) {
+    const int2 r = get<SC>(&g.arc[a]);
+    if (r.y > 0 && hu > get<SC>(&g.h[r.x]) + 1) {
         const int32_t c = xchg<SC>(cf_ptr(g.arc, a), 0);
         if (c > 0) {
             add<SC>(cf_ptr(g.arc, g.twin[a]), c);
@@ -1437,8 +1528,8 @@ __device__ void remove_invalid(const DevGraph &g, const Team &tm, const int32_t 
         int u = -1, beg = 0, end = 0, hu = 0;
         bool heavy = false;
         if (i < count) {
-            u = list[i];
-            hu = g.h[u];
+            u = get<SC>(&list[i]);
+            hu = get<SC>(&g.h[u]);
             if (skip_cut && hu >= g.n) {
                 u = -1;
             } else {
@@ -1593,8 +1684,8 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
         // --- global relabel ---
         if (leader) {
             for (int k = 0; k < 3; ++k) c->lst[k] = ListCtr{};
-            c->prev_pushes = c->phase_pushes;
-            c->prev_relabels = c->phase_relabels;
+            c->prev_pushes = ld<SC>(&c->phase_pushes);
+            c->prev_relabels = ld<SC>(&c->phase_relabels);
             c->feat_esum = 0;
             for (int b = 0; b < 8; ++b) c->feat_hist[b] = 0;
             c->nrelab = 0;
@@ -1617,7 +1708,7 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
         // did not reach) have their whole arc lists scanned at every level
         const bool dir = p.bu_alpha > 0 && g.bu_items != nullptr && !g.part_restrict;
         bfs_roots<SC>(g, tm, counts, feats, dir, tl);
-        if (!grid_barrier(c, tm, bar_epoch, p.barrier_ticks)) return;
+        if (!grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
         int L = 0;
         bool bu = false;
         int64_t seen_arcs = 0;  // arcs of the vertices reached so far
@@ -1655,7 +1746,7 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
                         bfs_level<SC>(g, bt, L, k, feats, counts, dir, k >= p.lazy_items,
                                       !alone && k >= kBfsStageMin ? stage : nullptr, stage, tl);
                     if (!alone) break;
-                    __syncthreads();
+                    block_sync<SC>();
                     ++L;
                     k = uniform(ld<SC>(&c->qcount[L % 3]));
                     if (k == 0 || k > p.solo_items) break;
@@ -1663,7 +1754,7 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
                 }
                 if (alone && threadIdx.x == 0) c->solo_level = L;
             }
-            if (!grid_barrier(c, tm, bar_epoch, p.barrier_ticks)) return;
+            if (!grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
             L = alone ? uniform(ld<SC>(&c->solo_level)) : L + 1;
         }
         if (dir) reach_prev = seen_arcs;
@@ -1690,7 +1781,7 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
         int act = 0;
         if (policy) {
             if (tm.rank == 0 && threadIdx.x < 64) policy_decide<SC>(g, p, c, L, iter);
-            if (!grid_barrier(c, tm, bar_epoch, p.barrier_ticks)) return;
+            if (!grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
             act = uniform(ld<SC>(&c->action));
         }
         const int64_t budget = act == 0 ? p.relabel_budget : max((int64_t)64, p.relabel_budget * act_budget(act) / 4);
@@ -1766,7 +1857,7 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
                     else pr_round<SC, WALK>(g, rt, rd, nl, nh, nu, p.kc, rc, p.combine ? comb : nullptr, tl);
                     ++r;
                     if (!alone) break;
-                    __syncthreads();
+                    block_sync<SC>();
                     const int rdn = r % 3;
                     const int64_t lhn = uniform(ld<SC>(reinterpret_cast<const int64_t *>(&c->lst[rdn])));
                     const int nun = uniform(ld<SC>(&c->lst[rdn].huge));
@@ -1782,7 +1873,7 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
                 }
             }
             if (!alone && done) break;  // the phase ends for every workgroup alike
-            if (!grid_barrier(c, tm, bar_epoch, p.barrier_ticks)) return;
+            if (!grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
             if (alone) {
                 r = uniform(ld<SC>(&c->solo_r));
                 reason = uniform(ld<SC>(&c->solo_reason));
@@ -1828,7 +1919,7 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
             if ((int64_t)(wall_clock64() - t0) > p.deadline_ticks) c->stop = 1;
         }
         flush_tally<SC>(c, tl);
-        if (!grid_barrier(c, tm, bar_epoch, p.barrier_ticks)) return;
+        if (!grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
         ++iter;
     }
     // --- value: e(t) plus the deficits of vertices other than s and t ---
@@ -1839,26 +1930,29 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
         __syncthreads();
         int64_t part = 0;
         for (int64_t v = tm.tid(); v < g.n; v += tm.nthreads()) {
-            const int64_t ev = g.e[v];
+            const int64_t ev = get<SC>(&g.e[v]);
             if (ev < 0 && v != g.s && v != g.t) part += ev;
         }
         part = wave_sum(part);
         if (lane_id() == 0 && part) atomicAdd((unsigned long long *)&s_def, (unsigned long long)part);
         __syncthreads();
         if (threadIdx.x == 0 && s_def) add<SC>(&c->deficit, s_def);
-        if (leader) c->e_t = g.e[g.t];
+        if (leader) c->e_t = get<SC>(&g.e[g.t]);
     }
     flush_tally<SC>(c, tl);
 }
 
-// The whole grid is one team (cooperative launch), or a single workgroup.
+// The whole grid is one team (see join_team), or a single workgroup.
 // WALK: long arc lists are visited by the downhill walk (else scan first);
 // the two are separate instances, since both inlined side by side would spill.
 template <int BLOCK, int SC, bool WALK>
 __global__ void __launch_bounds__(BLOCK) k_loop(DevGraph g, LoopParams p) {
     BfsStage *stage = nullptr;
     Combine *comb = nullptr;
-    if constexpr (SC == kAgent) {
+    Team tm{0, 1};
+    if constexpr (SC != kGroup) {
+        tm = join_team<SC>(g.ctrl, p.team_want, p.join_ticks);
+        if (tm.size == 0) return;
         __shared__ BfsStage s_stage;
         __shared__ Combine s_comb;
         if (threadIdx.x < 4) s_stage.cnt[threadIdx.x] = 0;
@@ -1875,7 +1969,7 @@ __global__ void __launch_bounds__(BLOCK) k_loop(DevGraph g, LoopParams p) {
         stage = &s_stage;
         comb = &s_comb;
     }
-    solve_loop<SC, WALK>(g, Team{(int)blockIdx.x, (int)gridDim.x}, p, stage, comb);
+    solve_loop<SC, WALK>(g, tm, p, stage, comb);
 }
 
 // Two teams in one cooperative launch: workgroups [0, split) run the solve
@@ -2499,12 +2593,17 @@ hipError_t launch_loop(const DevGraph &g, const LoopParams &p, int grid, hipStre
         else hipLaunchKernelGGL((k_loop<kBlock, kGroup, false>), dim3(1), dim3(kBlock), 0, st, g, p);
         return hipGetLastError();
     }
-    DevGraph ga = g;
     LoopParams pa = p;
-    void *args[] = {&ga, &pa};
-    const void *fn = p.walk ? reinterpret_cast<const void *>(k_loop<kBlock, kAgent, true>)
-                            : reinterpret_cast<const void *>(k_loop<kBlock, kAgent, false>);
-    return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kBlock), args, 0, st);
+    pa.team_want = grid;
+    if (p.xcd) {  // one workgroup in kXcds lands on the team's XCD, the others leave at once
+        const dim3 blocks(grid * kXcds);
+        if (p.walk) hipLaunchKernelGGL((k_loop<kBlock, kXcd, true>), blocks, dim3(kBlock), 0, st, g, pa);
+        else hipLaunchKernelGGL((k_loop<kBlock, kXcd, false>), blocks, dim3(kBlock), 0, st, g, pa);
+    } else {
+        if (p.walk) hipLaunchKernelGGL((k_loop<kBlock, kAgent, true>), dim3(grid), dim3(kBlock), 0, st, g, pa);
+        else hipLaunchKernelGGL((k_loop<kBlock, kAgent, false>), dim3(grid), dim3(kBlock), 0, st, g, pa);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_batch(const DevGraph *graphs, const int32_t *order, int count, const LoopParams &p,
