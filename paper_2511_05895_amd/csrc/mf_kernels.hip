@@ -128,29 +128,59 @@ __device__ __forceinline__ int32_t *cf_ptr(int2 *arc, int32_t a) {
     return reinterpret_cast<int32_t *>(arc) + 2 * (int64_t)a + 1;
 }
 
+// Wavefront scans and reductions on the vector ALU's lane-shift paths (DPP):
+// row shifts by 1, 2, 4, 8 inside rows of 16 lanes, then the last lane of one
+// row added to the next row and of the first half to the second.  A step costs
+// a few cycles, where a shuffle goes through the LDS unit and returns after
+// about a hundred; a push/relabel or BFS step has dozens of them one after
+// another.  Every lane of the wavefront must call them.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp(int identity, int x) {
+    return __builtin_amdgcn_update_dpp(identity, x, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int64_t dpp(int64_t identity, int64_t x) {
+    const uint32_t lo = (uint32_t)dpp<CTRL, ROWS>((int)(uint32_t)identity, (int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)dpp<CTRL, ROWS>((int)((uint64_t)identity >> 32), (int)((uint64_t)x >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+template <typename T, typename OP>
+__device__ __forceinline__ T wave_scan(T x, T identity, OP op) {
+    x = op(x, dpp<0x111, 0xf>(identity, x));  // row_shr 1
+    x = op(x, dpp<0x112, 0xf>(identity, x));
+    x = op(x, dpp<0x114, 0xf>(identity, x));
+    x = op(x, dpp<0x118, 0xf>(identity, x));
+    x = op(x, dpp<0x142, 0xa>(identity, x));  // row_bcast 15 into rows 1 and 3
+    x = op(x, dpp<0x143, 0xc>(identity, x));  // row_bcast 31 into rows 2 and 3
+    return x;
+}
+// value of a lane known at compile time or alike in all lanes
+__device__ __forceinline__ int lane_value(int x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
+__device__ __forceinline__ int64_t lane_value(int64_t x, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)((uint64_t)x >> 32), lane);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
 __device__ __forceinline__ int wave_incl_scan(int x) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        int y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
-    }
-    return x;
+    return wave_scan(x, 0, [](int a, int b) { return a + b; });
 }
-
 __device__ __forceinline__ int64_t wave_incl_scan64(int64_t x) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int64_t y = __shfl_up(x, d, 64);
-        if (lane_id() >= d) x += y;
-    }
-    return x;
+    return wave_scan(x, (int64_t)0, [](int64_t a, int64_t b) { return a + b; });
 }
-
-__device__ __forceinline__ int64_t wave_sum(int64_t x) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
-    return x;
+__device__ __forceinline__ int64_t wave_sum(int64_t x) { return lane_value(wave_incl_scan64(x), 63); }
+__device__ __forceinline__ int wave_sum(int x) { return lane_value(wave_incl_scan(x), 63); }
+__device__ __forceinline__ int wave_min(int x) {
+    return lane_value(wave_scan(x, INT32_MAX, [](int a, int b) { return min(a, b); }), 63);
+}
+__device__ __forceinline__ uint64_t wave_or(uint64_t x) {
+    return (uint64_t)lane_value(wave_scan((int64_t)x, (int64_t)0, [](int64_t a, int64_t b) { return a | b; }), 63);
+}
+// Minimum over a group of 8 lanes (pairs, then quads, then the mirrored half
+// row), for all of them; lanes outside a group may idle.
+__device__ __forceinline__ int group8_min(int x) {
+    x = min(x, dpp<0xb1, 0xf>(x, x));
+    x = min(x, dpp<0x4e, 0xf>(x, x));
+    return min(x, dpp<0x141, 0xf>(x, x));
 }
 
 __device__ __forceinline__ int mask_rank(uint64_t mask) {
@@ -167,7 +197,7 @@ __device__ __forceinline__ int wave_append1(int32_t *counter, bool pred) {
     int leader = __ffsll((unsigned long long)mask) - 1;
     int base = 0;
     if (lane_id() == leader) base = fetch_add<SC>(counter, __popcll(mask));
-    base = __shfl(base, leader, 64);
+    base = lane_value(base, __builtin_amdgcn_readfirstlane(leader));
     return pred ? base + mask_rank(mask) : -1;
 }
 
@@ -176,11 +206,11 @@ __device__ __forceinline__ int wave_append1(int32_t *counter, bool pred) {
 template <int SC>
 __device__ __forceinline__ int wave_appendn(int32_t *counter, int c) {
     int incl = wave_incl_scan(c);
-    int total = __shfl(incl, 63, 64);
+    const int total = lane_value(incl, 63);
     if (total == 0) return 0;
     int base = 0;
     if (lane_id() == 63) base = fetch_add<SC>(counter, total);
-    base = __shfl(base, 63, 64);
+    base = lane_value(base, 63);
     return base + incl - c;
 }
 
@@ -391,7 +421,7 @@ __device__ void bfs_roots(const DevGraph &g, const Team &tm, bool counts, bool f
             }
         }
         const int c = root ? n_items(end - beg) : 0;
-        const int nroot = (int)wave_sum((int64_t)root);
+        const int nroot = __popcll(__ballot(root));
         if (counts && lane_id() == 0 && nroot) add<SC>(&g.hcount[0], nroot);
         if (feats && lane_id() == 0 && nroot) add<SC>(&g.ctrl->feat_reached, nroot);
         if (track && nroot) {
@@ -486,13 +516,13 @@ __device__ __forceinline__ void bfs_emit(const DevGraph &g, int L, bool disc, in
     const int vdeg = vend - vbeg;
     const int c = disc ? n_items(vdeg) : 0;
     const int cincl = wave_incl_scan(c);
-    const int ctotal = __shfl(cincl, 63, 64);
+    const int ctotal = lane_value(cincl, 63);
     const bool light = active && vdeg <= kLightMaxDeg;
     const bool heavy = active && vdeg > kLightMaxDeg && vdeg <= kHugeDeg;
     const bool huge = active && vdeg > kHugeDeg;
     const uint64_t lm = __ballot(light), hm = __ballot(heavy);
     const int ndisc = counts || feats || track ? __popcll(__ballot(disc)) : 0;
-    const int64_t darcs = track ? wave_sum((int64_t)vdeg) : 0;
+    const int64_t darcs = track ? (int64_t)wave_sum(vdeg) : 0;  // at most A < 2^31
     int qbase = 0, lsb = -1, hsb = -1, qsb = -1;
     int64_t lbase = 0;
     if (lane == 63) {
@@ -519,11 +549,11 @@ __device__ __forceinline__ void bfs_emit(const DevGraph &g, int L, bool disc, in
         if (gl | gh)
             lbase = fetch_add<SC>(reinterpret_cast<int64_t *>(&g.ctrl->lst[0]), ((int64_t)gh << 32) | (int64_t)gl);
     }
-    qbase = __shfl(qbase, 63, 64);
-    lbase = __shfl(lbase, 63, 64);
-    qsb = __shfl(qsb, 63, 64);
-    lsb = __shfl(lsb, 63, 64);
-    hsb = __shfl(hsb, 63, 64);
+    qbase = lane_value(qbase, 63);
+    lbase = lane_value(lbase, 63);
+    qsb = lane_value(qsb, 63);
+    lsb = lane_value(lsb, 63);
+    hsb = lane_value(hsb, 63);
     int2 *qdst = qsb < 0 ? qout + qbase : st->items + qsb;
     const int qb = cincl - c;
     for (int k = 0; k < c; ++k) qdst[qb + k] = make_int2(vbeg + k * kChunk, min(vbeg + (k + 1) * kChunk, vend));
@@ -621,17 +651,15 @@ __device__ void bfs_level(const DevGraph &g, const Team &tm, int L, int cnt, boo
         }
         const int incl = wave_incl_scan(len);
         const int excl = incl - len;
-        const int total = __shfl(incl, 63, 64);
+        const int total = lane_value(incl, 63);
         for (int off = 0; off < total; off += 64) {
             const int j = off + lane;
-            // largest lane o with excl[o] <= j (that lane has len > 0)
-            int o = 0;
-#pragma unroll
-            for (int step = 32; step >= 1; step >>= 1) {
-                const int cand = o + step;
-                const int ex = __shfl(excl, cand, 64);
-                if (ex <= j) o = cand;
-            }
+            // the lane whose item holds arc j: items are never empty, so it is
+            // the number of items that start at or before j, less one
+            const bool here = len > 0 && excl >= off && excl < off + 64;
+            const uint64_t starts = wave_or(here ? 1ull << (excl - off) : 0ull);
+            const int before = __popcll(__ballot(len > 0 && excl < off));
+            const int o = before + mask_rank(starts) + (int)((starts >> lane) & 1ull) - 1;
             const int obeg = __shfl(beg, o, 64);
             const int oexcl = __shfl(excl, o, 64);
             bool disc = false;
@@ -705,7 +733,7 @@ __device__ void bfs_bottom_up(const DevGraph &g, const Team &tm, int L, bool fea
         bool disc = false;
         for (;;) {
             const int incl = wave_incl_scan(len);
-            const int total = __shfl(incl, 63, 64);
+            const int total = lane_value(incl, 63);
             if (total == 0) break;
             const int excl = incl - len;
             // largest lane o with excl[o] <= lane (that lane still has arcs)
@@ -926,6 +954,38 @@ __device__ __forceinline__ void scan_lowest(const DevGraph &g, int first, int la
     }
 }
 
+// Reductions over a group of G lanes, G = 8 or 64; lanes of other groups may
+// idle.
+template <int G>
+__device__ __forceinline__ int group_min(int x) {
+    static_assert(G == 8 || G == 64, "group width");
+    if constexpr (G == 64) return wave_min(x);
+    else return group8_min(x);
+}
+template <int G>
+__device__ __forceinline__ int64_t group_incl_scan(int64_t x) {
+    if constexpr (G == 64) {
+        return wave_incl_scan64(x);
+    } else {
+        // row shifts cross from one group into the next of the same row of 16:
+        // those lanes take nothing
+        const int gl = lane_id() & 7;
+        int64_t y = dpp<0x111, 0xf>((int64_t)0, x);
+        if (gl >= 1) x += y;
+        y = dpp<0x112, 0xf>((int64_t)0, x);
+        if (gl >= 2) x += y;
+        y = dpp<0x114, 0xf>((int64_t)0, x);
+        if (gl >= 4) x += y;
+        return x;
+    }
+}
+// value of the group's last lane
+template <int G>
+__device__ __forceinline__ int64_t group_last(int64_t x) {
+    if constexpr (G == 64) return lane_value(x, 63);
+    else return __shfl(x, 7, 8);
+}
+
 // A group of G lanes (G = 64: a wavefront) visits vertex u: the lanes scan
 // its arcs G at a time for the lowest residual neighbour height, and the push
 // pass hands the excess to the lowest arcs in arc order with a prefix sum of
@@ -953,8 +1013,7 @@ __device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx 
     // excess of u as last seen: loaded once, then taken from the returning
     // subtraction of what u pushed (incoming pushes only ever add to it)
     int64_t eu = 0;
-    if (gl == 0) eu = ld<SC>(&g.e[u]);
-    eu = __shfl(eu, 0, G);
+    eu = ld<SC>(&g.e[u]);  // every lane: one request, no shuffle
     for (int cyc = 0; cyc < kc && hu < n; ++cyc) {
         if (eu <= 0) break;
         if (gl == 0) tl.pr_cyc++;
@@ -962,8 +1021,7 @@ __device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx 
         int64_t cmin = 0;  // not needed here
         scan_lowest<SC>(g, beg + gl, end, G, hmin, cmin);
         if (gl == 0) tl.pr_a += end - beg;
-#pragma unroll
-        for (int d = G / 2; d >= 1; d >>= 1) hmin = min(hmin, __shfl_xor(hmin, d, G));
+        hmin = group_min<G>(hmin);
         if (hmin == INT32_MAX) break;
         if (hu > hmin) {
             int64_t sent = 0, now = eu;
@@ -980,16 +1038,11 @@ __device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx 
                     }
                 }
                 // inclusive prefix sum of c over the group, in arc order
-                int64_t incl = c;
-#pragma unroll
-                for (int d = 1; d < G; d <<= 1) {
-                    const int64_t y = __shfl_up(incl, d, G);
-                    if (gl >= d) incl += y;
-                }
+                const int64_t incl = group_incl_scan<G>(c);
                 const int64_t room = eu - sent;
                 const int64_t excl = incl - c;
                 const int64_t d = (c > 0 && excl < room) ? min(c, room - excl) : 0;
-                const int64_t tot = min(__shfl(incl, G - 1, G), room);
+                const int64_t tot = min(group_last<G>(incl), room);
                 // the group's total leaves u before its lanes push it on, so
                 // the returning subtraction overlaps the pushes
                 if (gl == 0 && tot > 0) now = fetch_add<SC>(&g.e[u], -tot) - tot;
@@ -1041,9 +1094,7 @@ __device__ int discharge_walk(const DevGraph &g, int u, int kc, const RoundCtx &
         }
         hu = n;
     }
-    int64_t eu = 0;
-    if (lane == 0) eu = ld<SC>(&g.e[u]);
-    eu = __shfl(eu, 0, 64);
+    int64_t eu = lane_value(ld<SC>(&g.e[u]), 0);
     for (int cyc = 0; cyc < kc && hu < n; ++cyc) {
         if (eu <= 0) break;
         if (lane == 0) tl.pr_cyc++;
@@ -1075,7 +1126,7 @@ __device__ int discharge_walk(const DevGraph &g, int u, int kc, const RoundCtx &
             const int64_t room = e0 - sent;
             const int64_t excl = incl - c;
             const int64_t d = (c > 0 && excl < room) ? min(c, room - excl) : 0;
-            const int64_t tot = min(__shfl(incl, 63, 64), room);
+            const int64_t tot = min(lane_value(incl, 63), room);
             if (lane == 0 && tot > 0) now = fetch_add<SC>(&g.e[u], -tot) - tot;
             if (d > 0) {
                 push_arc<SC>(g, rc, a, g.twin[a], v, (int32_t)d, to_t, tl);
@@ -1085,12 +1136,11 @@ __device__ int discharge_walk(const DevGraph &g, int u, int kc, const RoundCtx &
             sent += tot;
         }
         if (lane == 0) tl.pr_a += walked;
-        eu = __shfl(now, 0, 64);
+        eu = lane_value(now, 0);
         if (sent >= e0) continue;  // the excess went downhill
         // the walk reached the end of the list with excess left: relabel
         if (eu <= 0) break;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) hrest = min(hrest, __shfl_xor(hrest, d, 64));
+        hrest = wave_min(hrest);
         if (hrest == INT32_MAX) break;  // no residual arc left
         int hn = 0;
         if (lane == 0) {
@@ -1098,7 +1148,7 @@ __device__ int discharge_walk(const DevGraph &g, int u, int kc, const RoundCtx &
             tl.relabel++;
             note_relabel<SC>(g, rc, u, stamp);
         }
-        hu = __shfl(hn, 0, 64);
+        hu = lane_value(hn, 0);
         relabels++;
     }
     if (lane == 0 && hu < n && eu > 0) list_add<SC>(g, rc, u);
@@ -1201,7 +1251,7 @@ __device__ int discharge_block(const DevGraph &g, int u, int kc, const RoundCtx 
                     push_arc<SC>(g, rc, a, tw, v, (int32_t)d, to_t, tl);
                     tl.push++;
                 }
-                sent += min(__shfl(incl, 63, 64), rem);
+                sent += min(lane_value(incl, 63), rem);
             }
             if (lane == 0 && sent > 0) add<SC>(&g.e[u], -sent);
             __syncthreads();
@@ -1310,8 +1360,7 @@ __device__ int discharge_block_walk(const DevGraph &g, int u, int kc, const Roun
         eu = s_now;
         if (sent >= e0) continue;  // the excess went downhill
         if (eu <= 0) break;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) hrest = min(hrest, __shfl_xor(hrest, d, 64));
+        hrest = wave_min(hrest);
         if (lane == 0) s_wmin[w] = hrest;
         __syncthreads();
         int hmin = INT32_MAX;
@@ -1546,9 +1595,9 @@ __device__ void remove_invalid(const DevGraph &g, const Team &tm, const int32_t 
         while (hm) {
             const int l = __ffsll((unsigned long long)hm) - 1;
             hm &= hm - 1;
-            const int w = __shfl(u, l, 64);
-            const int wb = __shfl(beg, l, 64), we = __shfl(end, l, 64);
-            const int hw = __shfl(hu, l, 64);
+            const int w = lane_value(u, l);
+            const int wb = lane_value(beg, l), we = lane_value(end, l);
+            const int hw = lane_value(hu, l);
             for (int a = wb + lane; a < we; a += 64) rie_arc<SC>(g, w, hw, a, tl);
             if (lane == 0) tl.rie_a += we - wb;
         }
@@ -2346,8 +2395,8 @@ __global__ void k_pull_round(DevGraph g, const int64_t *ids, int64_t k, const in
             }
             if (v >= 0) need = -ld<kAgent>(&g.e[v]);
         }
-        v = __shfl(v, 0, 64);
-        need = __shfl(need, 0, 64);
+        v = lane_value(v, 0);
+        need = lane_value(need, 0);
         if (need <= 0) continue;
         const int beg = g.row_ptr[v], end = g.row_ptr[v + 1];
         int64_t got = 0;
