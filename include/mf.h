@@ -96,7 +96,9 @@ typedef struct {
                                this many vertices (none of more than 4096
                                arcs), is run by one workgroup alone, with
                                workgroup barriers between its levels or
-                               rounds, while the others wait; 0 = 128,
+                               rounds, while the others wait (solves whose
+                               workgroups share one XCD keep small levels and
+                               rounds among themselves instead); 0 = 128,
                                < 0 = never                                   */
     int32_t lazy_items;     /* a BFS level whose frontier holds at least this
                                many items reads the residual of an arc's

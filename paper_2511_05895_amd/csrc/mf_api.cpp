@@ -133,10 +133,15 @@ constexpr int32_t kLazyItems = 1024;
 // arcs not reached yet; back to top-down below n / beta frontier vertices.
 constexpr int32_t kBuAlpha = 14;
 constexpr int32_t kBuBeta = 24;
-// Arcs up to which the solve kernel's team stays on one XCD.  Static solves,
-// one XCD (32 workgroups) against workgroups all over the device: R-MAT 2^16
-// (1.8 M arcs) 1.52 against 1.82 ms, R-MAT 2^18 (7.6 M arcs) 3.87 against 2.73
-// ms; segmentation grid 512^2 (2.1 M arcs) 64 against 72 ms.
+// Arcs up to which one workgroup solves alone, and up to which the solve
+// kernel's team stays on one XCD (32 workgroups).  Static solves, one workgroup
+// against one XCD: 20 x 20 grid (2,880 arcs) 0.67 against 0.70 ms, random graph
+// of 1,000 vertices (16 k arcs) 0.45 against 0.48 ms, R-MAT 2^10 (24 k arcs) 0.50
+// against 0.25 ms, grid 64^2 (32 k arcs) 5.1 against 3.9 ms.  One XCD against
+// workgroups all over the device: R-MAT 2^16 (1.8 M arcs) 1.30 against 1.81 ms,
+// grid 720^2 (4.1 M arcs) 79 against 105 ms, R-MAT 2^17 (3.7 M arcs) 2.1 against
+// 2.3 ms, R-MAT 2^18 (7.6 M arcs) 3.6 against 2.6 ms.
+constexpr int64_t kOneMaxArcs = 1 << 14;
 constexpr int64_t kXcdMaxArcs = 1 << 22;
 // Rounds of local pulls into the deficits a batch leaves (the last one
 // without handing deficits on).
@@ -871,14 +876,15 @@ MF_API int mf_create(const mf_csr_t *g, const int32_t *cap, int32_t s, int32_t t
     int maxb = 0;
     if ((e = mf::loop_max_coresident(o.device, &maxb)) != hipSuccess)
         return bail(MF_EDEVICE, std::string("occupancy query: ") + hipGetErrorString(e));
-    // one workgroup for small graphs (no grid barrier at all); otherwise about
-    // one 1024-thread workgroup per 64K arcs, at most one per compute unit:
-    // a grid barrier costs roughly 60 ns per participating workgroup
+    // one workgroup for small graphs, the workgroups of one XCD for larger
+    // ones (kOneMaxArcs, kXcdMaxArcs); otherwise about one 1024-thread
+    // workgroup per 64K arcs, at most one per compute unit: a barrier of
+    // workgroups on several XCDs costs roughly 60 ns per workgroup
     int cus = 0;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, o.device);
     int grid = o.grid_blocks;
     if (grid == 0) {
-        if ((int64_t)n <= 8192 && A <= (1 << 17)) grid = 1;
+        if (A <= kOneMaxArcs) grid = 1;
         else grid = (int)std::min<int64_t>(std::min(maxb, std::max(cus, 1)),
                                            std::max<int64_t>(8, (A + 65535) / 65536));
         // Graphs of up to kXcdMaxArcs arcs run on the compute units of one XCD

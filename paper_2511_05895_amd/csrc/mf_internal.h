@@ -82,6 +82,10 @@ struct alignas(128) PaddedU32 {
     uint32_t v;
     uint32_t pad[31];
 };
+struct alignas(128) PaddedU64 {
+    uint64_t v;
+    uint64_t pad[15];
+};
 
 // One active-vertex list of the push/relabel rounds: vertices with short arc
 // lists fill items[0, light) from the front, long ones items[n-heavy, n) from
@@ -104,6 +108,7 @@ struct Ctrl {
     PaddedU32 join;       // workgroups that registered for the launch's team (top bit: closed)
     PaddedU32 team_size;  // its size once closed
     PaddedU32 xcd_pick;   // XCD of an XCD-local team, plus one
+    PaddedU64 sum[4];     // summing barriers of a run, in turn
     PaddedU32 bar_group[kBarGroups];  // arrivals per group of workgroups (two-level barrier)
     int32_t qcount[4];  // frontier items per BFS level, triple-buffered
     int32_t qverts[4];  // vertices discovered per BFS level (direction rule), same buffering
@@ -131,7 +136,7 @@ struct Ctrl {
     int64_t e_t;        // e(t) at termination
     int64_t cut;        // cut capacity (k_min_cut)
     // state of the rounds a workgroup ran alone, handed to the others
-    int64_t solo_last_deliv;
+    int64_t run_arcs;   // arcs of the vertices that BFS runs discovered (this launch)
     int32_t solo_r, solo_done, solo_reason, solo_last_change;
     int32_t check;      // failed invariants of the debug check (bits, see k_check_state)
     int32_t pad_;

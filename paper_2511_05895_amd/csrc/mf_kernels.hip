@@ -16,8 +16,9 @@
 //    frontiers still fill all 64 lanes.  The active worklist is built during the
 //    same BFS (a discovered vertex with positive excess is active), with
 //    ballot/mbcnt compaction and one atomic per wavefront, or per workgroup
-//    (LDS staging) on large levels; small frontiers are expanded by one
-//    workgroup alone, level after level, without grid barriers.
+//    (LDS staging) on large levels; small frontiers and short round lists stay
+//    in the LDS of a team on one XCD, or of one workgroup (runs of levels
+//    and rounds, see bfs_run and pr_rounds).
 //  * Push/relabel gives a group of lanes to a vertex with at most kLightMaxDeg
 //    arcs, a wavefront to a longer list and a workgroup to a huge one.  Every
 //    counter or list that all workgroups share is updated once per workgroup
@@ -112,6 +113,13 @@ template <int SC>
 __device__ __forceinline__ bool cas(int32_t *p, int32_t expected, int32_t desired) {
     return __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED,
                                                 __ATOMIC_RELAXED, scope_of<SC>);
+}
+
+// The value found (the swap happened when it is `expected`).
+template <int SC>
+__device__ __forceinline__ int32_t cas_seen(int32_t *p, int32_t expected, int32_t desired) {
+    __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED, __ATOMIC_RELAXED, scope_of<SC>);
+    return expected;
 }
 
 // Workgroup barrier after which every wave may read what the others stored.
@@ -214,6 +222,17 @@ __device__ __forceinline__ int wave_appendn(int32_t *counter, int c) {
     return base + incl - c;
 }
 
+// One of a view's rotating buffers by a number known only at run time: picked by
+// selects (an indexed read of the kernel's argument would put a copy of the
+// whole view in scratch memory).
+__device__ __forceinline__ int2 *frontier(const DevGraph &g, int L) { return (L & 1) ? g.q[1] : g.q[0]; }
+__device__ __forceinline__ int32_t *round_list(const DevGraph &g, int k) {
+    return k == 0 ? g.list[0] : k == 1 ? g.list[1] : g.list[2];
+}
+__device__ __forceinline__ int32_t *huge_list(const DevGraph &g, int k) {
+    return k == 0 ? g.huge[0] : k == 1 ? g.huge[1] : g.huge[2];
+}
+
 __device__ __forceinline__ int n_items(int deg) { return (deg + kChunk - 1) / kChunk; }
 
 // Appends of a round to the next round's list are staged per workgroup in
@@ -256,7 +275,7 @@ struct Team {
 // co-residency ever failed.  Every thread of every workgroup of the team calls
 // it with the same epoch, which it advances.
 template <int SC>
-__device__ bool grid_barrier(Ctrl *c, const Team &tm, uint32_t &epoch, int64_t limit) {
+__device__ __forceinline__ bool grid_barrier(Ctrl *c, const Team &tm, uint32_t &epoch, int64_t limit) {
     block_sync<SC>();
     if (tm.size == 1) return true;
     __shared__ int s_ok;
@@ -313,6 +332,79 @@ __device__ bool grid_barrier(Ctrl *c, const Team &tm, uint32_t &epoch, int64_t l
     return s_ok != 0;
 }
 
+// LDS of a run: consecutive BFS levels or push/relabel rounds whose frontier or
+// list stays in the workgroups' LDS (see bfs_run and rounds_run).
+constexpr int kRunItems = 1024;
+struct RunStage {
+    // BFS: frontier items of two levels, kRunItems each; rounds: short lists
+    // of two rounds, then long lists of two rounds, kStageCap each
+    int32_t buf[4 * kRunItems];
+    // BFS: active vertices found, short then long lists; rounds: relabelled
+    // vertices
+    int32_t aux[2 * kStageCap];
+    int32_t icnt[2], lcnt[2], hcnt[2], rcnt;
+    int32_t found;  // BFS: frontier items found in this level,
+    uint64_t act;   // short (low half) and long active vertices found in this run
+    int32_t larcs;     // BFS: arcs of the vertices discovered in this level
+    int32_t spill;     // something did not fit and went to the global lists
+    int32_t relabels;  // of this round
+    int32_t deliv;     // this round delivered excess
+    int32_t base[3];
+    int64_t acc[4];    // of the run: excess into t, relabels, pushes, deliveries into deficits
+    int64_t arcs;      // arcs of the vertices a BFS run discovered
+    uint64_t total;    // sum of the last team_sum
+    int32_t ok;
+};
+// The workgroup's one RunStage.  (Functions name it here instead of taking a
+// pointer, so that every access is known to be LDS.)
+__device__ __forceinline__ RunStage *run_stage() {
+    __shared__ RunStage s;
+    return &s;
+}
+static_assert(kStageCap == kRunItems, "the two views of RunStage::buf");
+
+// Barrier of a run that also adds up one word per workgroup (thread 0's
+// `mine`, below 2^56 in sum): a level or round ends with one atomic and its
+// poll, and the poll brings the totals that the next decision needs.  The
+// words rotate over four, each cleared by the leader two barriers before its
+// next use.  Only for teams of one workgroup, or of one XCD (no cache
+// maintenance; call block_sync first).  Every thread of the team calls it.
+template <int SC>
+__device__ __forceinline__ uint64_t team_sum(Ctrl *c, const Team &tm, uint32_t &epoch, uint64_t mine, int64_t limit, bool *ok) {
+    RunStage *rs = run_stage();
+    if (threadIdx.x == 0) {
+        int good = 1;
+        uint64_t x = mine;
+        if (tm.size > 1) {
+            uint64_t *word = &c->sum[epoch & 3u].v;
+            constexpr uint64_t one = 1ull << 56;
+            x = __hip_atomic_fetch_add(word, mine + one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine + one;
+            uint32_t spins = 0;
+            uint64_t t0 = 0;
+            while ((int)(x >> 56) != tm.size) {
+                if ((++spins & 1023u) == 0) {
+                    if (t0 == 0) t0 = wall_clock64();
+                    if (__hip_atomic_load(&c->abort.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
+                        (int64_t)(wall_clock64() - t0) > limit) {
+                        __hip_atomic_store(&c->abort.v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        good = 0;
+                        break;
+                    }
+                }
+                x = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (tm.rank == 0) c->sum[(epoch + 2u) & 3u].v = 0;
+            x &= one - 1;
+        }
+        rs->total = x;
+        rs->ok = good;
+    }
+    ++epoch;
+    __syncthreads();
+    *ok = rs->ok != 0;
+    return (uint64_t)uniform((int64_t)rs->total);
+}
+
 // The team of a launch forms itself: the workgroups that arrive register in
 // Ctrl::join, the first of them closes the team once `want` have registered or
 // `limit` ticks have passed, and whoever arrives later leaves the kernel.  A
@@ -324,7 +416,7 @@ __device__ bool grid_barrier(Ctrl *c, const Team &tm, uint32_t &epoch, int64_t l
 // before any grid barrier, on a cleared control block.
 constexpr uint32_t kTeamClosed = 0x80000000u;
 template <int SC>
-__device__ Team join_team(Ctrl *c, int want, int64_t limit) {
+__device__ __forceinline__ Team join_team(Ctrl *c, int want, int64_t limit) {
     __shared__ int s_rank, s_size;
     if (threadIdx.x == 0) {
         int rank = -1, size = 0;
@@ -375,7 +467,7 @@ struct Tally {
 
 // Every thread of the workgroup must call it.
 template <int SC>
-__device__ void flush_tally(Ctrl *c, Tally &t) {
+__device__ __forceinline__ void flush_tally(Ctrl *c, Tally &t) {
     __shared__ int64_t s_acc[8];
     if (threadIdx.x < 8) s_acc[threadIdx.x] = 0;
     __syncthreads();
@@ -401,7 +493,7 @@ __device__ void flush_tally(Ctrl *c, Tally &t) {
 // tags, only vertices of the wanted part can be roots, and with part_restrict
 // the heights of the other vertices are left alone.
 template <int SC>
-__device__ void bfs_roots(const DevGraph &g, const Team &tm, bool counts, bool feats, bool track, Tally &tl) {
+__device__ __forceinline__ void bfs_roots(const DevGraph &g, const Team &tm, bool counts, bool feats, bool track, Tally &tl) {
     const int64_t gtid = tm.tid();
     const int64_t stride = tm.nthreads();
     const int64_t nr = ((int64_t)g.n + 63) & ~63ll;
@@ -476,6 +568,12 @@ struct BfsStage {
     int64_t tarcs;
 };
 
+// The workgroup's one BfsStage (teams of several workgroups only).
+__device__ __forceinline__ BfsStage *bfs_stage() {
+    __shared__ BfsStage s;
+    return &s;
+}
+
 // Reserve k slots of an LDS counter if they fit under cap (no partial
 // reservation); returns the first slot or -1.
 __device__ __forceinline__ int stage_reserve(int32_t *ctr, int k, int cap) {
@@ -501,8 +599,9 @@ __device__ __forceinline__ int stage_reserve(int32_t *ctr, int k, int cap) {
 // staged (null: straight to the global counters).
 template <int SC>
 __device__ __forceinline__ void bfs_emit(const DevGraph &g, int L, bool disc, int v, int vbeg, int vend, int64_t ev,
-                                         bool feats, bool counts, bool track, BfsStage *st, BfsStage *tst,
-                                         int2 *qout, int32_t *qout_count, Tally &tl) {
+                                         bool feats, bool counts, bool track, bool staged, int2 *qout,
+                                         int32_t *qout_count, Tally &tl) {
+    BfsStage *st = bfs_stage();
     const int lane = lane_id();
     const int n = g.n;
     bool active = false;
@@ -527,7 +626,7 @@ __device__ __forceinline__ void bfs_emit(const DevGraph &g, int L, bool disc, in
     int64_t lbase = 0;
     if (lane == 63) {
         const int nl = __popcll(lm), nh = __popcll(hm);
-        if (st) {
+        if (SC != kGroup && staged) {
             if (ctotal) qsb = stage_reserve(&st->cnt[0], ctotal, kBfsStageItems);
             if (nl) lsb = stage_reserve(&st->cnt[1], nl, kStageCap);
             if (nh) hsb = stage_reserve(&st->cnt[2], nh, kStageCap);
@@ -536,12 +635,9 @@ __device__ __forceinline__ void bfs_emit(const DevGraph &g, int L, bool disc, in
         } else if (ndisc) {
             if (counts) add<SC>(&g.hcount[L + 1], ndisc);
             if (feats) add<SC>(&g.ctrl->feat_reached, ndisc);
-            if (track && tst) {
-                atomicAdd(&tst->tverts, ndisc);
-                atomicAdd(reinterpret_cast<unsigned long long *>(&tst->tarcs), (unsigned long long)darcs);
-            } else if (track) {
-                add<SC>(&g.ctrl->qverts[(L + 1) % 3], ndisc);
-                add<SC>(&g.ctrl->qarcs[(L + 1) % 3], darcs);
+            if (SC != kGroup && track) {
+                atomicAdd(&st->tverts, ndisc);
+                atomicAdd(reinterpret_cast<unsigned long long *>(&st->tarcs), (unsigned long long)darcs);
             }
         }
         if (ctotal && qsb < 0) qbase = fetch_add<SC>(qout_count, ctotal);
@@ -554,9 +650,12 @@ __device__ __forceinline__ void bfs_emit(const DevGraph &g, int L, bool disc, in
     qsb = lane_value(qsb, 63);
     lsb = lane_value(lsb, 63);
     hsb = lane_value(hsb, 63);
-    int2 *qdst = qsb < 0 ? qout + qbase : st->items + qsb;
     const int qb = cincl - c;
-    for (int k = 0; k < c; ++k) qdst[qb + k] = make_int2(vbeg + k * kChunk, min(vbeg + (k + 1) * kChunk, vend));
+    for (int k = 0; k < c; ++k) {
+        const int2 item = make_int2(vbeg + k * kChunk, min(vbeg + (k + 1) * kChunk, vend));
+        if (qsb < 0) qout[qbase + qb + k] = item;
+        else st->items[qsb + qb + k] = item;
+    }
     if (light) {
         if (lsb < 0) g.list[0][(int)(uint32_t)lbase + mask_rank(lm)] = v;
         else st->light[lsb + mask_rank(lm)] = v;
@@ -573,8 +672,9 @@ __device__ __forceinline__ void bfs_emit(const DevGraph &g, int L, bool disc, in
 // staged output, then a coalesced copy (the stage counters start from zero
 // again).  Every thread of the workgroup calls it.
 template <int SC>
-__device__ void bfs_flush(const DevGraph &g, int L, BfsStage *st, bool counts, bool feats, bool track, int2 *qout,
+__device__ __forceinline__ void bfs_flush(const DevGraph &g, int L, bool counts, bool feats, bool track, int2 *qout,
                           int32_t *qout_count) {
+    BfsStage *st = bfs_stage();
     const int n = g.n;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -608,7 +708,8 @@ __device__ void bfs_flush(const DevGraph &g, int L, BfsStage *st, bool counts, b
 // the global counters, one atomic each (every thread of the workgroup calls
 // it; the next use of the tallies comes after a barrier).
 template <int SC>
-__device__ void bfs_tally_flush(const DevGraph &g, int L, BfsStage *tst) {
+__device__ __forceinline__ void bfs_tally_flush(const DevGraph &g, int L) {
+    BfsStage *tst = bfs_stage();
     __syncthreads();
     if (threadIdx.x == 0 && tst->tverts) {
         add<SC>(&g.ctrl->qverts[(L + 1) % 3], tst->tverts);
@@ -628,10 +729,10 @@ __device__ void bfs_tally_flush(const DevGraph &g, int L, BfsStage *tst) {
 // feats: tally the schedule's features.  Every thread of the workgroup calls
 // it.
 template <int SC>
-__device__ void bfs_level(const DevGraph &g, const Team &tm, int L, int cnt, bool feats, bool counts,
-                          bool track, bool lazy, BfsStage *st, BfsStage *tst, Tally &tl) {
-    const int2 *qin = g.q[L & 1];
-    int2 *qout = g.q[(L + 1) & 1];
+__device__ __forceinline__ void bfs_level(const DevGraph &g, const Team &tm, int L, int cnt, bool feats, bool counts,
+                          bool track, bool lazy, bool staged, Tally &tl) {
+    const int2 *qin = frontier(g, L);
+    int2 *qout = frontier(g, L + 1);
     int32_t *qout_count = &g.ctrl->qcount[(L + 1) % 3];
     const int lane = lane_id();
     const int64_t gwave = tm.wave();
@@ -688,14 +789,13 @@ __device__ void bfs_level(const DevGraph &g, const Team &tm, int L, int cnt, boo
                     disc = cas<SC>(&g.h[v], n, L + 1);
                 }
             }
-            bfs_emit<SC>(g, L, disc, v, vbeg, vend, ev, feats, counts, track, st, st ? nullptr : tst, qout,
-                         qout_count, tl);
+            bfs_emit<SC>(g, L, disc, v, vbeg, vend, ev, feats, counts, track, staged, qout, qout_count, tl);
         }
     }
-    if (st)
-        bfs_flush<SC>(g, L, st, counts, feats, track, qout, qout_count);
-    else if (track && tst)
-        bfs_tally_flush<SC>(g, L, tst);
+    if constexpr (SC != kGroup) {
+        if (staged) bfs_flush<SC>(g, L, counts, feats, track, qout, qout_count);
+        else if (track) bfs_tally_flush<SC>(g, L);
+    }
 }
 
 // One BFS level, bottom-up (the direction-optimising BFS): every vertex v
@@ -711,9 +811,8 @@ __device__ void bfs_level(const DevGraph &g, const Team &tm, int L, int cnt, boo
 // height makes one of them the discovery.  Output as in the top-down step.
 // Every thread of the workgroup calls it.
 template <int SC>
-__device__ void bfs_bottom_up(const DevGraph &g, const Team &tm, int L, bool feats, bool counts, BfsStage *st,
-                              Tally &tl) {
-    int2 *qout = g.q[(L + 1) & 1];
+__device__ __forceinline__ void bfs_bottom_up(const DevGraph &g, const Team &tm, int L, bool feats, bool counts, Tally &tl) {
+    int2 *qout = frontier(g, L + 1);
     int32_t *qout_count = &g.ctrl->qcount[(L + 1) % 3];
     const int lane = lane_id();
     const int n = g.n;
@@ -772,9 +871,242 @@ __device__ void bfs_bottom_up(const DevGraph &g, const Team &tm, int L, bool fea
             vend = g.row_ptr[v + 1];
             ev = get<SC>(&g.e[v]);
         }
-        bfs_emit<SC>(g, L, disc, v, vbeg, vend, ev, feats, counts, true, st, nullptr, qout, qout_count, tl);
+        bfs_emit<SC>(g, L, disc, v, vbeg, vend, ev, feats, counts, true, true, qout, qout_count, tl);
     }
-    if (st) bfs_flush<SC>(g, L, st, counts, feats, true, qout, qout_count);
+    bfs_flush<SC>(g, L, counts, feats, true, qout, qout_count);
+}
+
+// A run of BFS levels, top-down, whose frontier stays in LDS: every workgroup
+// of the team keeps the items of the vertices it discovered and expands them
+// in the next level, so a level needs no reservation in a shared list, no
+// reload of items or counters and only the barrier that also sums the next
+// frontier's size.  What bounds such a level is its chain of dependent loads
+// (arc and twin, head height and twin residual, compare-and-swap), not the
+// work.  Starts with the `cnt` items of level L in the global frontier; ends
+// when a level finds nothing, or with the next level's items back in the
+// global frontier when they hold more than `most` arcs, when a workgroup's share
+// outgrew its LDS or after a quarter of the barrier's wait limit.  Returns the
+// level it ended at; *ok is false when a barrier wait ran out.  Measured on an
+// XCD team of 32 workgroups, segmentation grids 256^2 / 512^2: 6.4 / 8.3 us a
+// level through the global frontier, 3.8 / 5.2 us in a run; push/relabel rounds
+// (pr_rounds, the same way) 8.4 / 14.8 us, in runs 5.3 / 10.0 us.
+template <int SC>
+__device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const LoopParams &p, int L, int cnt, int64_t most, bool feats,
+                       bool counts, bool dir, uint32_t &epoch, Tally &tl, bool *ok) {
+    RunStage *rs = run_stage();
+    const int t = threadIdx.x, lane = lane_id(), w = uniform(t >> 6), nw = blockDim.x >> 6;
+    const int n = g.n;
+    Ctrl *c = g.ctrl;
+    int2 *items = reinterpret_cast<int2 *>(rs->buf);
+    {
+        const int2 *q = frontier(g, L);
+        const int mine = (cnt - tm.rank + tm.size - 1) / tm.size;
+        for (int i = t; i < mine; i += blockDim.x) items[i] = get<SC>(&q[tm.rank + i * tm.size]);
+        if (t == 0) {
+            rs->icnt[0] = mine;
+            rs->spill = 0;
+            rs->found = 0;
+            rs->act = 0;
+            rs->arcs = 0;
+            rs->larcs = 0;
+        }
+    }
+    __syncthreads();
+    const uint64_t ts = wall_clock64();
+    constexpr int G = 8;  // lanes per item while every item of a wavefront's batch is short
+    const int gl = lane & (G - 1);
+    int cur = 0;
+    bool dump = false;
+    for (int it = 1;; ++it) {
+        if (t == 0 && tm.rank == 0) {
+            c->qcount[(L + 2) % 3] = 0;
+            c->qverts[(L + 2) % 3] = 0;
+            c->qarcs[(L + 2) % 3] = 0;
+        }
+        const int m = rs->icnt[cur], nxt = cur ^ 1;
+        const int2 *in = items + cur * kRunItems;
+        int found_arcs = 0;
+        // a wavefront takes 8 items at a time: 8 lanes each when none is long,
+        // otherwise all lanes over the items' arcs in turn
+        for (int base = w * G; base < m; base += nw * G) {
+            int beg = 0, len = 0;
+            if (base + lane / G < m) {
+                const int2 item = in[base + lane / G];
+                beg = item.x;
+                len = item.y - item.x;
+            }
+            const bool spread = __ballot(len > 4 * G) != 0;
+            int excl = 0, total = 0;
+            if (spread) {  // item k moves to lane k
+                const int b = __shfl(beg, (lane * G) & 63, 64), l = __shfl(len, (lane * G) & 63, 64);
+                beg = b;
+                len = lane < G ? l : 0;
+                const int incl = wave_incl_scan(len);
+                excl = incl - len;
+                total = lane_value(incl, 63);
+            }
+            for (int off = 0;; off += spread ? 64 : G) {
+                int a = beg + off + gl;
+                bool valid = off + gl < len;
+                if (spread) {
+                    if (off >= total) break;
+                    const bool here = len > 0 && excl >= off && excl < off + 64;
+                    const uint64_t starts = wave_or(here ? 1ull << (excl - off) : 0ull);
+                    const int before = __popcll(__ballot(len > 0 && excl < off));
+                    const int o = before + mask_rank(starts) + (int)((starts >> lane) & 1ull) - 1;
+                    a = __shfl(beg, o, 64) + (off + lane - __shfl(excl, o, 64));
+                    valid = off + lane < total;
+                } else if (__ballot(valid) == 0) {
+                    break;
+                }
+                // the compare-and-swap leaves first and its result is used after
+                // the loads beside it have left too
+                int v = -1, seen = -1, row0 = 0, row1 = 0;
+                int64_t ev = 0;
+                if (valid) {
+                    const int2 rec = get<SC>(&g.arc[a]);
+                    const int tw = g.twin[a];
+                    v = rec.x;
+                    const int hv = get<SC>(&g.h[v]);
+                    const int cft = get<SC>(cf_ptr(g.arc, tw));
+                    tl.bfs_a++;
+                    if (v != g.s && hv == n && cft > 0 && (!g.part_restrict || g.part[v] == g.part_want)) {
+                        seen = cas_seen<SC>(&g.h[v], n, L + 1);
+                        row0 = g.row_ptr[v];
+                        row1 = g.row_ptr[v + 1];
+                        ev = get<SC>(&g.e[v]);
+                    }
+                }
+                const bool disc = seen == n;
+                const uint64_t dm = __ballot(disc);
+                if (dm == 0) continue;
+                const int vbeg = row0, vdeg = row1 - row0;
+                // what the step found goes to the stage: frontier items, short
+                // and long active vertices, one reservation for the three
+                const int ni = disc ? n_items(vdeg) : 0;
+                int slot = mask_rank(dm), ntot = __popcll(dm);
+                if (__ballot(ni > 1) != 0) {
+                    const int ii = wave_incl_scan(ni);
+                    ntot = lane_value(ii, 63);
+                    slot = ii - ni;
+                }
+                const bool active = disc && v != g.t && ev > 0;
+                const bool light = active && vdeg <= kLightMaxDeg;
+                const bool heavy = active && vdeg > kLightMaxDeg && vdeg <= kHugeDeg;
+                const bool huge = active && vdeg > kHugeDeg;
+                const uint64_t lm = __ballot(light), hm = __ballot(heavy);
+                const int nl = __popcll(lm), nh = __popcll(hm);
+                int ib = 0;
+                uint64_t ab = 0;
+                if (lane == 0) {
+                    ib = atomicAdd(&rs->found, ntot);
+                    if (nl | nh)
+                        ab = atomicAdd(reinterpret_cast<unsigned long long *>(&rs->act),
+                                       ((unsigned long long)nh << 32) | (unsigned long long)nl);
+                }
+                ib = lane_value(ib, 0);
+                ab = (uint64_t)lane_value((int64_t)ab, 0);
+                const int lb = (int)(uint32_t)ab, hb = (int)(ab >> 32);
+                // what the stage has no room for goes straight to the global
+                // lists: from their bases (ig, lg, hg) less the stage's size
+                int ig = 0, lg = 0, hg = 0;
+                const bool full = ib + ntot > kRunItems || lb + nl > kStageCap || hb + nh > kStageCap;
+                if (full) {
+                    const int io = max(ib, kRunItems), lo = max(lb, kStageCap), ho = max(hb, kStageCap);
+                    if (lane == 0) {
+                        if (ib + ntot > io) {
+                            rs->spill = 1;
+                            ig = fetch_add<SC>(&c->qcount[(L + 1) % 3], ib + ntot - io);
+                        }
+                        if (lb + nl > lo) lg = fetch_add<SC>(&c->lst[0].light, lb + nl - lo);
+                        if (hb + nh > ho) hg = fetch_add<SC>(&c->lst[0].heavy, hb + nh - ho);
+                    }
+                    ig = lane_value(ig, 0) - io;
+                    lg = lane_value(lg, 0) - lo;
+                    hg = lane_value(hg, 0) - ho;
+                }
+                for (int k = 0; k < ni; ++k) {
+                    const int2 item = make_int2(vbeg + k * kChunk, min(vbeg + (k + 1) * kChunk, vbeg + vdeg));
+                    const int at = ib + slot + k;
+                    if (at < kRunItems) items[nxt * kRunItems + at] = item;
+                    else frontier(g, L + 1)[ig + at] = item;
+                }
+                if (light) {
+                    const int at = lb + mask_rank(lm);
+                    if (at < kStageCap) rs->aux[at] = v;
+                    else g.list[0][lg + at] = v;
+                }
+                if (heavy) {
+                    const int at = hb + mask_rank(hm);
+                    if (at < kStageCap) rs->aux[kStageCap + at] = v;
+                    else g.list[0][n - 1 - (hg + at)] = v;
+                }
+                const int su = wave_append1<SC>(&c->lst[0].huge, huge);  // rare: hubs only
+                if (huge) g.huge[0][su] = v;
+                if (counts && lane == 0) add<SC>(&g.hcount[L + 1], __popcll(dm));
+                if (feats) {
+                    if (lane == 0) add<SC>(&c->feat_reached, __popcll(dm));
+                    feature_tally<SC>(c, active, ev);
+                }
+                if (disc) {
+                    tl.bfs_v++;
+                    found_arcs += vdeg;
+                }
+            }
+        }
+        if (w * G < m) {
+            const int fa = wave_sum(found_arcs);  // below A < 2^31
+            if (lane == 0 && fa) atomicAdd(&rs->larcs, fa);
+        }
+        block_sync<SC>();
+        uint64_t mine = 0;
+        if (t == 0) {
+            const bool late = (it & 15) == 0 && (int64_t)(wall_clock64() - ts) > p.barrier_ticks / 4;
+            const int got = min(rs->found, kRunItems);
+            rs->icnt[nxt] = got;
+            rs->found = 0;
+            mine = (uint64_t)rs->larcs | ((uint64_t)(rs->spill || late) << 48);
+            rs->arcs += rs->larcs;
+            rs->larcs = 0;
+        }
+        const uint64_t sum = team_sum<SC>(c, tm, epoch, mine, p.barrier_ticks, ok);
+        if (!*ok) return L;
+        ++L;
+        cur = nxt;
+        dump = (sum >> 48) != 0 || (int64_t)sum > most;
+        if (dump || sum == 0) break;
+    }
+    // the active vertices found (and the items, when the run ends early) go
+    // to the global lists, one reservation each
+    const int nq = dump ? rs->icnt[cur] : 0;
+    const int nl = min((int)(uint32_t)rs->act, kStageCap), nh = min((int)(rs->act >> 32), kStageCap);
+    if (t == 0) {
+        if (nq) {
+            rs->base[0] = fetch_add<SC>(&c->qcount[L % 3], nq);
+            if (dir) add<SC>(&c->qverts[L % 3], nq);  // the direction rule takes an item for a vertex here
+        }
+        if (nl | nh) {
+            const int64_t b = fetch_add<SC>(reinterpret_cast<int64_t *>(&c->lst[0]), ((int64_t)nh << 32) | (int64_t)nl);
+            rs->base[1] = (int)(uint32_t)b;
+            rs->base[2] = (int)(b >> 32);
+        }
+    }
+    __syncthreads();
+    if (dir && t == 0 && rs->arcs) add<SC>(&c->run_arcs, rs->arcs);
+    int64_t qa = 0;
+    for (int i = t; i < nq; i += blockDim.x) {
+        const int2 item = items[cur * kRunItems + i];
+        frontier(g, L)[rs->base[0] + i] = item;
+        qa += item.y - item.x;
+    }
+    for (int i = t; i < nl; i += blockDim.x) g.list[0][rs->base[1] + i] = rs->aux[i];
+    for (int i = t; i < nh; i += blockDim.x) g.list[0][n - 1 - (rs->base[2] + i)] = rs->aux[kStageCap + i];
+    if (dir && nq) {
+        qa = wave_sum(qa);
+        if (lane == 0 && qa) add<SC>(&c->qarcs[L % 3], qa);
+    }
+    __syncthreads();  // the stage is free again
+    return L;
 }
 
 // ---------------------------------------------------------------------------
@@ -808,45 +1140,57 @@ struct Combine {
     int64_t sum[kCombine];
 };
 
+// The workgroup's one Combine.
+__device__ __forceinline__ Combine *combine_stage() {
+    __shared__ Combine s;
+    return &s;
+}
+
+// A round: appends to the next round's lists and first relabels are staged in
+// the workgroup's RunStage, half `par` of its list buffers.
 struct RoundCtx {
     int32_t *next;     // list of the next round
     int32_t *next_huge;  // its huge-vertex list
-    // the workgroup's staging of next-round appends and of first relabels
-    // (LDS; null: append directly)
-    int32_t *lbuf, *hbuf, *rbuf;
-    int32_t *lcnt, *hcnt, *rcnt;
-    Combine *comb;     // push sums of the workgroup (LDS), or null
     ListCtr *next_ctr;
     int32_t next_id;   // round id stamped into mark[] for that list
     int32_t phase_id;  // stamped into rmark[] on a vertex's first relabel
+    int32_t par;
+    bool comb;         // add pushes up per target first (combine_stage)
     bool use_gap;      // gap heuristic on
+    bool eager;        // a push lists its target whatever excess it had (see push_arc)
 };
 
-// Add v to the next round's list unless it is already there.
+// Put v (of deg arcs) on the next round's list.
 template <int SC>
-__device__ __forceinline__ void list_add(const DevGraph &g, const RoundCtx &rc, int v) {
-    const int deg = g.row_ptr[v + 1] - g.row_ptr[v];  // read alongside the exchange
-    if (xchg<SC>(&g.mark[v], rc.next_id) == rc.next_id) return;
+__device__ __forceinline__ void list_append(const DevGraph &g, const RoundCtx &rc, int v, int deg) {
+    RunStage *rs = run_stage();
     if (deg <= kLightMaxDeg) {
-        const int k = rc.lbuf ? atomicAdd(rc.lcnt, 1) : kStageCap;
+        const int k = atomicAdd(&rs->lcnt[rc.par], 1);
         if (k < kStageCap) {
-            rc.lbuf[k] = v;
-        } else {
-            const int slot = fetch_add<SC>(&rc.next_ctr->light, 1);
-            rc.next[slot] = v;
+            rs->buf[rc.par * kStageCap + k] = v;
+            return;
         }
+        const int slot = fetch_add<SC>(&rc.next_ctr->light, 1);
+        rc.next[slot] = v;
     } else if (deg <= kHugeDeg) {
-        const int k = rc.hbuf ? atomicAdd(rc.hcnt, 1) : kStageCap;
+        const int k = atomicAdd(&rs->hcnt[rc.par], 1);
         if (k < kStageCap) {
-            rc.hbuf[k] = v;
-        } else {
-            const int slot = fetch_add<SC>(&rc.next_ctr->heavy, 1);
-            rc.next[g.n - 1 - slot] = v;
+            rs->buf[(2 + rc.par) * kStageCap + k] = v;
+            return;
         }
+        const int slot = fetch_add<SC>(&rc.next_ctr->heavy, 1);
+        rc.next[g.n - 1 - slot] = v;
     } else {
         const int slot = fetch_add<SC>(&rc.next_ctr->huge, 1);
         rc.next_huge[slot] = v;
     }
+    rs->spill = 1;
+}
+
+// The same unless v is there already.
+template <int SC>
+__device__ __forceinline__ void list_add(const DevGraph &g, const RoundCtx &rc, int v, int deg) {
+    if (xchg<SC>(&g.mark[v], rc.next_id) != rc.next_id) list_append<SC>(g, rc, v, deg);
 }
 
 // First relabel of u in this phase: remember u for RemoveInvalidEdges.  Only
@@ -857,9 +1201,10 @@ __device__ __forceinline__ void note_relabel(const DevGraph &g, const RoundCtx &
     if (stamp != rc.phase_id) {
         stamp = rc.phase_id;
         g.rmark[u] = rc.phase_id;
-        const int k = rc.rbuf ? atomicAdd(rc.rcnt, 1) : kStageCap;
+        RunStage *rs = run_stage();
+        const int k = atomicAdd(&rs->rcnt, 1);
         if (k < kStageCap) {
-            rc.rbuf[k] = u;
+            rs->aux[k] = u;
         } else {
             const int slot = fetch_add<SC>(&g.ctrl->nrelab, 1);
             g.relab[slot] = u;
@@ -889,6 +1234,22 @@ __device__ __forceinline__ int relabel_to(const DevGraph &g, int u, int ho, int 
     return hn;
 }
 
+// Take a push of d into v into the workgroup's push sums; false when its slot
+// belongs to another vertex (or sums are off).
+__device__ __forceinline__ bool combine_push(const RoundCtx &rc, int v, int32_t d) {
+    if (!rc.comb) return false;
+    Combine *comb = combine_stage();
+    const int slot = (int)(((uint32_t)v * 2654435761u) >> (32 - kCombineBits));
+    int k = comb->key[slot];
+    if (k < 0) {
+        k = atomicCAS(&comb->key[slot], -1, v);
+        if (k < 0) k = v;
+    }
+    if (k != v) return false;
+    atomicAdd(reinterpret_cast<unsigned long long *>(&comb->sum[slot]), (unsigned long long)d);
+    return true;
+}
+
 // Push d from u along arc a to v = head(a).  Residual capacity moves to the
 // twin; excess moves from u to v except that the excess taken from u is
 // subtracted by the caller (one atomic per visit chunk).
@@ -899,22 +1260,11 @@ __device__ __forceinline__ void push_arc(const DevGraph &g, const RoundCtx &rc, 
     add<SC>(cf_ptr(g.arc, tw), d);
     if (v == g.t) {
         to_t += d;
-    } else {
-        if (rc.comb) {
-            const int slot = (int)(((uint32_t)v * 2654435761u) >> (32 - kCombineBits));
-            int k = rc.comb->key[slot];
-            if (k < 0) {
-                k = atomicCAS(&rc.comb->key[slot], -1, v);
-                if (k < 0) k = v;
-            }
-            if (k == v) {
-                atomicAdd(reinterpret_cast<unsigned long long *>(&rc.comb->sum[slot]), (unsigned long long)d);
-                return;
-            }
-        }
+    } else if (!combine_push(rc, v, d)) {
+        const int dv = g.row_ptr[v + 1] - g.row_ptr[v];  // read alongside the addition
         const int64_t old = fetch_add<SC>(&g.e[v], (int64_t)d);
         if (old < 0) tl.deliv += min((int64_t)d, -old);  // part of a deficit filled
-        if (old <= 0 && old + d > 0 && v != g.s) list_add<SC>(g, rc, v);
+        if (old <= 0 && old + d > 0 && v != g.s) list_add<SC>(g, rc, v, dv);
     }
 }
 
@@ -954,49 +1304,26 @@ __device__ __forceinline__ void scan_lowest(const DevGraph &g, int first, int la
     }
 }
 
-// Reductions over a group of G lanes, G = 8 or 64; lanes of other groups may
-// idle.
-template <int G>
-__device__ __forceinline__ int group_min(int x) {
-    static_assert(G == 8 || G == 64, "group width");
-    if constexpr (G == 64) return wave_min(x);
-    else return group8_min(x);
-}
-template <int G>
-__device__ __forceinline__ int64_t group_incl_scan(int64_t x) {
-    if constexpr (G == 64) {
-        return wave_incl_scan64(x);
-    } else {
-        // row shifts cross from one group into the next of the same row of 16:
-        // those lanes take nothing
-        const int gl = lane_id() & 7;
-        int64_t y = dpp<0x111, 0xf>((int64_t)0, x);
-        if (gl >= 1) x += y;
-        y = dpp<0x112, 0xf>((int64_t)0, x);
-        if (gl >= 2) x += y;
-        y = dpp<0x114, 0xf>((int64_t)0, x);
-        if (gl >= 4) x += y;
-        return x;
-    }
-}
-// value of the group's last lane
-template <int G>
-__device__ __forceinline__ int64_t group_last(int64_t x) {
-    if constexpr (G == 64) return lane_value(x, 63);
-    else return __shfl(x, 7, 8);
+// Inclusive scan over groups of 8 lanes, saturating at 2^32 - 1.  Row shifts
+// cross from one group into the next of the same row of 16: those lanes take
+// nothing.  Every lane of the wavefront must call it.
+__device__ __forceinline__ uint32_t group8_incl_scan_sat(uint32_t x) {
+    const int gl = lane_id() & 7;
+    const uint32_t y1 = (uint32_t)dpp<0x111, 0xf>(0, (int)x);
+    x = __builtin_elementwise_add_sat(x, gl >= 1 ? y1 : 0u);
+    const uint32_t y2 = (uint32_t)dpp<0x112, 0xf>(0, (int)x);
+    x = __builtin_elementwise_add_sat(x, gl >= 2 ? y2 : 0u);
+    const uint32_t y4 = (uint32_t)dpp<0x114, 0xf>(0, (int)x);
+    return __builtin_elementwise_add_sat(x, gl >= 4 ? y4 : 0u);
 }
 
-// A group of G lanes (G = 64: a wavefront) visits vertex u: the lanes scan
-// its arcs G at a time for the lowest residual neighbour height, and the push
-// pass hands the excess to the lowest arcs in arc order with a prefix sum of
-// their residual capacities over the group.  u < 0: the group idles.  Every
-// loop bound is uniform inside the group, so its lanes stay converged and the
-// shuffles of width G stay inside it.  Returns relabels (on the group's lane
-// 0).
-template <int SC, int G>
-__device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx &rc, Tally &tl,
-                               int64_t &to_t) {
-    const int gl = lane_id() & (G - 1);
+// A wavefront visits vertex u: the lanes scan its arcs 64 at a time for the
+// lowest residual neighbour height, and the push pass hands the excess to the
+// lowest arcs in arc order with a prefix sum of their residual capacities.
+// u < 0: idle.  Returns relabels (on lane 0).
+template <int SC>
+__device__ __forceinline__ int discharge_wave(const DevGraph &g, int u, int kc, const RoundCtx &rc, Tally &tl, int64_t &to_t) {
+    const int lane = lane_id();
     if (u < 0) return 0;
     const int n = g.n;
     const int beg = g.row_ptr[u], end = g.row_ptr[u + 1];
@@ -1004,7 +1331,7 @@ __device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx 
     int32_t stamp = get<SC>(&g.rmark[u]);  // phase of u's last first-relabel (read with the rest)
     int relabels = 0;
     if (rc.use_gap && hu < n && hu > ld<SC>(&g.ctrl->gap)) {  // above a gap: cut off
-        if (gl == 0) {
+        if (lane == 0) {
             add<SC>(&g.hcount[hu], -1);
             g.h[u] = n;
         }
@@ -1012,21 +1339,20 @@ __device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx 
     }
     // excess of u as last seen: loaded once, then taken from the returning
     // subtraction of what u pushed (incoming pushes only ever add to it)
-    int64_t eu = 0;
-    eu = ld<SC>(&g.e[u]);  // every lane: one request, no shuffle
+    int64_t eu = lane_value(ld<SC>(&g.e[u]), 0);
     for (int cyc = 0; cyc < kc && hu < n; ++cyc) {
         if (eu <= 0) break;
-        if (gl == 0) tl.pr_cyc++;
+        if (lane == 0) tl.pr_cyc++;
         int hmin = INT32_MAX;
         int64_t cmin = 0;  // not needed here
-        scan_lowest<SC>(g, beg + gl, end, G, hmin, cmin);
-        if (gl == 0) tl.pr_a += end - beg;
-        hmin = group_min<G>(hmin);
+        scan_lowest<SC>(g, beg + lane, end, 64, hmin, cmin);
+        if (lane == 0) tl.pr_a += end - beg;
+        hmin = wave_min(hmin);
         if (hmin == INT32_MAX) break;
         if (hu > hmin) {
             int64_t sent = 0, now = eu;
-            for (int base = beg; base < end && sent < eu; base += G) {
-                const int a = base + gl;
+            for (int base = beg; base < end && sent < eu; base += 64) {
+                const int a = base + lane;
                 int64_t c = 0;
                 int v = -1, tw = 0;
                 if (a < end) {
@@ -1037,35 +1363,179 @@ __device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx 
                         v = r.x;
                     }
                 }
-                // inclusive prefix sum of c over the group, in arc order
-                const int64_t incl = group_incl_scan<G>(c);
+                const int64_t incl = wave_incl_scan64(c);  // in arc order
                 const int64_t room = eu - sent;
                 const int64_t excl = incl - c;
                 const int64_t d = (c > 0 && excl < room) ? min(c, room - excl) : 0;
-                const int64_t tot = min(group_last<G>(incl), room);
-                // the group's total leaves u before its lanes push it on, so
-                // the returning subtraction overlaps the pushes
-                if (gl == 0 && tot > 0) now = fetch_add<SC>(&g.e[u], -tot) - tot;
+                const int64_t tot = min(lane_value(incl, 63), room);
+                // the total leaves u before the lanes push it on, so the
+                // returning subtraction overlaps the pushes
+                if (lane == 0 && tot > 0) now = fetch_add<SC>(&g.e[u], -tot) - tot;
                 if (d > 0) {
                     push_arc<SC>(g, rc, a, tw, v, (int32_t)d, to_t, tl);
                     tl.push++;
                 }
                 sent += tot;
             }
-            eu = __shfl(now, 0, G);
+            eu = lane_value(now, 0);
         } else {
             int hn = 0;
-            if (gl == 0) {
+            if (lane == 0) {
                 hn = relabel_to<SC>(g, u, hu, hmin, rc.use_gap);
                 tl.relabel++;
                 note_relabel<SC>(g, rc, u, stamp);
             }
-            hu = __shfl(hn, 0, G);
+            hu = lane_value(hn, 0);
             relabels++;
         }
     }
-    if (gl == 0 && hu < n && eu > 0) list_add<SC>(g, rc, u);
-    return gl == 0 ? relabels : 0;
+    if (lane == 0 && hu < n && eu > 0) list_add<SC>(g, rc, u, end - beg);
+    return lane == 0 ? relabels : 0;
+}
+
+// Groups of 8 lanes visit vertices of at most 8 * K arcs, one each (u < 0: the
+// group idles): the cycle of discharge_wave with the arcs, twins and head
+// heights held in registers between the scan and the pushes.  What bounds a
+// visit in a short list is its chain of dependent steps: bounds and state
+// (loaded by the caller), arcs, head heights, atomics.  So pushes and relabels
+// of different groups issue their atomics before anyone waits for a result,
+// and with rc.eager a push stamps its target's mark beside the addition to
+// its excess instead of after it.  Then the target is listed whatever excess
+// it had: one that empties in its own visit of this round, or is still in
+// deficit, is visited in vain in the next.  The group's last lane acts for
+// the group (a scan's total is already there).  Every lane of the wavefront
+// calls it.  Returns relabels (on the groups' last lanes).
+template <int SC, int K>
+__device__ __forceinline__ int visit_light(const DevGraph &g, int u, int beg, int end, int hu, int64_t eu,
+                                           int32_t stamp, int kc, const RoundCtx &rc, Tally &tl, int64_t &to_t) {
+    constexpr int G = 8;
+    const int gl = lane_id() & (G - 1);
+    const bool lead = gl == G - 1;
+    const int n = g.n;
+    int relabels = 0;
+    bool spent = false;   // no residual arc left: the cycles end
+    bool listed = false;  // already on the next list
+    for (int cyc = 0; cyc < kc; ++cyc) {
+        const bool act = hu < n && eu > 0 && !spent;  // alike in a group
+        if (__ballot(act) == 0) break;
+        int v[K], c[K], tw[K], hv[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int a = beg + k * G + gl;
+            c[k] = v[k] = tw[k] = 0;
+            if (act && a < end) {
+                const int2 r = get<SC>(&g.arc[a]);
+                tw[k] = g.twin[a];
+                v[k] = r.x;
+                c[k] = r.y;
+                if (cyc > 0) c[k] = max(0, ld<SC>(cf_ptr(g.arc, a)));
+            }
+        }
+        int hmin = INT32_MAX;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            hv[k] = c[k] > 0 ? get<SC>(&g.h[v[k]]) : INT32_MAX;
+            hmin = min(hmin, hv[k]);
+        }
+        hmin = group8_min(hmin);
+        const bool push = act && hmin < hu;
+        const bool lift = act && !push && hmin != INT32_MAX;
+        spent = act && hmin == INT32_MAX;
+        if (act && lead) {
+            tl.pr_cyc++;
+            tl.pr_a += end - beg;
+        }
+        int64_t left = eu, now = eu;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (k > 0 && __ballot(push && beg + k * G < end) == 0) break;
+            // shares in arc order; the scan saturates at 2^32 - 1, above any room
+            const uint32_t room = (uint32_t)min(left, (int64_t)INT32_MAX);
+            const uint32_t ck = push && hv[k] == hmin ? (uint32_t)c[k] : 0u;
+            const uint32_t incl = group8_incl_scan_sat(ck);
+            const uint32_t before = (uint32_t)dpp<0x111, 0xf>(0, (int)incl);
+            const uint32_t excl = gl == 0 ? 0u : before;
+            const uint32_t d = excl < room ? min(ck, room - excl) : 0u;
+            const int64_t tot = (int64_t)min(incl, room);  // the group's on its last lane
+            // all atomics leave before any result is used
+            const bool out = d > 0, pay = lead && tot > 0, up = k == 0 && lift && lead;
+            const bool side = out && v[k] != g.t && !combine_push(rc, v[k], (int32_t)d);
+            int64_t had = 0, old = 1;
+            int32_t seen = rc.next_id, seen_u = rc.next_id;
+            int row0 = 0, row1 = 0;
+            if (pay) had = fetch_add<SC>(&g.e[u], -tot);
+            if (side) {
+                old = fetch_add<SC>(&g.e[v[k]], (int64_t)d);
+                if (rc.eager) seen = xchg<SC>(&g.mark[v[k]], rc.next_id);
+                row0 = g.row_ptr[v[k]];
+                row1 = g.row_ptr[v[k] + 1];
+            }
+            if (up) {
+                hu = relabel_to<SC>(g, u, hu, hmin, rc.use_gap);
+                // u keeps its excess, so after the last cycle it is listed
+                if (cyc == kc - 1 && hu < n) seen_u = xchg<SC>(&g.mark[u], rc.next_id);
+                tl.relabel++;
+                relabels++;
+                note_relabel<SC>(g, rc, u, stamp);
+            }
+            if (out) {
+                add<SC>(cf_ptr(g.arc, beg + k * G + gl), -(int32_t)d);
+                add<SC>(cf_ptr(g.arc, tw[k]), (int32_t)d);
+                tl.push++;
+                if (v[k] == g.t) to_t += d;
+            }
+            if (side) {
+                if (old < 0) tl.deliv += min((int64_t)d, -old);  // part of a deficit filled
+                if (v[k] != g.s) {
+                    if (rc.eager) {
+                        if (seen != rc.next_id) list_append<SC>(g, rc, v[k], row1 - row0);
+                    } else if (old <= 0 && old + d > 0) {
+                        list_add<SC>(g, rc, v[k], row1 - row0);
+                    }
+                }
+            }
+            if (up && cyc == kc - 1) {
+                if (seen_u != rc.next_id) list_append<SC>(g, rc, u, end - beg);
+                listed = true;
+            }
+            if (pay) now = had - tot;
+            if (K > 1) left -= __shfl(tot, G - 1, G);
+        }
+        eu = now;
+        if (kc > 1) {
+            eu = __shfl(eu, G - 1, G);
+            hu = __shfl(hu, G - 1, G);
+        }
+    }
+    if (lead && !listed && hu < n && eu > 0) list_add<SC>(g, rc, u, end - beg);
+    return relabels;
+}
+
+// Groups of 8 lanes visit vertices of at most kLightMaxDeg arcs (u < 0: the
+// group idles); a wavefront whose lists all hold at most 8 arcs takes the
+// shorter code.  Every lane of the wavefront calls it.
+template <int SC>
+__device__ __forceinline__ int discharge_light(const DevGraph &g, int u, int kc, const RoundCtx &rc, Tally &tl,
+                                               int64_t &to_t) {
+    int beg = 0, end = 0, hu = g.n;
+    int32_t stamp = 0;
+    int64_t eu = 0;
+    if (u >= 0) {
+        beg = g.row_ptr[u];
+        end = g.row_ptr[u + 1];
+        hu = get<SC>(&g.h[u]);
+        stamp = get<SC>(&g.rmark[u]);
+        eu = ld<SC>(&g.e[u]);
+        if (rc.use_gap && hu < g.n && hu > ld<SC>(&g.ctrl->gap)) {  // above a gap: cut off
+            if ((lane_id() & 7) == 7) {
+                add<SC>(&g.hcount[hu], -1);
+                g.h[u] = g.n;
+            }
+            hu = g.n;
+        }
+    }
+    if (__ballot(end - beg > 8) == 0) return visit_light<SC, 1>(g, u, beg, end, hu, eu, stamp, kc, rc, tl, to_t);
+    return visit_light<SC, kLightMaxDeg / 8>(g, u, beg, end, hu, eu, stamp, kc, rc, tl, to_t);
 }
 
 // A wavefront visits vertex u by walking its arcs in arc order, 64 at a
@@ -1079,7 +1549,7 @@ __device__ int discharge_group(const DevGraph &g, int u, int kc, const RoundCtx 
 // relabel left steep is pushed to like any downhill head.  Every lane of the
 // wavefront calls it with the same u (u < 0: idle).  Returns relabels (lane 0).
 template <int SC>
-__device__ int discharge_walk(const DevGraph &g, int u, int kc, const RoundCtx &rc, Tally &tl, int64_t &to_t) {
+__device__ __forceinline__ int discharge_walk(const DevGraph &g, int u, int kc, const RoundCtx &rc, Tally &tl, int64_t &to_t) {
     const int lane = lane_id();
     if (u < 0) return 0;
     const int n = g.n;
@@ -1151,7 +1621,7 @@ __device__ int discharge_walk(const DevGraph &g, int u, int kc, const RoundCtx &
         hu = lane_value(hn, 0);
         relabels++;
     }
-    if (lane == 0 && hu < n && eu > 0) list_add<SC>(g, rc, u);
+    if (lane == 0 && hu < n && eu > 0) list_add<SC>(g, rc, u, end - beg);
     return lane == 0 ? relabels : 0;
 }
 
@@ -1165,12 +1635,12 @@ constexpr int kLightGroup = 8;
 // chunks' capacities at the overall lowest height h^ split the excess in arc
 // order, so every wavefront then pushes its share along its own chunk without
 // workgroup barriers.  Without races this makes exactly the pushes of one
-// pass over all arcs in arc order (the same as discharge_group); a capacity
+// pass over all arcs in arc order (the same as discharge_wave); a capacity
 // or height that changed since the scan only leaves excess behind.  Every
 // thread of the workgroup calls it with the same u; all decisions are
 // uniform.
 template <int SC>
-__device__ int discharge_block(const DevGraph &g, int u, int kc, const RoundCtx &rc, Tally &tl,
+__device__ __forceinline__ int discharge_block(const DevGraph &g, int u, int kc, const RoundCtx &rc, Tally &tl,
                                int64_t &to_t) {
     __shared__ int s_min[32];
     __shared__ int64_t s_sum[32];
@@ -1270,7 +1740,7 @@ __device__ int discharge_block(const DevGraph &g, int u, int kc, const RoundCtx 
             relabels++;
         }
     }
-    if (t == 0 && hu < n && eu > 0) list_add<SC>(g, rc, u);
+    if (t == 0 && hu < n && eu > 0) list_add<SC>(g, rc, u, end - beg);
     return t == 0 ? relabels : 0;
 }
 
@@ -1282,7 +1752,7 @@ __device__ int discharge_block(const DevGraph &g, int u, int kc, const RoundCtx 
 // Every thread of the workgroup calls it with the same u; all decisions are
 // uniform.
 template <int SC>
-__device__ int discharge_block_walk(const DevGraph &g, int u, int kc, const RoundCtx &rc, Tally &tl,
+__device__ __forceinline__ int discharge_block_walk(const DevGraph &g, int u, int kc, const RoundCtx &rc, Tally &tl,
                                     int64_t &to_t) {
     __shared__ int64_t s_wsum[32];
     __shared__ int s_wmin[32];
@@ -1377,163 +1847,212 @@ __device__ int discharge_block_walk(const DevGraph &g, int u, int kc, const Roun
         __syncthreads();
         relabels++;
     }
-    if (t == 0 && hu < n && eu > 0) list_add<SC>(g, rc, u);
+    if (t == 0 && hu < n && eu > 0) list_add<SC>(g, rc, u, end - beg);
     return t == 0 ? relabels : 0;
 }
 
-// Excess pushed into t by the lanes of a wavefront, added with one atomic
-// (topology-driven rounds; data-driven rounds sum per workgroup).
+// Copy the workgroup's staged appends (half rc.par) into the next round's list
+// and the phase's relabelled list, one reservation per list and workgroup, and
+// add the workgroup's counters (acc: excess into t, relabels, pushes,
+// deliveries into deficits).  Every thread of the workgroup calls it.
 template <int SC>
-__device__ __forceinline__ void flush_to_t(const DevGraph &g, int64_t &to_t) {
-    const int64_t s = wave_sum(to_t);
-    if (lane_id() == 0 && s) {
-        add<SC>(&g.e[g.t], s);
-        add<SC>(&g.ctrl->phase_deliv, s);
-    }
-    to_t = 0;
-}
-
-template <int SC>
-__device__ __forceinline__ void flush_relabels(Ctrl *c, int64_t &rl, int64_t pushes, int64_t deliv) {
-    const int64_t s = wave_sum(rl);
-    const int64_t p = wave_sum(pushes);
-    const int64_t dv = wave_sum(deliv);
-    if (lane_id() == 0 && s) add<SC>(&c->phase_relabels, s);
-    if (lane_id() == 0 && p) add<SC>(&c->phase_pushes, p);
-    if (lane_id() == 0 && dv) add<SC>(&c->phase_deliv, dv);
-    rl = 0;
-}
-
-// Copy the workgroup's staged appends into the next round's list and the
-// phase's relabelled list: one reservation per list and workgroup; add the workgroup's round counters
-// (acc: excess into t, relabels, pushes, deliveries into deficits).  Every
-// thread of the workgroup calls it.
-template <int SC>
-__device__ void flush_stage(const DevGraph &g, const RoundCtx &rc, const int64_t *acc) {
-    __shared__ int s_lb, s_hb, s_rb;
+__device__ __forceinline__ void flush_stage(const DevGraph &g, const RoundCtx &rc) {
+    RunStage *rs = run_stage();
     __syncthreads();
-    const int nl = min(*rc.lcnt, kStageCap), nh = min(*rc.hcnt, kStageCap), nr = min(*rc.rcnt, kStageCap);
+    const int nl = min(rs->lcnt[rc.par], kStageCap), nh = min(rs->hcnt[rc.par], kStageCap);
+    const int nr = min(rs->rcnt, kStageCap);
     if (threadIdx.x == 0) {
-        s_lb = nl ? fetch_add<SC>(&rc.next_ctr->light, nl) : 0;
-        s_hb = nh ? fetch_add<SC>(&rc.next_ctr->heavy, nh) : 0;
-        s_rb = nr ? fetch_add<SC>(&g.ctrl->nrelab, nr) : 0;
+        rs->base[0] = nl ? fetch_add<SC>(&rc.next_ctr->light, nl) : 0;
+        rs->base[1] = nh ? fetch_add<SC>(&rc.next_ctr->heavy, nh) : 0;
+        rs->base[2] = nr ? fetch_add<SC>(&g.ctrl->nrelab, nr) : 0;
         Ctrl *c = g.ctrl;
+        const int64_t *acc = rs->acc;
         if (acc[0]) add<SC>(&g.e[g.t], acc[0]);
         if (acc[0] + acc[3]) add<SC>(&c->phase_deliv, acc[0] + acc[3]);
         if (acc[1]) add<SC>(&c->phase_relabels, acc[1]);
         if (acc[2]) add<SC>(&c->phase_pushes, acc[2]);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < nl; i += blockDim.x) rc.next[s_lb + i] = rc.lbuf[i];
-    for (int i = threadIdx.x; i < nh; i += blockDim.x) rc.next[g.n - 1 - (s_hb + i)] = rc.hbuf[i];
-    for (int i = threadIdx.x; i < nr; i += blockDim.x) g.relab[s_rb + i] = rc.rbuf[i];
+    const int32_t *light = rs->buf + rc.par * kStageCap, *heavy = rs->buf + (2 + rc.par) * kStageCap;
+    for (int i = threadIdx.x; i < nl; i += blockDim.x) rc.next[rs->base[0] + i] = light[i];
+    for (int i = threadIdx.x; i < nh; i += blockDim.x) rc.next[g.n - 1 - (rs->base[1] + i)] = heavy[i];
+    for (int i = threadIdx.x; i < nr; i += blockDim.x) g.relab[rs->base[2] + i] = rs->aux[i];
+    __syncthreads();  // the stage is free again
 }
 
 // Add the workgroup's push sums to the targets' excess (every thread of the
 // workgroup calls it); a target whose excess turns positive joins the next
 // round's list, as after a single push.
 template <int SC>
-__device__ void flush_combine(const DevGraph &g, const RoundCtx &rc, Tally &tl) {
+__device__ __forceinline__ void flush_combine(const DevGraph &g, const RoundCtx &rc, Tally &tl) {
+    Combine *comb = combine_stage();
     __syncthreads();
     for (int i = threadIdx.x; i < kCombine; i += blockDim.x) {
-        const int v = rc.comb->key[i];
+        const int v = comb->key[i];
         if (v < 0) continue;
-        const int64_t d = rc.comb->sum[i];
-        rc.comb->key[i] = -1;
-        rc.comb->sum[i] = 0;
+        const int64_t d = comb->sum[i];
+        comb->key[i] = -1;
+        comb->sum[i] = 0;
         const int64_t old = fetch_add<SC>(&g.e[v], d);
         if (old < 0) tl.deliv += min(d, -old);
-        if (old <= 0 && old + d > 0 && v != g.s) list_add<SC>(g, rc, v);
+        if (old <= 0 && old + d > 0 && v != g.s) list_add<SC>(g, rc, v, g.row_ptr[v + 1] - g.row_ptr[v]);
     }
 }
 
-// One data-driven round over list rd: short lists by lane, long ones by
-// wavefronts that take the next vertex from a shared counter.
+// One round, or a run of rounds, of push/relabel.
+//
+// A round visits list r: a group of 8 lanes per short arc list, a workgroup
+// per huge one, a wavefront per other long one, dealt out round-robin (no
+// shared counter for thousands of wavefronts to contend on).  Topology-driven
+// rounds visit every vertex instead (idle when inactive).
+//
+// A run (run = true; lists of round r, none huge) is consecutive rounds whose
+// lists stay in LDS: every workgroup of the team keeps the vertices that its
+// visits put on the next round's list and visits them in that round, and a
+// round ends with the barrier that also sums list sizes, relabels and
+// deliveries, with which the phase's limits are tested as between single
+// rounds.  It ends with the phase (*done and its *reason), or with the next
+// lists back in global memory when they hold more than `most` vertices, a huge
+// one, more than a workgroup's LDS, or after a quarter of the barrier's wait
+// limit.  The totals (excess into t, relabels, pushes, deliveries, relabelled
+// vertices) are added at the end of the round or run.  Returns the number of
+// the next round; *ok is false when a barrier wait ran out.
+struct PhaseLimits {
+    int64_t budget;
+    int round_cap, stall;
+};
 template <int SC, bool WALK>
-__device__ void pr_round(const DevGraph &g, const Team &tm, int rd, int nl, int nh, int nu, int kc,
-                         const RoundCtx &rc0, Combine *comb, Tally &tl) {
-    const int64_t gtid = tm.tid();
-    const int64_t stride = tm.nthreads();
-    __shared__ int32_t s_lbuf[kStageCap], s_hbuf[kStageCap], s_rbuf[kStageCap];
-    __shared__ int32_t s_lcnt, s_hcnt, s_rcnt;
-    __shared__ int64_t s_acc[4];  // the workgroup's excess into t, relabels, pushes, deliveries
-    if (threadIdx.x == 0) s_lcnt = s_hcnt = s_rcnt = 0;
-    if (threadIdx.x < 4) s_acc[threadIdx.x] = 0;
+__device__ __forceinline__ int pr_rounds(const DevGraph &g, const Team &tm, const LoopParams &p, const PhaseLimits &lim, bool run,
+                         int32_t rbase, int r, int nl, int nh, int nu, int64_t relabels, int most, int *reason,
+                         bool *done, int *last_change, uint32_t &epoch, Tally &tl, bool *ok) {
+    constexpr int G = 8;  // lanes per vertex with a short arc list
+    const int t = threadIdx.x, lane = lane_id(), w = uniform(t >> 6), nw = blockDim.x >> 6;
+    const bool topology = p.mode == 1;
+    const bool comb = SC != kGroup && p.combine;
+    Ctrl *c = g.ctrl;
+    RunStage *rs = run_stage();
+    {
+        const int32_t *lst = round_list(g, r % 3);
+        const int ml = run ? (nl - tm.rank + tm.size - 1) / tm.size : 0;
+        const int mh = run ? (nh - tm.rank + tm.size - 1) / tm.size : 0;
+        for (int i = t; i < ml; i += blockDim.x) rs->buf[i] = get<SC>(&lst[tm.rank + i * tm.size]);
+        for (int i = t; i < mh; i += blockDim.x)
+            rs->buf[2 * kStageCap + i] = get<SC>(&lst[g.n - 1 - (tm.rank + i * tm.size)]);
+        if (t == 0) {
+            rs->lcnt[0] = ml;
+            rs->hcnt[0] = mh;
+            rs->lcnt[1] = rs->hcnt[1] = rs->rcnt = 0;
+            rs->spill = rs->relabels = rs->deliv = 0;
+        }
+        if (t < 4) rs->acc[t] = 0;
+    }
     __syncthreads();
-    RoundCtx rc = rc0;
-    rc.lbuf = s_lbuf;
-    rc.hbuf = s_hbuf;
-    rc.rbuf = s_rbuf;
-    rc.lcnt = &s_lcnt;
-    rc.hcnt = &s_hcnt;
-    rc.rcnt = &s_rcnt;
-    rc.comb = comb;
-    const int32_t *lst = g.list[rd];
-    int64_t to_t = 0, rl = 0;
+    const uint64_t ts = run ? wall_clock64() : 0;
     const uint32_t push0 = tl.push;
-    {
-        const int64_t grp = gtid / kLightGroup, ngrp = stride / kLightGroup;
-        const int64_t trips = (nl + ngrp - 1) / ngrp;  // the same for every group
-        for (int64_t k = 0, i = grp; k < trips; ++k, i += ngrp)
-            rl += discharge_group<SC, kLightGroup>(g, i < nl ? get<SC>(&lst[i]) : -1, kc, rc, tl, to_t);
-    }
-    // huge arc lists: one workgroup per vertex, handed out by a counter
-    if (nu > 0) {
-        __shared__ int s_idx;
-        const int32_t *hl = g.huge[rd];
-        for (;;) {
-            if (threadIdx.x == 0) s_idx = fetch_add<SC>(&g.ctrl->lst[rd].hgrab, 1);
-            __syncthreads();
-            const int idx = s_idx;
-            __syncthreads();
-            if (idx >= nu) break;
-            if constexpr (WALK) rl += discharge_block_walk<SC>(g, get<SC>(&hl[idx]), kc, rc, tl, to_t);
-            else rl += discharge_block<SC>(g, get<SC>(&hl[idx]), kc, rc, tl, to_t);
+    int64_t to_t = 0, all_deliv = 0, all_relabels = 0;
+    int cur = 0;
+    bool dump = true;
+    for (int it = 1;; ++it) {
+        if (t == 0 && tm.rank == 0) c->lst[(r + 2) % 3] = ListCtr{};
+        const int nxt = cur ^ 1, wr = (r + 1) % 3;
+        const RoundCtx rc{round_list(g, wr), huge_list(g, wr), &c->lst[wr], rbase + r + 1, rbase, nxt, comb, p.use_gap != 0,
+                          run && !comb};
+        const int32_t *lst = round_list(g, r % 3);
+        int rl = 0;
+        const int64_t to_t0 = to_t;
+        {
+            const int *light = rs->buf + cur * kStageCap;
+            const int ml = run ? rs->lcnt[cur] : topology ? g.n : nl;
+            const int64_t step = (run ? nw : tm.nwaves()) * (64 / G);
+            for (int64_t base = (run ? w : tm.wave()) * (64 / G); base < ml; base += step) {
+                const int i = (int)base + lane / G;
+                int u = -1;
+                if (i < ml) {
+                    u = run ? light[i] : topology ? i : get<SC>(&lst[i]);
+                    if (topology && (u == g.s || u == g.t || g.row_ptr[u + 1] - g.row_ptr[u] > kLightMaxDeg)) u = -1;
+                }
+                rl += discharge_light<SC>(g, u, p.kc, rc, tl, to_t);
+            }
         }
-    }
-    // long arc lists: one wavefront per vertex, dealt out round-robin (no
-    // shared counter for thousands of wavefronts to contend on)
-    for (int64_t i = tm.wave(); i < nh; i += tm.nwaves()) {
-        const int u = get<SC>(&lst[g.n - 1 - i]);
-        if constexpr (WALK) rl += discharge_walk<SC>(g, u, kc, rc, tl, to_t);
-        else rl += discharge_group<SC, 64>(g, u, kc, rc, tl, to_t);
-    }
-    if (comb) flush_combine<SC>(g, rc, tl);
-    // the round's counters: summed over the workgroup, one atomic each
-    {
-        const int64_t v[4] = {wave_sum(to_t), wave_sum(rl), wave_sum((int64_t)(tl.push - push0)),
-                              wave_sum(tl.deliv)};
-        if (lane_id() == 0)
-            for (int k = 0; k < 4; ++k)
-                if (v[k]) atomicAdd(reinterpret_cast<unsigned long long *>(&s_acc[k]), (unsigned long long)v[k]);
+        if (nu > 0 && !topology) {  // handed out by a counter (heavy_all holds them too)
+            __shared__ int s_idx;
+            const int32_t *hl = huge_list(g, r % 3);
+            for (;;) {
+                if (t == 0) s_idx = fetch_add<SC>(&c->lst[r % 3].hgrab, 1);
+                __syncthreads();
+                const int idx = s_idx;
+                __syncthreads();
+                if (idx >= nu) break;
+                if constexpr (WALK) rl += discharge_block_walk<SC>(g, get<SC>(&hl[idx]), p.kc, rc, tl, to_t);
+                else rl += discharge_block<SC>(g, get<SC>(&hl[idx]), p.kc, rc, tl, to_t);
+            }
+        }
+        {
+            const int *heavy = rs->buf + (2 + cur) * kStageCap;
+            const int mh = run ? rs->hcnt[cur] : topology ? g.n_heavy_all : nh;
+            const int64_t step = run ? nw : tm.nwaves();
+            for (int64_t i = run ? w : tm.wave(); i < mh; i += step) {
+                const int u = uniform(run ? heavy[i] : topology ? g.heavy_all[i] : get<SC>(&lst[g.n - 1 - i]));
+                if constexpr (WALK) rl += discharge_walk<SC>(g, u, p.kc, rc, tl, to_t);
+                else rl += discharge_wave<SC>(g, u, p.kc, rc, tl, to_t);
+            }
+        }
+        if (comb) flush_combine<SC>(g, rc, tl);
+        all_relabels += rl;
+        all_deliv += tl.deliv;
+        if (!run) {
+            tl.deliv = 0;
+            ++r;
+            cur = nxt;
+            break;
+        }
+        const int s = wave_sum(rl);
+        if (lane == 0 && s) atomicAdd(&rs->relabels, s);
+        if (__ballot(to_t != to_t0 || tl.deliv != 0) != 0 && lane == 0) rs->deliv = 1;
         tl.deliv = 0;
-    }
-    flush_stage<SC>(g, rc, s_acc);
-}
-
-// One topology-driven round: every vertex is visited (idle when inactive).
-template <int SC>
-__device__ void pr_round_topology(const DevGraph &g, const Team &tm, int kc, const RoundCtx &rc,
-                                  Tally &tl) {
-    const int64_t gtid = tm.tid();
-    const int64_t stride = tm.nthreads();
-    int64_t to_t = 0, rl = 0;
-    const uint32_t push0 = tl.push;
-    {
-        const int64_t grp = gtid / kLightGroup, ngrp = stride / kLightGroup;
-        const int64_t trips = ((int64_t)g.n + ngrp - 1) / ngrp;
-        for (int64_t k = 0, i = grp; k < trips; ++k, i += ngrp) {
-            int u = (int)i;
-            if (i >= g.n || u == g.s || u == g.t || g.row_ptr[u + 1] - g.row_ptr[u] > kLightMaxDeg) u = -1;
-            rl += discharge_group<SC, kLightGroup>(g, u, kc, rc, tl, to_t);
+        block_sync<SC>();
+        uint64_t mine = 0;
+        if (t == 0) {
+            const bool late = (it & 15) == 0 && (int64_t)(wall_clock64() - ts) > p.barrier_ticks / 4;
+            const int list = min(rs->lcnt[nxt], kStageCap) + min(rs->hcnt[nxt], kStageCap);
+            // relabels are capped so that a team's sum fits its 20 bits (only
+            // the budget test reads them)
+            mine = (uint64_t)min(rs->relabels, (1 << 20) / tm.size - 1) | ((uint64_t)list << 20) |
+                   ((uint64_t)rs->deliv << 40) | ((uint64_t)(rs->spill || late) << 48);
+            rs->lcnt[cur] = rs->hcnt[cur] = rs->relabels = rs->deliv = 0;
         }
+        const uint64_t sum = team_sum<SC>(c, tm, epoch, mine, p.barrier_ticks, ok);
+        if (!*ok) return r;
+        ++r;
+        cur = nxt;
+        relabels += (int64_t)(sum & 0xfffffu);
+        const int size = (int)((sum >> 20) & 0xfffffu);
+        if ((sum >> 40) & 0xffu) *last_change = r;
+        dump = (sum >> 48) != 0 || size > most;
+        if (dump) break;
+        // the phase's limits, in the order of the rounds outside a run
+        if (size != 0) {
+            if (r >= lim.round_cap) *reason = 1;
+            else if (relabels > lim.budget) *reason = 2;
+            else if (lim.stall > 0 && r - *last_change >= lim.stall) *reason = 3;
+            else continue;
+        }
+        *done = true;
+        break;
     }
-    flush_to_t<SC>(g, to_t);
-    for (int64_t i = tm.wave(); i < g.n_heavy_all; i += tm.nwaves())
-        rl += discharge_group<SC, 64>(g, g.heavy_all[i], kc, rc, tl, to_t);
-    flush_to_t<SC>(g, to_t);
-    flush_relabels<SC>(g.ctrl, rl, (int64_t)(tl.push - push0), tl.deliv);
-    tl.deliv = 0;
+    // the totals, and the lists when the phase goes on outside the run
+    const int64_t v[4] = {wave_sum(to_t), wave_sum(all_relabels), (int64_t)wave_sum((int)(tl.push - push0)),
+                          wave_sum(all_deliv)};
+    if (lane == 0)
+        for (int k = 0; k < 4; ++k)
+            if (v[k]) atomicAdd(reinterpret_cast<unsigned long long *>(&rs->acc[k]), (unsigned long long)v[k]);
+    if (!dump) {
+        __syncthreads();
+        if (t == 0) rs->lcnt[cur] = rs->hcnt[cur] = 0;
+    }
+    const RoundCtx rc{round_list(g, r % 3), nullptr, &c->lst[r % 3], 0, 0, cur, false, false, false};
+    flush_stage<SC>(g, rc);
+    return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -1563,7 +2082,7 @@ __device__ __forceinline__ void rie_arc(const DevGraph &g, int u, int hu, int a,
 // would push flow out of the source side and create deficits (new roots)
 // there, undoing the cut.
 template <int SC>
-__device__ void remove_invalid(const DevGraph &g, const Team &tm, const int32_t *list, int64_t count,
+__device__ __forceinline__ void remove_invalid(const DevGraph &g, const Team &tm, const int32_t *list, int64_t count,
                                bool skip_cut, Tally &tl) {
     // a group of kLightGroup lanes per listed vertex: a short list is scanned by
     // its group (arcs gl, gl + kLightGroup, ..., loads independent of each
@@ -1634,7 +2153,7 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x) {
 // a fixed action (forced).  Lane 0 publishes the action in Ctrl; the features
 // and the action go to the policy trace.
 template <int SC>
-__device__ int policy_decide(const DevGraph &g, const LoopParams &p, Ctrl *c, int L, int64_t iter) {
+__device__ __forceinline__ int policy_decide(const DevGraph &g, const LoopParams &p, Ctrl *c, int L, int64_t iter) {
     constexpr int F = kPolF, H = kPolH, K = kPolK;
     constexpr int oW1 = 0, ob1 = oW1 + H * F, oW2 = ob1 + H, ob2 = oW2 + H * H, oW3 = ob2 + H, ob3 = oW3 + K * H;
     const int lane = lane_id();
@@ -1705,9 +2224,25 @@ __device__ int policy_decide(const DevGraph &g, const LoopParams &p, Ctrl *c, in
 // The persistent solve loop (Alg. 1 / Alg. 4 while-loop)
 // ---------------------------------------------------------------------------
 
+// Clear the LDS stages that start from zero (every thread of the workgroup).
+__device__ __forceinline__ void init_stages() {
+    BfsStage *st = bfs_stage();
+    Combine *comb = combine_stage();
+    if (threadIdx.x < 4) st->cnt[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        st->arcs = 0;
+        st->tverts = 0;
+        st->tarcs = 0;
+    }
+    for (int i = threadIdx.x; i < kCombine; i += blockDim.x) {
+        comb->key[i] = -1;
+        comb->sum[i] = 0;
+    }
+    __syncthreads();
+}
+
 template <int SC, bool WALK>
-__device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &p, BfsStage *stage,
-                           Combine *comb) {
+__device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &p) {
     Ctrl *c = g.ctrl;
     if (ld<SC>(&c->err)) return;  // update batch rejected: leave the state alone
     Tally tl;
@@ -1715,6 +2250,22 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
     const bool topology = p.mode == 1;
     int64_t iter = 0;
     uint32_t bar_epoch = 0;  // barriers this launch has passed
+    uint32_t sum_epoch = 0;  // and summing barriers of its runs
+    // Runs (frontier or list in LDS) are made by the whole team when it is one
+    // workgroup or shares an XCD, and by the first workgroup alone otherwise.
+    const Team run_team = SC == kAgent ? Team{0, 1} : tm;
+    const bool runner = SC != kAgent || tm.rank == 0;
+    // Items or vertices up to which a run starts (a list's run ends above
+    // twice that), and arcs above which a BFS run ends (it starts with up to half that):
+    // a frontier that gives every lane of the run's workgroups more than an arc or
+    // two is bound by throughput, which the whole team has more of, and the
+    // direction rule applies to it.  One workgroup has no other choice.
+    // (R-MAT 2^14, 2^15 static: 1.36, 1.96 ms without the arc limit, 1.09, 1.48 with it.)
+    const bool apart = SC == kAgent && tm.size > 1;
+    const int run_from = apart ? min(p.solo_items, kRunItems / 2) : tm.size * (kRunItems / 4);
+    const int run_most = apart ? run_from : 2 * run_from;
+    const int64_t run_arcs_most = apart ? 8 * kBlock : tm.size > 1 ? (int64_t)tm.size * 2 * kBlock : INT64_MAX;
+    int64_t run_arcs = 0;  // arcs discovered in BFS runs so far
     const bool policy = p.policy_mode != kPolicyFixed;
     // vertices per height are counted only for the gap heuristic
     const bool counts = p.use_gap != 0;
@@ -1774,37 +2325,37 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
                 const int64_t dead = reach_prev < 0 ? 0 : min(rest, max((int64_t)0, (int64_t)g.A - reach_prev));
                 bu = bu ? (int64_t)fv * p.bu_beta >= g.n : fa * p.bu_alpha > rest + (p.bu_alpha - 1) * dead;
             }
-            // A small frontier is expanded by the first workgroup alone, level
-            // after level with workgroup barriers in between (no grid barrier,
-            // no L2 invalidation), while the others wait at the next grid
-            // barrier.  The stretch ends at a level with no item or more than
-            // solo_items items, or after a quarter of the barrier's wait limit.
-            const bool alone = !bu && tm.size > 1 && cnt <= p.solo_items;
-            if (!alone || tm.rank == 0) {
-                const Team bt = alone ? Team{0, 1} : tm;
-                const uint64_t ts = wall_clock64();
-                for (int k = cnt;;) {
-                    if (threadIdx.x == 0 && tm.rank == 0) {
-                        c->qcount[(L + 2) % 3] = 0;
-                        c->qverts[(L + 2) % 3] = 0;
-                        c->qarcs[(L + 2) % 3] = 0;
-                    }
-                    if (bu)
-                        bfs_bottom_up<SC>(g, bt, L, feats, counts, stage, tl);
-                    else
-                        bfs_level<SC>(g, bt, L, k, feats, counts, dir, k >= p.lazy_items,
-                                      !alone && k >= kBfsStageMin ? stage : nullptr, stage, tl);
-                    if (!alone) break;
-                    block_sync<SC>();
-                    ++L;
-                    k = uniform(ld<SC>(&c->qcount[L % 3]));
-                    if (k == 0 || k > p.solo_items) break;
-                    if (uniform((int64_t)(wall_clock64() - ts)) > p.barrier_ticks / 4) break;
+            // A small frontier is expanded in a run (bfs_run): by the first
+            // workgroup alone, while the others wait at the next grid
+            // barrier, or by the whole of a team that shares an XCD.
+            if (!bu && cnt <= run_from && fa <= run_arcs_most / 2) {
+                bool ok = true;
+                if (runner) {
+                    L = bfs_run<SC>(g, run_team, p, L, cnt, run_arcs_most, feats, counts, dir, sum_epoch, tl, &ok);
+                    if (SC == kAgent && threadIdx.x == 0) c->solo_level = L;
                 }
-                if (alone && threadIdx.x == 0) c->solo_level = L;
+                if (!ok || !grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
+                if (SC == kAgent) L = uniform(ld<SC>(&c->solo_level));
+                if (dir) {
+                    const int64_t ra = uniform(ld<SC>(&c->run_arcs));
+                    seen_arcs += ra - run_arcs;
+                    run_arcs = ra;
+                }
+                continue;
             }
+            if (threadIdx.x == 0 && tm.rank == 0) {
+                c->qcount[(L + 2) % 3] = 0;
+                c->qverts[(L + 2) % 3] = 0;
+                c->qarcs[(L + 2) % 3] = 0;
+            }
+            // large levels of a team stage their output per workgroup
+            if (SC != kGroup && bu)
+                bfs_bottom_up<SC>(g, tm, L, feats, counts, tl);
+            else
+                bfs_level<SC>(g, tm, L, cnt, feats, counts, dir, cnt >= p.lazy_items,
+                              SC != kGroup && cnt >= kBfsStageMin, tl);
             if (!grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
-            L = alone ? uniform(ld<SC>(&c->solo_level)) : L + 1;
+            ++L;
         }
         if (dir) reach_prev = seen_arcs;
         const uint64_t tp = wall_clock64();
@@ -1847,88 +2398,56 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
         int64_t last_deliv = -1;
         int last_change = 0;
         for (;;) {
-            // A small round list (at most solo_items vertices, none huge) is
-            // worked by the first workgroup alone, round after round with
-            // workgroup barriers, while the others wait at the next grid
-            // barrier; the stretch hands its round count and stall state over
-            // in Ctrl.  It stops where a list grows, or after a quarter of the
-            // barrier's wait limit.
-            bool alone = false;
-            if (tm.size > 1 && !topology && p.solo_items > 0) {  // a one-workgroup team is always alone
-                const int rd0 = r % 3;
-                const int64_t lh0 = uniform(ld<SC>(reinterpret_cast<const int64_t *>(&c->lst[rd0])));
-                const int nu0 = uniform(ld<SC>(&c->lst[rd0].huge));
-                const int size0 = (int)(uint32_t)lh0 + (int)((uint64_t)lh0 >> 32) + nu0;
-                alone = nu0 == 0 && size0 > 0 && size0 <= p.solo_items;
+            const int rd = r % 3;
+            // the round's control words, read together before any decision;
+            // all were written before the last barrier, so every workgroup of
+            // the team takes the same decisions
+            const int64_t lh = uniform(ld<SC>(reinterpret_cast<const int64_t *>(&c->lst[rd])));
+            const int nu = uniform(ld<SC>(&c->lst[rd].huge));
+            const int64_t prl = uniform(ld<SC>(&c->phase_relabels));
+            const int64_t dl = uniform(ld<SC>(&c->phase_deliv));
+            const int nl = (int)(uint32_t)lh;
+            const int nh = (int)((uint64_t)lh >> 32);
+            if (nl + nh + nu == 0) break;
+            if (dl != last_deliv) {
+                last_deliv = dl;
+                last_change = r;
             }
-            bool done = false;
-            if (!alone || tm.rank == 0) {
-                const Team rt = alone ? Team{0, 1} : tm;
-                const uint64_t ts = wall_clock64();
-                for (;;) {
-                    const int rd = r % 3, wr = (r + 1) % 3, rs = (r + 2) % 3;
-                    // the round's control words, read together before any decision
-                    const int64_t lh = uniform(ld<SC>(reinterpret_cast<const int64_t *>(&c->lst[rd])));
-                    const int nu = uniform(ld<SC>(&c->lst[rd].huge));
-                    const int64_t prl = uniform(ld<SC>(&c->phase_relabels));
-                    const int64_t dl = uniform(ld<SC>(&c->phase_deliv));
-                    const int nl = (int)(uint32_t)lh;
-                    const int nh = (int)((uint64_t)lh >> 32);
-                    if (nl + nh + nu == 0) {
-                        done = true;
-                        break;
-                    }
-                    if (r >= round_cap) {
-                        reason = 1;
-                        done = true;
-                        break;
-                    }
-                    if (prl > budget) {
-                        reason = 2;
-                        done = true;
-                        break;
-                    }
-                    // all values read here were written before the last barrier, so
-                    // every workgroup of the team takes the same decision
-                    if (dl != last_deliv) {
-                        last_deliv = dl;
-                        last_change = r;
-                    }
-                    if (stall_lim > 0 && r - last_change >= stall_lim) {
-                        reason = 3;
-                        done = true;
-                        break;
-                    }
-                    if (leader) c->lst[rs] = ListCtr{};
-                    const RoundCtx rc{g.list[wr], g.huge[wr], nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                      nullptr, &c->lst[wr], rbase + r + 1, rbase, p.use_gap != 0};
-                    if (topology) pr_round_topology<SC>(g, rt, p.kc, rc, tl);
-                    else pr_round<SC, WALK>(g, rt, rd, nl, nh, nu, p.kc, rc, p.combine ? comb : nullptr, tl);
-                    ++r;
-                    if (!alone) break;
-                    block_sync<SC>();
-                    const int rdn = r % 3;
-                    const int64_t lhn = uniform(ld<SC>(reinterpret_cast<const int64_t *>(&c->lst[rdn])));
-                    const int nun = uniform(ld<SC>(&c->lst[rdn].huge));
-                    if (nun > 0 || (int)(uint32_t)lhn + (int)((uint64_t)lhn >> 32) > p.solo_items) break;
-                    if (uniform((int64_t)(wall_clock64() - ts)) > p.barrier_ticks / 4) break;
-                }
-                if (alone && threadIdx.x == 0) {
-                    c->solo_r = r;
-                    c->solo_done = done ? 1 : 0;
-                    c->solo_reason = reason;
-                    c->solo_last_change = last_change;
-                    c->solo_last_deliv = last_deliv;
-                }
+            if (r >= round_cap) {
+                reason = 1;
+                break;
             }
-            if (!alone && done) break;  // the phase ends for every workgroup alike
-            if (!grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
-            if (alone) {
-                r = uniform(ld<SC>(&c->solo_r));
-                reason = uniform(ld<SC>(&c->solo_reason));
-                last_change = uniform(ld<SC>(&c->solo_last_change));
-                last_deliv = uniform(ld<SC>(&c->solo_last_deliv));
-                if (uniform(ld<SC>(&c->solo_done))) break;
+            if (prl > budget) {
+                reason = 2;
+                break;
+            }
+            if (stall_lim > 0 && r - last_change >= stall_lim) {
+                reason = 3;
+                break;
+            }
+            // A small round list without huge vertices is worked in a run of
+            // rounds, like a small BFS frontier.
+            const bool run = !topology && nu == 0 && nl + nh <= run_from;
+            bool ok = true, done = false;
+            if (!run || runner)
+                r = pr_rounds<SC, WALK>(g, run ? run_team : tm, p, PhaseLimits{budget, round_cap, stall_lim}, run, rbase,
+                                        r, nl, nh, nu, prl, run_most, &reason, &done, &last_change, sum_epoch, tl, &ok);
+            if (SC == kAgent && run && runner && threadIdx.x == 0) {
+                c->solo_r = r;
+                c->solo_done = done ? 1 : 0;
+                c->solo_reason = reason;
+                c->solo_last_change = last_change;
+            }
+            if (!ok || !grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
+            if (run) {
+                if (SC == kAgent) {
+                    r = uniform(ld<SC>(&c->solo_r));
+                    reason = uniform(ld<SC>(&c->solo_reason));
+                    last_change = uniform(ld<SC>(&c->solo_last_change));
+                    done = uniform(ld<SC>(&c->solo_done)) != 0;
+                }
+                last_deliv = uniform(ld<SC>(&c->phase_deliv));
+                if (done) break;
             }
         }
         // --- RemoveInvalidEdges over the vertices that relabelled ---
@@ -1996,29 +2515,62 @@ __device__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &
 // the two are separate instances, since both inlined side by side would spill.
 template <int BLOCK, int SC, bool WALK>
 __global__ void __launch_bounds__(BLOCK) k_loop(DevGraph g, LoopParams p) {
-    BfsStage *stage = nullptr;
-    Combine *comb = nullptr;
     Team tm{0, 1};
     if constexpr (SC != kGroup) {
         tm = join_team<SC>(g.ctrl, p.team_want, p.join_ticks);
         if (tm.size == 0) return;
-        __shared__ BfsStage s_stage;
-        __shared__ Combine s_comb;
-        if (threadIdx.x < 4) s_stage.cnt[threadIdx.x] = 0;
-        if (threadIdx.x == 0) {
-            s_stage.arcs = 0;
-            s_stage.tverts = 0;
-            s_stage.tarcs = 0;
-        }
-        for (int i = threadIdx.x; i < kCombine; i += blockDim.x) {
-            s_comb.key[i] = -1;
-            s_comb.sum[i] = 0;
-        }
-        __syncthreads();
-        stage = &s_stage;
-        comb = &s_comb;
+        init_stages();
     }
-    solve_loop<SC, WALK>(g, tm, p, stage, comb);
+    solve_loop<SC, WALK>(g, tm, p);
+}
+
+// A view read from a device table, its pointers read as pointers to global
+// memory.  Read as they are they would be generic addresses, and every access
+// through them a flat one, which also waits on the LDS counter.
+template <typename T>
+__device__ __forceinline__ T *as_global(T *const &field) {
+    using Global = __attribute__((address_space(1))) T;
+    return (T *)*reinterpret_cast<Global *const *>(&field);
+}
+__device__ __forceinline__ DevGraph global_view(const DevGraph &v) {
+    DevGraph g;
+    g.n = v.n;
+    g.s = v.s;
+    g.t = v.t;
+    g.A = v.A;
+    g.m = v.m;
+    g.qcap = v.qcap;
+    g.n_heavy_all = v.n_heavy_all;
+    g.n_bu_items = v.n_bu_items;
+    g.part_want = v.part_want;
+    g.part_restrict = v.part_restrict;
+    g.row_ptr = as_global(v.row_ptr);
+    g.arc = as_global(v.arc);
+    g.twin = as_global(v.twin);
+    g.cap = as_global(v.cap);
+    g.edge2arc = as_global(v.edge2arc);
+    g.ecap = as_global(v.ecap);
+    g.stamp = as_global(v.stamp);
+    g.e = as_global(v.e);
+    g.h = as_global(v.h);
+    g.q[0] = as_global(v.q[0]);
+    g.q[1] = as_global(v.q[1]);
+    g.list[0] = as_global(v.list[0]);
+    g.list[1] = as_global(v.list[1]);
+    g.list[2] = as_global(v.list[2]);
+    g.huge[0] = as_global(v.huge[0]);
+    g.huge[1] = as_global(v.huge[1]);
+    g.huge[2] = as_global(v.huge[2]);
+    g.mark = as_global(v.mark);
+    g.rmark = as_global(v.rmark);
+    g.relab = as_global(v.relab);
+    g.hcount = as_global(v.hcount);
+    g.heavy_all = as_global(v.heavy_all);
+    g.bu_items = as_global(v.bu_items);
+    g.ptrace = as_global(v.ptrace);
+    g.ctrl = as_global(v.ctrl);
+    g.part = as_global(v.part);
+    return g;
 }
 
 // Two teams in one cooperative launch: workgroups [0, split) run the solve
@@ -2030,30 +2582,15 @@ __global__ void __launch_bounds__(BLOCK) k_loop(DevGraph g, LoopParams p) {
 template <int BLOCK, bool WALK>
 __global__ void __launch_bounds__(BLOCK)
     k_teams(const DevGraph *__restrict__ views, const LoopParams *__restrict__ params, const int64_t *work) {
-    __shared__ BfsStage s_stage;
-    __shared__ Combine s_comb;
-    if (threadIdx.x < 4) s_stage.cnt[threadIdx.x] = 0;
-    if (threadIdx.x == 0) {
-        s_stage.arcs = 0;
-        s_stage.tverts = 0;
-        s_stage.tarcs = 0;
-    }
-    for (int i = threadIdx.x; i < kCombine; i += blockDim.x) {
-        s_comb.key[i] = -1;
-        s_comb.sum[i] = 0;
-    }
-    __syncthreads();
+    init_stages();
     const int G = (int)gridDim.x;
     const int64_t wa = work[0], wb = work[1];
     int64_t sp = (wa + wb) > 0 ? ((int64_t)G * wa + (wa + wb) / 2) / (wa + wb) : G / 2;
     const int split = (int)min((int64_t)G - 1, max((int64_t)1, sp));
-    // one inlined loop; the view and its parameters are read by reference from
-    // the device table (a private copy of either would be indexed dynamically
-    // and spill)
     const int side = (int)blockIdx.x < split ? 0 : 1;
     const Team tm = side == 0 ? Team{(int)blockIdx.x, split} : Team{(int)blockIdx.x - split, G - split};
     const LoopParams &p = params[side];
-    solve_loop<kAgent, WALK>(views[side], tm, p, &s_stage, p.combine ? &s_comb : nullptr);
+    solve_loop<kAgent, WALK>(global_view(views[side]), tm, p);
 }
 
 // ---------------------------------------------------------------------------
@@ -2199,7 +2736,7 @@ __global__ void k_init_state(DevGraph g) {
 // e(u) += d, e(s) -= d (Alg. 1 third loop; Alg. 4 lines 3-8, where the
 // remaining residual is pushed rather than e(u) overwritten).
 template <int SC>
-__device__ void saturate_source(const DevGraph &g, const Team &tm) {
+__device__ __forceinline__ void saturate_source(const DevGraph &g, const Team &tm) {
     if (ld<SC>(&g.ctrl->err)) return;
     __shared__ int64_t s_sum, s_cnt;
     if (threadIdx.x == 0) {
@@ -2537,9 +3074,7 @@ __global__ void __launch_bounds__(BLOCK)
     k_batch(const DevGraph *__restrict__ graphs, const int32_t *__restrict__ order, LoopParams p,
             const int32_t *__restrict__ kc, BatchResult *__restrict__ res) {
     const int i = order[blockIdx.x];
-    // a reference into the read-only table (uniform loads), not a private copy:
-    // the solve loop indexes the list and frontier pointer arrays dynamically
-    const DevGraph &g = graphs[i];
+    const DevGraph g = global_view(graphs[i]);
     const Team tm{0, 1};
     {
         int *w = reinterpret_cast<int *>(g.ctrl);
@@ -2560,7 +3095,7 @@ __global__ void __launch_bounds__(BLOCK)
     LoopParams q = p;
     q.kc = kc[i];
     if (q.relabel_budget <= 0) q.relabel_budget = max((int64_t)1024, (int64_t)g.n / 16);
-    solve_loop<kGroup, false>(g, tm, q, nullptr, nullptr);
+    solve_loop<kGroup, false>(g, tm, q);
     __syncthreads();
     if (threadIdx.x == 0) {
         BatchResult r;

@@ -44,11 +44,11 @@ GRAPHS = {
 
 
 @pytest.mark.parametrize("name", sorted(GRAPHS))
-@pytest.mark.parametrize("grid", [0, 1, 5])
-def test_teams_match_oracle(mf, name, grid):
+@pytest.mark.parametrize("grid,mode", [(0, 0), (1, 0), (5, 0), (0, 1)])
+def test_teams_match_oracle(mf, name, grid, mode):
     g = GRAPHS[name]()
     cap = g.cap.copy()
-    with mf.MaxFlow(g, grid_blocks=grid, flags=mf.MF_FLAG_DEBUG_CHECKS) as F:
+    with mf.MaxFlow(g, grid_blocks=grid, mode=mode, flags=mf.MF_FLAG_DEBUG_CHECKS) as F:
         F.solve()
         check_solved(F, g, cap)
         rng = np.random.default_rng(3)
