@@ -114,7 +114,8 @@ struct Ctrl {
     int32_t qverts[4];  // vertices discovered per BFS level (direction rule), same buffering
     int64_t qarcs[4];   // their arcs
     ListCtr lst[3];     // active lists of the rounds, triple-buffered
-    int32_t nrelab;     // vertices relabelled in the current phase
+    int32_t nrelab[2];  // vertices listed for RemoveInvalidEdges in the current phase: short, long arc lists
+    int32_t nfirsts;    // vertices relabelled in the current phase
     int32_t status;
     int32_t err;        // update validation: 1 id range, 2 capacity range, 4 duplicate
     int32_t stop;       // set by the leader when the time budget ran out
@@ -163,8 +164,8 @@ struct DevGraph {
     int32_t *list[3];   // n each: active lists of the push/relabel rounds
     int32_t *huge[3];   // active vertices with more than kHugeDeg arcs, per list
     int32_t *mark;      // n: id of the round list a vertex was last added to
-    int32_t *rmark;     // n: id of the phase a vertex last relabelled in
-    int32_t *relab;     // n: vertices relabelled in the current phase
+    int32_t *rmark;     // n: twice the id of the phase a vertex last relabelled in, plus one once it is in relab
+    int32_t *relab;     // n: vertices for RemoveInvalidEdges in the current phase
     int32_t *hcount;    // n+1: vertices at each height below |V| (gap heuristic)
     int32_t *heavy_all; // vertices with long arc lists (topology-driven sweeps)
     int32_t n_heavy_all;

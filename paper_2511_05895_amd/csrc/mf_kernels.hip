@@ -339,17 +339,18 @@ struct RunStage {
     // BFS: frontier items of two levels, kRunItems each; rounds: short lists
     // of two rounds, then long lists of two rounds, kStageCap each
     int32_t buf[4 * kRunItems];
-    // BFS: active vertices found, short then long lists; rounds: relabelled
-    // vertices
+    // BFS: active vertices found, rounds: vertices for RemoveInvalidEdges;
+    // short lists, then long ones
     int32_t aux[2 * kStageCap];
-    int32_t icnt[2], lcnt[2], hcnt[2], rcnt;
+    int32_t icnt[2], lcnt[2], hcnt[2], rcnt[2];
     int32_t found;  // BFS: frontier items found in this level,
     uint64_t act;   // short (low half) and long active vertices found in this run
     int32_t larcs;     // BFS: arcs of the vertices discovered in this level
     int32_t spill;     // something did not fit and went to the global lists
+    int32_t firsts;    // rounds: vertices relabelled for the first time in the phase
     int32_t relabels;  // of this round
     int32_t deliv;     // this round delivered excess
-    int32_t base[3];
+    int32_t base[4];
     int64_t acc[4];    // of the run: excess into t, relabels, pushes, deliveries into deficits
     int64_t arcs;      // arcs of the vertices a BFS run discovered
     uint64_t total;    // sum of the last team_sum
@@ -1193,22 +1194,37 @@ __device__ __forceinline__ void list_add(const DevGraph &g, const RoundCtx &rc, 
     if (xchg<SC>(&g.mark[v], rc.next_id) != rc.next_id) list_append<SC>(g, rc, v, deg);
 }
 
-// First relabel of u in this phase: remember u for RemoveInvalidEdges.  Only
-// the one lane (or group) visiting u in a round touches rmark[u]; `stamp` is
-// its value as read at the start of the visit.
+// u was relabelled, `rose` above its height at the start of the visit.  Counts
+// u once per phase, and remembers it for RemoveInvalidEdges when it rose by 3
+// or more: only such a vertex can own a steep arc.  (A relabel leaves u at most
+// one above every head it saw residual; heights never drop inside a phase.  So
+// an arc (u, v) can be steep only if it turned residual after u's scan, by a
+// push from v.  A push in a later round finds h(v) above u's new height; one in
+// the same round found h(v) at least 1 above u's height at the start of the
+// round, so h(v) + 2 <= h(u) asks for a rise of 3.)  With the gap heuristic,
+// which lifts vertices without a scan, every relabelled vertex is remembered.
+// Only the one lane (or group) visiting u in a round touches rmark[u]; `stamp`
+// is its value as read at the start of the visit: twice the phase's id, plus one
+// once u is remembered.
 template <int SC>
-__device__ __forceinline__ void note_relabel(const DevGraph &g, const RoundCtx &rc, int u, int32_t &stamp) {
-    if (stamp != rc.phase_id) {
-        stamp = rc.phase_id;
-        g.rmark[u] = rc.phase_id;
-        RunStage *rs = run_stage();
-        const int k = atomicAdd(&rs->rcnt, 1);
-        if (k < kStageCap) {
-            rs->aux[k] = u;
-        } else {
-            const int slot = fetch_add<SC>(&g.ctrl->nrelab, 1);
-            g.relab[slot] = u;
-        }
+__device__ __forceinline__ void note_relabel(const DevGraph &g, const RoundCtx &rc, int u, int deg, int rose,
+                                             int32_t &stamp) {
+    const int32_t once = (int32_t)(2u * (uint32_t)rc.phase_id);
+    const bool first = (stamp & ~1) != once;
+    const bool keep = (rose >= 3 || rc.use_gap) && (first || stamp == once);
+    if (!first && !keep) return;
+    stamp = once | (keep ? 1 : 0);
+    g.rmark[u] = stamp;
+    RunStage *rs = run_stage();
+    if (first) atomicAdd(&rs->firsts, 1);
+    if (!keep) return;
+    const int far = deg > kLightMaxDeg;  // short lists from the front, long ones from the back
+    const int k = atomicAdd(&rs->rcnt[far], 1);
+    if (k < kStageCap) {
+        rs->aux[far * kStageCap + k] = u;
+    } else {
+        const int slot = fetch_add<SC>(&g.ctrl->nrelab[far], 1);
+        g.relab[far ? g.n - 1 - slot : slot] = u;
     }
 }
 
@@ -1328,7 +1344,8 @@ __device__ __forceinline__ int discharge_wave(const DevGraph &g, int u, int kc, 
     const int n = g.n;
     const int beg = g.row_ptr[u], end = g.row_ptr[u + 1];
     int hu = get<SC>(&g.h[u]);
-    int32_t stamp = get<SC>(&g.rmark[u]);  // phase of u's last first-relabel (read with the rest)
+    int32_t stamp = get<SC>(&g.rmark[u]);
+    const int h0 = hu;
     int relabels = 0;
     if (rc.use_gap && hu < n && hu > ld<SC>(&g.ctrl->gap)) {  // above a gap: cut off
         if (lane == 0) {
@@ -1383,7 +1400,7 @@ __device__ __forceinline__ int discharge_wave(const DevGraph &g, int u, int kc, 
             if (lane == 0) {
                 hn = relabel_to<SC>(g, u, hu, hmin, rc.use_gap);
                 tl.relabel++;
-                note_relabel<SC>(g, rc, u, stamp);
+                note_relabel<SC>(g, rc, u, end - beg, hn - h0, stamp);
             }
             hu = lane_value(hn, 0);
             relabels++;
@@ -1412,6 +1429,7 @@ __device__ __forceinline__ int visit_light(const DevGraph &g, int u, int beg, in
     const int gl = lane_id() & (G - 1);
     const bool lead = gl == G - 1;
     const int n = g.n;
+    const int h0 = hu;
     int relabels = 0;
     bool spent = false;   // no residual arc left: the cycles end
     bool listed = false;  // already on the next list
@@ -1476,7 +1494,7 @@ __device__ __forceinline__ int visit_light(const DevGraph &g, int u, int beg, in
                 if (cyc == kc - 1 && hu < n) seen_u = xchg<SC>(&g.mark[u], rc.next_id);
                 tl.relabel++;
                 relabels++;
-                note_relabel<SC>(g, rc, u, stamp);
+                note_relabel<SC>(g, rc, u, end - beg, hu - h0, stamp);
             }
             if (out) {
                 add<SC>(cf_ptr(g.arc, beg + k * G + gl), -(int32_t)d);
@@ -1556,6 +1574,7 @@ __device__ __forceinline__ int discharge_walk(const DevGraph &g, int u, int kc, 
     const int beg = g.row_ptr[u], end = g.row_ptr[u + 1];
     int hu = get<SC>(&g.h[u]);
     int32_t stamp = get<SC>(&g.rmark[u]);
+    const int h0 = hu;
     int relabels = 0;
     if (rc.use_gap && hu < n && hu > ld<SC>(&g.ctrl->gap)) {  // above a gap: cut off
         if (lane == 0) {
@@ -1616,7 +1635,7 @@ __device__ __forceinline__ int discharge_walk(const DevGraph &g, int u, int kc, 
         if (lane == 0) {
             hn = relabel_to<SC>(g, u, hu, hrest, rc.use_gap);
             tl.relabel++;
-            note_relabel<SC>(g, rc, u, stamp);
+            note_relabel<SC>(g, rc, u, end - beg, hn - h0, stamp);
         }
         hu = lane_value(hn, 0);
         relabels++;
@@ -1653,6 +1672,7 @@ __device__ __forceinline__ int discharge_block(const DevGraph &g, int u, int kc,
     const int cb = min(end, beg + w * chunk), ce = min(end, cb + chunk);
     int hu = get<SC>(&g.h[u]);
     int32_t stamp = get<SC>(&g.rmark[u]);
+    const int h0 = hu;
     int relabels = 0;
     if (rc.use_gap && hu < n && hu > ld<SC>(&g.ctrl->gap)) {  // above a gap: cut off
         if (t == 0) {
@@ -1732,7 +1752,7 @@ __device__ __forceinline__ int discharge_block(const DevGraph &g, int u, int kc,
             if (t == 0) {
                 s_h = relabel_to<SC>(g, u, hu, hmin, rc.use_gap);
                 tl.relabel++;
-                note_relabel<SC>(g, rc, u, stamp);
+                note_relabel<SC>(g, rc, u, end - beg, s_h - h0, stamp);
             }
             __syncthreads();
             hu = s_h;
@@ -1763,6 +1783,7 @@ __device__ __forceinline__ int discharge_block_walk(const DevGraph &g, int u, in
     const int beg = g.row_ptr[u], end = g.row_ptr[u + 1];
     int hu = get<SC>(&g.h[u]);
     int32_t stamp = get<SC>(&g.rmark[u]);
+    const int h0 = hu;
     int relabels = 0;
     if (rc.use_gap && hu < n && hu > ld<SC>(&g.ctrl->gap)) {  // above a gap: cut off
         if (t == 0) {
@@ -1840,7 +1861,7 @@ __device__ __forceinline__ int discharge_block_walk(const DevGraph &g, int u, in
         if (t == 0) {
             s_h = relabel_to<SC>(g, u, hu, hmin, rc.use_gap);
             tl.relabel++;
-            note_relabel<SC>(g, rc, u, stamp);
+            note_relabel<SC>(g, rc, u, end - beg, s_h - h0, stamp);
         }
         __syncthreads();
         hu = s_h;
@@ -1860,12 +1881,14 @@ __device__ __forceinline__ void flush_stage(const DevGraph &g, const RoundCtx &r
     RunStage *rs = run_stage();
     __syncthreads();
     const int nl = min(rs->lcnt[rc.par], kStageCap), nh = min(rs->hcnt[rc.par], kStageCap);
-    const int nr = min(rs->rcnt, kStageCap);
+    const int nr = min(rs->rcnt[0], kStageCap), nf = min(rs->rcnt[1], kStageCap);
     if (threadIdx.x == 0) {
         rs->base[0] = nl ? fetch_add<SC>(&rc.next_ctr->light, nl) : 0;
         rs->base[1] = nh ? fetch_add<SC>(&rc.next_ctr->heavy, nh) : 0;
-        rs->base[2] = nr ? fetch_add<SC>(&g.ctrl->nrelab, nr) : 0;
         Ctrl *c = g.ctrl;
+        rs->base[2] = nr ? fetch_add<SC>(&c->nrelab[0], nr) : 0;
+        rs->base[3] = nf ? fetch_add<SC>(&c->nrelab[1], nf) : 0;
+        if (rs->firsts) add<SC>(&c->nfirsts, rs->firsts);
         const int64_t *acc = rs->acc;
         if (acc[0]) add<SC>(&g.e[g.t], acc[0]);
         if (acc[0] + acc[3]) add<SC>(&c->phase_deliv, acc[0] + acc[3]);
@@ -1877,6 +1900,7 @@ __device__ __forceinline__ void flush_stage(const DevGraph &g, const RoundCtx &r
     for (int i = threadIdx.x; i < nl; i += blockDim.x) rc.next[rs->base[0] + i] = light[i];
     for (int i = threadIdx.x; i < nh; i += blockDim.x) rc.next[g.n - 1 - (rs->base[1] + i)] = heavy[i];
     for (int i = threadIdx.x; i < nr; i += blockDim.x) g.relab[rs->base[2] + i] = rs->aux[i];
+    for (int i = threadIdx.x; i < nf; i += blockDim.x) g.relab[g.n - 1 - (rs->base[3] + i)] = rs->aux[kStageCap + i];
     __syncthreads();  // the stage is free again
 }
 
@@ -1941,7 +1965,7 @@ __device__ __forceinline__ int pr_rounds(const DevGraph &g, const Team &tm, cons
         if (t == 0) {
             rs->lcnt[0] = ml;
             rs->hcnt[0] = mh;
-            rs->lcnt[1] = rs->hcnt[1] = rs->rcnt = 0;
+            rs->lcnt[1] = rs->hcnt[1] = rs->rcnt[0] = rs->rcnt[1] = rs->firsts = 0;
             rs->spill = rs->relabels = rs->deliv = 0;
         }
         if (t < 4) rs->acc[t] = 0;
@@ -2057,10 +2081,14 @@ __device__ __forceinline__ int pr_rounds(const DevGraph &g, const Team &tm, cons
 
 // ---------------------------------------------------------------------------
 // RemoveInvalidEdges (Alg. 3): saturate every residual arc (u, v) with
-// h(u) > h(v) + 1.  Heights never drop inside a phase and start exact, so only
-// vertices that relabelled in the phase can own such an arc; the phase keeps
-// them in a list.  Only u lowers c_f of its own arcs, so an exchange with 0
-// reads and clears the residual in one step.
+// h(u) > h(v) + 1.  Only vertices that rose by 3 or more in one visit can own
+// such an arc (see note_relabel); the phase keeps them in a list, short arc
+// lists from its front and long ones from its back.  Only u lowers c_f of its
+// own arcs, so an exchange with 0 reads and clears the residual in one step.
+// What bounded it was the scan itself and its uneven lists: with every
+// relabelled vertex listed and a hub scanned by one wavefront, on R-MAT
+// 2^22 x 16 a solve read 205 M arcs here (12.3 ms in all); now 9 k (8.7 ms).
+// R-MAT 2^20: 6.3 -> 5.0 ms, 2^18: 2.5 -> 1.9 ms.
 // ---------------------------------------------------------------------------
 
 template <int SC>
@@ -2082,43 +2110,43 @@ __device__ __forceinline__ void rie_arc(const DevGraph &g, int u, int hu, int a,
 // would push flow out of the source side and create deficits (new roots)
 // there, undoing the cut.
 template <int SC>
-__device__ __forceinline__ void remove_invalid(const DevGraph &g, const Team &tm, const int32_t *list, int64_t count,
-                               bool skip_cut, Tally &tl) {
-    // a group of kLightGroup lanes per listed vertex: a short list is scanned by
-    // its group (arcs gl, gl + kLightGroup, ..., loads independent of each
-    // other); a long one by a whole wavefront after the group step
+__device__ __forceinline__ void remove_invalid(const DevGraph &g, const Team &tm, int nshort, int nlong, bool skip_cut,
+                                               Tally &tl) {
+    // a group of 8 lanes per short list
     constexpr int G = 8;
-    const int64_t grp = tm.tid() / G, ngrp = tm.nthreads() / G;
-    const int gl = lane_id() & (G - 1);
-    const int lane = lane_id();
-    const int64_t trips = (count + ngrp - 1) / ngrp;  // the same for every lane
-    for (int64_t k = 0, i = grp; k < trips; ++k, i += ngrp) {
-        int u = -1, beg = 0, end = 0, hu = 0;
-        bool heavy = false;
-        if (i < count) {
-            u = get<SC>(&list[i]);
+    const int lane = lane_id(), gl = lane & (G - 1);
+    const int64_t ngrp = tm.nthreads() / G;
+    for (int64_t i = tm.tid() / G; i < nshort; i += ngrp) {
+        const int u = get<SC>(&g.relab[i]);
+        const int hu = get<SC>(&g.h[u]);
+        if (skip_cut && hu >= g.n) continue;
+        const int beg = g.row_ptr[u], end = g.row_ptr[u + 1];
+        for (int a = beg + gl; a < end; a += G) rie_arc<SC>(g, u, hu, a, tl);
+        if (gl == 0) tl.rie_a += end - beg;
+    }
+    // a wavefront per long list, a workgroup per huge one: the workgroup takes
+    // up to 64 vertices at a time, one lane each, and deals them out
+    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int per = min(64, max(1, (nlong + tm.size - 1) / tm.size));
+    for (int64_t base = (int64_t)tm.rank * per; base < nlong; base += (int64_t)tm.size * per) {
+        int u = -1, hu = 0, beg = 0, end = 0;
+        if (lane < per && base + lane < nlong) {
+            u = get<SC>(&g.relab[g.n - 1 - (base + lane)]);
             hu = get<SC>(&g.h[u]);
-            if (skip_cut && hu >= g.n) {
-                u = -1;
-            } else {
+            if (!(skip_cut && hu >= g.n)) {
                 beg = g.row_ptr[u];
                 end = g.row_ptr[u + 1];
-                heavy = end - beg > kLightMaxDeg;
             }
         }
-        if (u >= 0 && !heavy) {
-            for (int a = beg + gl; a < end; a += G) rie_arc<SC>(g, u, hu, a, tl);
-            if (gl == 0) tl.rie_a += end - beg;
-        }
-        uint64_t hm = __ballot(heavy && gl == 0);
-        while (hm) {
-            const int l = __ffsll((unsigned long long)hm) - 1;
-            hm &= hm - 1;
-            const int w = lane_value(u, l);
-            const int wb = lane_value(beg, l), we = lane_value(end, l);
-            const int hw = lane_value(hu, l);
-            for (int a = wb + lane; a < we; a += 64) rie_arc<SC>(g, w, hw, a, tl);
-            if (lane == 0) tl.rie_a += we - wb;
+        for (uint64_t m = __ballot(end > beg); m; m &= m - 1) {
+            const int l = __ffsll((unsigned long long)m) - 1;
+            const int b = lane_value(beg, l), e = lane_value(end, l);
+            const bool all = e - b > kHugeDeg;
+            if (!all && l % nw != w) continue;
+            const int v = lane_value(u, l), hv = lane_value(hu, l);
+            const int step = all ? blockDim.x : 64;
+            for (int a = b + (all ? (int)threadIdx.x : lane); a < e; a += step) rie_arc<SC>(g, v, hv, a, tl);
+            if (lane == 0 && (!all || w == 0)) tl.rie_a += e - b;
         }
     }
 }
@@ -2288,7 +2316,7 @@ __device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, co
             c->prev_relabels = ld<SC>(&c->phase_relabels);
             c->feat_esum = 0;
             for (int b = 0; b < 8; ++b) c->feat_hist[b] = 0;
-            c->nrelab = 0;
+            c->nrelab[0] = c->nrelab[1] = c->nfirsts = 0;
             c->phase_relabels = 0;
             c->phase_pushes = 0;
             c->phase_deliv = 0;
@@ -2452,8 +2480,8 @@ __device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, co
         }
         // --- RemoveInvalidEdges over the vertices that relabelled ---
         const uint64_t tr = wall_clock64();
-        const int nrel = uniform(ld<SC>(&c->nrelab));
-        if (!p.no_rie) remove_invalid<SC>(g, tm, g.relab, nrel, p.use_gap != 0, tl);
+        const int nrel = uniform(ld<SC>(&c->nrelab[0])), nrel_long = uniform(ld<SC>(&c->nrelab[1]));
+        if (!p.no_rie) remove_invalid<SC>(g, tm, nrel, nrel_long, p.use_gap != 0, tl);
         if (counts)
             for (int64_t i = tm.tid(); i <= g.n; i += tm.nthreads()) g.hcount[i] = 0;
         {
@@ -2464,7 +2492,7 @@ __device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, co
                 tr_rec[kTrRounds] = r;
                 tr_rec[kTrReason] = reason;
                 tr_rec[kTrRelabels] = (int32_t)min<int64_t>(ld<SC>(&c->phase_relabels), INT32_MAX);
-                tr_rec[kTrRelabelled] = nrel;
+                tr_rec[kTrRelabelled] = ld<SC>(&c->nfirsts);
                 tr_rec[kTrPushes] = (int32_t)min<int64_t>(ld<SC>(&c->phase_pushes), INT32_MAX);
                 tr_rec[kTrLastDeliv] = last_change;
                 if (policy && g.ptrace)
