@@ -9,9 +9,12 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
+#include <functional>
 #include <new>
 #include <numeric>
+#include <queue>
 #include <string>
 #include <vector>
 
@@ -44,10 +47,15 @@ struct mf_batch {
     std::vector<int64_t> arcs;       // A per instance
     std::vector<int32_t> order;      // instance ids, class by class, largest first
     std::vector<int32_t> class_begin;  // n_classes + 1 offsets into order
+    int32_t launch_end[MF_BATCH_MAX_CLASSES] = {};  // end of the classes launched with class c
+    int32_t team[MF_BATCH_MAX_CLASSES] = {};        // workgroups per instance of that launch
+    int32_t team_alone[MF_BATCH_MAX_CLASSES] = {};  // ... of class c launched alone
     mf::DevGraph *d_graphs = nullptr;
-    int32_t *d_order = nullptr;
+    int32_t *d_order = nullptr;  // order, then the order of the team launches
     int32_t *d_kc = nullptr;
     mf::BatchResult *d_res = nullptr;
+    mf::BatchCtl *d_ctl = nullptr;  // of the team launches, by first class
+    int32_t blocks = 0;             // its workgroups, one per compute unit
     mf::BatchResult *h_res = nullptr;  // pinned
     mf::Ctrl *h_ctrl = nullptr;        // pinned, one instance at a time
     uint8_t *d_side = nullptr;
@@ -153,6 +161,39 @@ int class_of(const mf_batch_opts_t &o, int64_t a) {
     return o.n_classes - 1;
 }
 
+// Workgroups of 1024 threads per instance: the size with the shortest schedule
+// of order[0, cnt), each instance taken by the first team that is free.  A team
+// of t needs about sqrt(A) (1 + A / (160000 t)) for an instance of A arcs
+// (its steps, and its work per step over the team): by teams of 1, 2, 4, 8, 16
+// and 32, a grid of 64 k arcs took 17 15 13 11 11 10 ms, one of 499 k arcs 90 59
+// 40 33 27 25, R-MAT of 427 k arcs 8.2 5.2 3.5 2.3 1.9 1.6.  Batches, at the
+// sizes chosen and beside them: 24 grids of 499 k, 8: 53 ms (4: 66, 16: 67); 128
+// of 135 k, 2: 32 (one workgroup each 46, 4: 49); 300 of 80 k, 1: 43 (2: 47).
+int team_size(const mf_batch_t *b, const int32_t *order, int32_t cnt) {
+    int best = 1;
+    double best_span = 0;
+    for (int t = 1; t <= b->blocks / mf::kXcds; t *= 2) {
+        std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
+        double span = 0;
+        for (int32_t j = 0; j < cnt; ++j) {
+            const double a = (double)b->arcs[order[j]];
+            double at = 0;
+            if ((int)busy.size() == b->blocks / t) {
+                at = busy.top();
+                busy.pop();
+            }
+            at += std::sqrt(a) * (1 + a / (160e3 * t));
+            busy.push(at);
+            span = std::max(span, at);
+        }
+        if (t == 1 || span < best_span) {
+            best = t;
+            best_span = span;
+        }
+    }
+    return best;
+}
+
 // Order the instances class by class, largest first inside a class, and
 // upload the order and the per-instance KERNELCYCLES.  Drops the captured
 // graph (its launches encode the class split).
@@ -169,10 +210,37 @@ int apply_config(mf_batch_t *b) {
     b->class_begin.assign(o.n_classes + 1, 0);
     for (int32_t i = 0; i < b->count; ++i) b->class_begin[cls[i] + 1]++;
     for (int c = 0; c < o.n_classes; ++c) b->class_begin[c + 1] += b->class_begin[c];
+    // Classes of 1024-thread workgroups next to each other share one launch and
+    // its queue, largest first, when teams solve them.
+    std::vector<int32_t> teams(b->order);
+    for (int c = 0, end = 0; c < o.n_classes; c = end) {
+        for (end = c; end < o.n_classes && o.block[end] == mf::kBlock; ++end) {
+            const int32_t beg = b->class_begin[end];
+            b->team_alone[end] = team_size(b, b->order.data() + beg, b->class_begin[end + 1] - beg);
+        }
+        if (end > c) {
+            const int32_t beg = b->class_begin[c], cnt = b->class_begin[end] - beg;
+            std::stable_sort(teams.begin() + beg, teams.begin() + beg + cnt,
+                             [&](int32_t x, int32_t y) { return b->arcs[x] > b->arcs[y]; });
+            b->team[c] = team_size(b, teams.data() + beg, cnt);
+            if (b->team[c] > 1) {
+                b->launch_end[c] = end;
+                continue;
+            }
+        } else {
+            b->team_alone[end++] = 1;
+        }
+        for (int k = c; k < end; ++k) {
+            b->launch_end[k] = k + 1;
+            b->team[k] = 1;
+        }
+    }
     std::vector<int32_t> kc(b->count);
     for (int32_t i = 0; i < b->count; ++i)
         kc[i] = o.kernel_cycles[cls[i]] > 0 ? o.kernel_cycles[cls[i]] : b->kc_auto[i];
     BHIP(b, hipMemcpyAsync(b->d_order, b->order.data(), sizeof(int32_t) * b->count, hipMemcpyHostToDevice,
+                           b->stream));
+    BHIP(b, hipMemcpyAsync(b->d_order + b->count, teams.data(), sizeof(int32_t) * b->count, hipMemcpyHostToDevice,
                            b->stream));
     BHIP(b, hipMemcpyAsync(b->d_kc, kc.data(), sizeof(int32_t) * b->count, hipMemcpyHostToDevice, b->stream));
     BHIP(b, hipStreamSynchronize(b->stream));
@@ -182,23 +250,31 @@ int apply_config(mf_batch_t *b) {
     return MF_OK;
 }
 
-// Launch class c alone on stream st.
-hipError_t launch_class(mf_batch_t *b, int c, hipStream_t st) {
-    const int32_t beg = b->class_begin[c], cnt = b->class_begin[c + 1] - beg;
+// Launch the classes [first, end) on stream st, `team` workgroups per instance
+// (the control words of a team launch are cleared).
+hipError_t launch_classes(mf_batch_t *b, int first, int end, int team, hipStream_t st) {
+    const int32_t beg = b->class_begin[first], cnt = b->class_begin[end] - beg;
     if (cnt == 0) return hipSuccess;
-    return mf::launch_batch(b->d_graphs, b->d_order + beg, cnt, b->params, b->d_kc, b->d_res,
-                            b->opts.block[c], st);
+    if (team == 1)
+        return mf::launch_batch(b->d_graphs, b->d_order + beg, cnt, b->params, b->d_kc, b->d_res,
+                                b->opts.block[first], st);
+    const int32_t *order = b->d_order + (end - first > 1 ? b->count : 0) + beg;
+    return mf::launch_batch_teams(b->d_graphs, order, cnt, b->params, b->d_kc, b->d_res,
+                                  b->d_ctl + first, team, b->blocks, st);
 }
 
 // All classes side by side: fork from the main stream, one class per side
 // stream, join back.  Recorded into a graph when the main stream captures.
 hipError_t enqueue_all(mf_batch_t *b) {
-    hipError_t e = hipEventRecord(b->fork_ev, b->stream);
+    hipError_t e = mf::launch_batch_reset(b->d_ctl, MF_BATCH_MAX_CLASSES, b->d_res, b->count, b->stream);
     if (e != hipSuccess) return e;
-    for (int c = 0; c < b->opts.n_classes; ++c) {
-        if (b->class_begin[c + 1] == b->class_begin[c]) continue;
+    if ((e = hipEventRecord(b->fork_ev, b->stream)) != hipSuccess) return e;
+    for (int c = 0, end = 0; c < b->opts.n_classes; c = end) {
+        end = b->launch_end[c];
+        if (b->class_begin[end] == b->class_begin[c]) continue;
         if ((e = hipStreamWaitEvent(b->side[c], b->fork_ev, 0)) != hipSuccess) return e;
-        if ((e = launch_class(b, c, b->side[c])) != hipSuccess) return e;
+        e = launch_classes(b, c, end, b->team[c], b->side[c]);
+        if (e != hipSuccess) return e;
         if ((e = hipEventRecord(b->join_ev[c], b->side[c])) != hipSuccess) return e;
         if ((e = hipStreamWaitEvent(b->stream, b->join_ev[c], 0)) != hipSuccess) return e;
     }
@@ -392,9 +468,10 @@ MF_API int mf_batch_create(int32_t count, const int32_t *n, const int64_t *m, co
     BALLOC(hcount_d, sum_n + count);
     BALLOC(ctrl_d, count);
     BALLOC(b->d_graphs, count);
-    BALLOC(b->d_order, count);
+    BALLOC(b->d_order, 2 * (int64_t)count);
     BALLOC(b->d_kc, count);
     BALLOC(b->d_res, count);
+    BALLOC(b->d_ctl, MF_BATCH_MAX_CLASSES);
 #undef BALLOC
     b->g.resize(count);
     b->cap_limit = lim;
@@ -481,6 +558,10 @@ MF_API int mf_batch_create(int32_t count, const int32_t *n, const int64_t *m, co
     pr.max_iter = -1;
     pr.deadline_ticks = budget_ms * (int64_t)clock_khz;
     pr.barrier_ticks = 10000 * (int64_t)clock_khz;
+    pr.join_ticks = clock_khz / 10;
+    int cus = 0;
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, o.device);
+    b->blocks = std::max(1, cus / mf::kXcds) * mf::kXcds;
     pr.relabel_budget = 0;  // per instance: max(1024, n/16)
     pr.max_rounds = 65536;
     pr.seq_base = 1;
@@ -550,8 +631,9 @@ MF_API int mf_batch_solve_class(mf_batch_t *b, int32_t c, double *kernel_ms) {
     if (!b) return bfail(nullptr, MF_EINVAL, "null batch");
     if (c < 0 || c >= b->opts.n_classes) return bfail(b, MF_EINVAL, "class out of range");
     BHIP(b, hipSetDevice(b->device));
+    BHIP(b, mf::launch_batch_reset(b->d_ctl, MF_BATCH_MAX_CLASSES, b->d_res, b->count, b->stream));
     BHIP(b, hipEventRecord(b->ev[0], b->stream));
-    BHIP(b, launch_class(b, c, b->stream));
+    BHIP(b, launch_classes(b, c, c + 1, b->team_alone[c], b->stream));
     BHIP(b, hipEventRecord(b->ev[1], b->stream));
     BHIP(b, hipMemcpyAsync(b->h_res, b->d_res, sizeof(mf::BatchResult) * b->count, hipMemcpyDeviceToHost,
                            b->stream));

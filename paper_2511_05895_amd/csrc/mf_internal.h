@@ -100,15 +100,19 @@ struct alignas(32) ListCtr {
     int32_t pad[4];
 };
 
-// Device control block: barrier words on their own cache lines, then loop
-// counters.  Reset by k_reset_ctrl before every solving call.
-struct Ctrl {
+// A team's barrier words, on their own cache lines.
+struct BarWords {
     PaddedU32 bar_count;  // monotonic barrier arrivals of the launch (groups, for large teams)
     PaddedU32 abort;
+    PaddedU64 sum[4];     // summing barriers of a run, in turn
+};
+
+// Device control block: barrier words, then loop counters.  Reset by
+// k_reset_ctrl before every solving call.
+struct Ctrl : BarWords {
     PaddedU32 join;       // workgroups that registered for the launch's team (top bit: closed)
     PaddedU32 team_size;  // its size once closed
     PaddedU32 xcd_pick;   // XCD of an XCD-local team, plus one
-    PaddedU64 sum[4];     // summing barriers of a run, in turn
     PaddedU32 bar_group[kBarGroups];  // arrivals per group of workgroups (two-level barrier)
     int32_t qcount[4];  // frontier items per BFS level, triple-buffered
     int32_t qverts[4];  // vertices discovered per BFS level (direction rule), same buffering
@@ -229,6 +233,17 @@ struct LoopParams {
                                // order and stops when the excess is gone (full scan only to relabel)
 };
 
+// Control words of a batch's team launch, cleared before it: the pools of
+// workgroups that form on each XCD, the next instance of the order, and every
+// team's barriers.
+constexpr int kBatchXccs = 16;  // values XCC_ID can take
+constexpr int kBatchTeams = 16; // teams per XCD
+struct BatchCtl {
+    PaddedU32 join[kBatchXccs], size[kBatchXccs];
+    PaddedU32 next;
+    BarWords team[kBatchXccs * kBatchTeams];
+};
+
 // Result of one instance of a batched solve.
 struct BatchResult {
     int64_t value;   // e(t) plus the deficits
@@ -263,6 +278,13 @@ hipError_t launch_check_state(const DevGraph &g, int solved, hipStream_t st);
 // KERNELCYCLES kc[order[j]] and writes res[order[j]].
 hipError_t launch_batch(const DevGraph *graphs, const int32_t *order, int count, const LoopParams &p,
                         const int32_t *kc, BatchResult *res, int block, hipStream_t st);
+// The same with teams of `team` workgroups (kBlock threads) of one XCD that take
+// instances from the order in turn; blocks: workgroups launched.  *ctl and the
+// results' statuses are cleared by launch_batch_reset first.
+hipError_t launch_batch_teams(const DevGraph *graphs, const int32_t *order, int count, const LoopParams &p,
+                              const int32_t *kc, BatchResult *res, BatchCtl *ctl, int team, int blocks,
+                              hipStream_t st);
+hipError_t launch_batch_reset(BatchCtl *ctl, int nctl, BatchResult *res, int count, hipStream_t st);
 hipError_t launch_fill_i32(int32_t *p, int64_t count, int32_t value, hipStream_t st);
 hipError_t launch_fill_f32(float *p, int64_t count, float value, hipStream_t st);
 // Value network (mf_policy.hip): loss gradient over N samples (grad and loss
