@@ -83,6 +83,7 @@ struct mf_handle {
     // an arc of the layout to its index in the layout of the caller's
     // numbering, computed on the first export or import that needs it.
     std::vector<int32_t> new_of_old, old_of_new, caller_of_arc;
+    int32_t *d_new_of_old = nullptr;  // the same on the device (null: the caller's numbering)
     int32_t combine = 0;
     double tick_ms = 1e-5;  // one wall-clock tick in ms
     int32_t seq = 1;  // next round id; round ids stamp mark[] and rmark[]
@@ -799,6 +800,7 @@ MF_API int mf_create(const mf_csr_t *g, const int32_t *cap, int32_t s, int32_t t
         d.cap = lay.cap;
         d.edge2arc = lay.edge2arc;
         d.ecap = lay.ecap;
+        h->d_new_of_old = lay.new_of_old;
     }
     // s and t in the layout's numbering
     if (!h->new_of_old.empty()) {
@@ -847,7 +849,7 @@ MF_API int mf_create(const mf_csr_t *g, const int32_t *cap, int32_t s, int32_t t
     ALLOC(d.hcount, (int64_t)n + 1);
     ALLOC(d.heavy_all, (int64_t)heavy.size());
     ALLOC(d.ctrl, 1);
-    ALLOC(h->d_side, n);
+    ALLOC(h->d_side, ((int64_t)n + 3) & ~3ll);  // written in whole words
     ALLOC(h->d_pmark, n);
 #undef ALLOC
     auto up = [&](void *dst, const void *src, size_t bytes) {
@@ -1095,21 +1097,12 @@ MF_API int mf_min_cut(mf_handle_t *h, uint8_t *side_out, int64_t *cut_cap_out) {
     if (!h) return fail(nullptr, MF_EINVAL, "null handle");
     if (h->state != State::Solved) return fail(h, MF_ESTATE, "not solved");
     HIP_TRY(h, hipSetDevice(h->device));
-    HIP_TRY(h, mf::launch_fill_i32(reinterpret_cast<int32_t *>(&h->g.ctrl->cut), 2, 0, h->stream));
-    HIP_TRY(h, mf::launch_min_cut(h->g, h->d_side, h->stream));
-    const bool renum = !h->new_of_old.empty();
-    std::vector<uint8_t> side;
-    if (side_out) {
-        if (renum) side.resize((size_t)h->g.n);
-        HIP_TRY(h, hipMemcpyAsync(renum ? side.data() : side_out, h->d_side, (size_t)h->g.n, hipMemcpyDeviceToHost,
-                                  h->stream));
-    }
-    int64_t cut = 0;
-    HIP_TRY(h, hipMemcpyAsync(&cut, &h->g.ctrl->cut, sizeof(int64_t), hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(h, mf::launch_min_cut(h->g, h->d_new_of_old, side_out ? h->d_side : nullptr, h->stream));
+    HIP_TRY(h, hipMemcpyAsync(&h->h_ctrl->cut, &h->g.ctrl->cut, sizeof(int64_t), hipMemcpyDeviceToHost, h->stream));
+    if (side_out)
+        HIP_TRY(h, hipMemcpyAsync(side_out, h->d_side, (size_t)h->g.n, hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
-    if (side_out && renum)
-        for (int32_t v = 0; v < h->g.n; ++v) side_out[v] = side[h->new_of_old[v]];
-    if (cut_cap_out) *cut_cap_out = cut;
+    if (cut_cap_out) *cut_cap_out = h->h_ctrl->cut;
     return MF_OK;
 }
 
@@ -1140,6 +1133,7 @@ MF_API int64_t mf_estimate_device_bytes(int32_t n, int64_t m) {
     b += 4 * ((int64_t)n + 1);            // hcount
     b += 4 * (int64_t)n;                  // heavy vertices (at most n)
     b += (int64_t)n;                      // cut side
+    b += 4 * (int64_t)n;                  // vertex numbering
     b += (int64_t)sizeof(mf::Ctrl);
     b += 256 * 24;                        // allocation rounding of the ~24 arrays
     return b;

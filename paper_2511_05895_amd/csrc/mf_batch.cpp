@@ -543,7 +543,7 @@ MF_API int mf_batch_create(int32_t count, const int32_t *n, const int64_t *m, co
             hipSuccess ||
         (e = mf::launch_fill_i32(stamp_d, sum_m, 0, b->stream)) != hipSuccess)
         return bail(MF_EDEVICE, std::string("init: ") + hipGetErrorString(e));
-    if ((e = balloc(b, &b->d_side, b->max_n)) != hipSuccess)
+    if ((e = balloc(b, &b->d_side, ((int64_t)b->max_n + 3) & ~3ll)) != hipSuccess)
         return bail(MF_ENOMEM, std::string("hipMalloc side: ") + hipGetErrorString(e));
 
     int clock_khz = 0;
@@ -726,8 +726,7 @@ MF_API int mf_batch_min_cut(mf_batch_t *b, int32_t i, uint8_t *side, int64_t *cu
     if (!b->solved) return bfail(b, MF_ESTATE, "not solved");
     const mf::DevGraph &g = b->g[i];
     BHIP(b, hipSetDevice(b->device));
-    BHIP(b, mf::launch_fill_i32(reinterpret_cast<int32_t *>(&g.ctrl->cut), 2, 0, b->stream));
-    BHIP(b, mf::launch_min_cut(g, side ? b->d_side : nullptr, b->stream));
+    BHIP(b, mf::launch_min_cut(g, nullptr, side ? b->d_side : nullptr, b->stream));
     if (side) BHIP(b, hipMemcpyAsync(side, b->d_side, g.n, hipMemcpyDeviceToHost, b->stream));
     BHIP(b, hipMemcpyAsync(b->h_ctrl, g.ctrl, sizeof(mf::Ctrl), hipMemcpyDeviceToHost, b->stream));
     BHIP(b, hipStreamSynchronize(b->stream));

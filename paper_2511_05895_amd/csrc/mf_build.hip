@@ -462,7 +462,8 @@ hipError_t build_layout_device(int32_t n, int64_t m, const int64_t *h_row_ptr, c
     // every arc list starts with its hub neighbours
     int32_t *d_perm = nullptr;
     if (renumber && n > 0) {
-        BTRY(talloc((void **)&d_perm, sizeof(int32_t) * n));
+        BTRY(mem.alloc_keep((void **)&d_perm, sizeof(int32_t) * n));
+        out->new_of_old = d_perm;
         BTRY(hipMemsetAsync(d_perm, 0, sizeof(int32_t) * n, st));
         if (m > 0) hipLaunchKernelGGL(k_degree, dim3(grid_of(m)), dim3(256), 0, st, d_tail, d_col, m, d_perm);
         hipLaunchKernelGGL(k_vertex_keys, dim3(grid_of(n)), dim3(256), 0, st, d_perm, n, b, d_k0, d_v0);

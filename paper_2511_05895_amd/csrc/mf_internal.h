@@ -139,7 +139,9 @@ struct Ctrl : BarWords {
     int32_t trace[kTraceCap][kTraceFields];
     int64_t deficit;    // sum of e(v) < 0 over v not in {s, t} at termination
     int64_t e_t;        // e(t) at termination
-    int64_t cut;        // cut capacity (k_min_cut)
+    int64_t cut;        // cut capacity
+    int32_t cut_items;  // pieces of long arc lists still to be summed into it
+    int32_t cut_pad;
     // state of the rounds a workgroup ran alone, handed to the others
     int64_t run_arcs;   // arcs of the vertices that BFS runs discovered (this launch)
     int32_t solo_r, solo_done, solo_reason, solo_last_change;
@@ -268,7 +270,9 @@ hipError_t launch_clamp(const DevGraph &g, const int64_t *ids, int64_t k, hipStr
 hipError_t launch_local_stage(const DevGraph &g, const int64_t *ids, int64_t k, int32_t *pmark, int32_t tag0,
                               int rounds, hipStream_t st);
 hipError_t launch_loop(const DevGraph &g, const LoopParams &p, int grid, hipStream_t st);
-hipError_t launch_min_cut(const DevGraph &g, uint8_t *d_side, hipStream_t st);
+// Source side (d_side: n bytes, in whole words, in the order of the caller's
+// ids; or null) and cut capacity (ctrl->cut); uses the frontier buffer q[0].
+hipError_t launch_min_cut(const DevGraph &g, const int32_t *new_of_old, uint8_t *d_side, hipStream_t st);
 // Invariant check of the state into ctrl->check (cleared first): 1 c_f < 0,
 // 2 pair sum broken, 4 excess != residual change, and when solved 8 active
 // vertex left, 16 residual arc from the source side to the sink side.
@@ -344,6 +348,7 @@ struct DeviceLayout {
     int32_t *cap = nullptr;       // A
     int32_t *edge2arc = nullptr;  // m, -1 for self-loops
     int32_t *ecap = nullptr;      // m: the input capacities
+    int32_t *new_of_old = nullptr;  // n: the renumbering (null: none)
 };
 // Inputs are host arrays already checked (row pointers monotone from 0 to m,
 // heads in range, capacities >= 0).  With renumber, the layout numbers the
