@@ -76,8 +76,7 @@ enum : int {
     kStCount
 };
 
-// Groups of the two-level grid barrier.
-constexpr int kBarGroups = 8;
+constexpr int kXccIds = 16;  // values the number of an XCD can take
 struct alignas(128) PaddedU32 {
     uint32_t v;
     uint32_t pad[31];
@@ -102,7 +101,7 @@ struct alignas(32) ListCtr {
 
 // A team's barrier words, on their own cache lines.
 struct BarWords {
-    PaddedU32 bar_count;  // monotonic barrier arrivals of the launch (groups, for large teams)
+    PaddedU32 bar_count;  // monotonic barrier arrivals of the launch
     PaddedU32 abort;
     PaddedU64 sum[4];     // summing barriers of a run, in turn
 };
@@ -113,7 +112,9 @@ struct Ctrl : BarWords {
     PaddedU32 join;       // workgroups that registered for the launch's team (top bit: closed)
     PaddedU32 team_size;  // its size once closed
     PaddedU32 xcd_pick;   // XCD of an XCD-local team, plus one
-    PaddedU32 bar_group[kBarGroups];  // arrivals per group of workgroups (two-level barrier)
+    PaddedU32 bar_top;    // XCDs that arrived (teams all over the device)
+    PaddedU32 bar_xcd[kXccIds];      // arrivals per XCD
+    PaddedU32 bar_members[kXccIds];  // the team's workgroups per XCD
     int32_t qcount[4];  // frontier items per BFS level, triple-buffered
     int32_t qverts[4];  // vertices discovered per BFS level (direction rule), same buffering
     int64_t qarcs[4];   // their arcs
@@ -238,12 +239,11 @@ struct LoopParams {
 // Control words of a batch's team launch, cleared before it: the pools of
 // workgroups that form on each XCD, the next instance of the order, and every
 // team's barriers.
-constexpr int kBatchXccs = 16;  // values XCC_ID can take
 constexpr int kBatchTeams = 16; // teams per XCD
 struct BatchCtl {
-    PaddedU32 join[kBatchXccs], size[kBatchXccs];
+    PaddedU32 join[kXccIds], size[kXccIds];
     PaddedU32 next;
-    BarWords team[kBatchXccs * kBatchTeams];
+    BarWords team[kXccIds * kBatchTeams];
 };
 
 // Result of one instance of a batched solve.

@@ -262,72 +262,81 @@ struct Team {
     __device__ int64_t nwaves() const { return (int64_t)size * (blockDim.x >> 6); }
 };
 
-// Barrier of a team with a bounded wait.  Arrivals count up monotonic
-// counters (cleared before every launch): barrier number `epoch` (0, 1, ...)
-// is complete once the top counter reaches (epoch + 1) * size, or, for a team
-// of 2 * kBarGroups workgroups or more, (epoch + 1) * kBarGroups, one count per
-// group whose own counter reached (epoch + 1) * its size.  One release fence before
-// the arrival and one acquire fence after the wait; the polls themselves are
-// relaxed loads, so waiting does not keep invalidating the caches that the
-// team's other workgroups are still working from.  Returns false when the
-// wait ran out (wall clock, `limit` ticks) or another workgroup aborted; the
-// caller must then leave the kernel, so every workgroup ends even if
-// co-residency ever failed.  Every thread of every workgroup of the team calls
-// it with the same epoch, which it advances.
+// Number of the XCD that runs this wave: hardware register XCC_ID (id 20), low
+// four bits.
+__device__ __forceinline__ int xcd_id() { return (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & (kXccIds - 1)); }
+
+// Barrier of a team with a bounded wait.  Arrivals count up monotonic counters
+// (cleared before every launch).  A team of one XCD has one counter and needs
+// no cache maintenance.  A team all over the device arrives XCD by XCD: the
+// workgroups of an XCD wait until their stores are in its L2 and count up the
+// XCD's counter, and the last of them alone writes that L2 back (the release
+// fence) and counts up the top counter, which every workgroup polls.  The
+// write-back is what such a barrier costs; made by every workgroup
+// such a barrier of 256 took 8.5 to 10.4 us, made once per XCD 3.9 to 5.2
+// (solve of R-MAT 2^22 x 16: 8.67 -> 8.25 ms, 1000 x 1000 grid: 175 -> 162 ms).
+// How many workgroups an XCD has in the team is counted at the first barrier
+// (`epoch` 0), at which every workgroup writes back and arrives at bar_count.
+// One acquire fence after the wait; the polls themselves are relaxed loads,
+// so waiting does not keep invalidating the caches that the team's other
+// workgroups are still working from.  Returns false when the wait ran out
+// (wall clock, `limit` ticks) or another workgroup aborted; the caller must
+// then leave the kernel, so every workgroup ends even if co-residency ever
+// failed.  Every thread of every workgroup of the team calls it with the same
+// epoch, which it advances.
 template <int SC>
 __device__ __forceinline__ bool grid_barrier(Ctrl *c, const Team &tm, uint32_t &epoch, int64_t limit) {
+    if constexpr (SC == kAgent) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     block_sync<SC>();
     if (tm.size == 1) return true;
     __shared__ int s_ok;
-    const uint32_t e1 = epoch + 1u;
-    ++epoch;
+    __shared__ uint32_t s_members, s_xcds;  // the team's workgroups on this XCD, its XCDs
     if (threadIdx.x == 0) {
         int ok = 1;
-        if constexpr (SC != kXcd) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        // Arrivals: a team of 2 * kBarGroups workgroups or more arrives in
-        // kBarGroups groups (rank mod kBarGroups), each on a counter of its own
-        // line, and the last arrival of a group (the one that completes its
-        // count) acquires the group's writes and releases them on to the top
-        // counter, which every workgroup polls.  Arrivals on one word
-        // serialise; this way each word takes a group's share of them.
-        const int G = SC == kXcd || tm.size < 2 * kBarGroups ? 1 : kBarGroups;
-        uint32_t target, before;
-        if (G == 1) {
-            target = e1 * (uint32_t)tm.size;
-            before = __hip_atomic_fetch_add(&c->bar_count.v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t target;
+        PaddedU32 *top = &c->bar_count;
+        if (SC == kXcd || epoch == 0) {
+            if constexpr (SC == kAgent) {
+                __hip_atomic_fetch_add(&c->bar_members[xcd_id()].v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            }
+            target = (epoch + 1u) * (uint32_t)tm.size;
+            __hip_atomic_fetch_add(&top->v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
-            const int gid = tm.rank % G;
-            const uint32_t ng = (uint32_t)((tm.size - gid + G - 1) / G);
-            target = e1 * (uint32_t)G;
-            before = target - 2u;  // not the last of its group: wait
-            if (__hip_atomic_fetch_add(&c->bar_group[gid].v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
-                e1 * ng) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
-                before = __hip_atomic_fetch_add(&c->bar_count.v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            top = &c->bar_top;
+            target = epoch * s_xcds;
+            if (__hip_atomic_fetch_add(&c->bar_xcd[xcd_id()].v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+                epoch * s_members) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                __hip_atomic_fetch_add(&top->v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
-        if ((int32_t)(before + 1u - target) < 0) {
-            const uint64_t tw = wall_clock64();
-            uint32_t spins = 0;
-            while ((int32_t)(__hip_atomic_load(&c->bar_count.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
-                             target) < 0) {
-                if constexpr (SC != kXcd) __builtin_amdgcn_s_sleep(1);
-                if ((++spins & 255u) == 0) {
-                    if (__hip_atomic_load(&c->abort.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                        ok = 0;
-                        break;
-                    }
-                    if ((int64_t)(wall_clock64() - tw) > limit) {
-                        __hip_atomic_store(&c->abort.v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        ok = 0;
-                        break;
-                    }
+        uint32_t spins = 0;
+        uint64_t tw = 0;
+        while ((int32_t)(__hip_atomic_load(&top->v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
+            if ((++spins & 255u) == 0) {
+                if (tw == 0) tw = wall_clock64();
+                if (__hip_atomic_load(&c->abort.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
+                    (int64_t)(wall_clock64() - tw) > limit) {
+                    __hip_atomic_store(&c->abort.v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    ok = 0;
+                    break;
                 }
             }
         }
-        if constexpr (SC != kXcd) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if constexpr (SC == kAgent) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            if (epoch == 0) {
+                uint32_t xcds = 0;
+                for (int x = 0; x < kXccIds; ++x)
+                    xcds += __hip_atomic_load(&c->bar_members[x].v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+                s_xcds = xcds;
+                s_members = __hip_atomic_load(&c->bar_members[xcd_id()].v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
         s_ok = ok;
     }
+    ++epoch;
     __syncthreads();
     return s_ok != 0;
 }
@@ -449,8 +458,7 @@ __device__ __forceinline__ Team join_team(Ctrl *c, int want, int64_t limit) {
         int rank = -1, size = 0;
         bool in = true;
         if constexpr (SC == kXcd) {
-            // hardware register XCC_ID (id 20), low four bits: this wave's XCD
-            const uint32_t me = (__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u) + 1u;
+            const uint32_t me = (uint32_t)xcd_id() + 1u;
             uint32_t first = 0;
             in = __hip_atomic_compare_exchange_strong(&c->xcd_pick.v, &first, me, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                       __HIP_MEMORY_SCOPE_AGENT) ||
@@ -3040,9 +3048,9 @@ __global__ void k_pull_round(DevGraph g, const int64_t *ids, int64_t k, const in
 // far, and a list of it is read in order with one height gather per arc; only
 // a crossing arc reads its twin and that arc's capacity.  Lists of more than
 // kChunk arcs go to k_cut_items in items, so a hub is split over the device.
-// Bound by the read of the heights when the sink side is small.  R-MAT 2^22 x 16: 5.1 ms (scanning
-// the source side, the numbering undone on the host) -> 0.36 ms; 2^20: 1.12 ->
-// 0.12 ms; a 512 x 512 grid: 175 -> 101 us.
+// Bound by the read of the heights when the sink side is small.  R-MAT 2^22 x
+// 16: 5.1 ms (scanning the source side, the numbering undone on the host) ->
+// 0.36 ms; 2^20: 1.12 -> 0.12 ms; a 512 x 512 grid: 175 -> 101 us.
 __device__ __forceinline__ int64_t cut_arc(const DevGraph &g, int a) {
     return g.h[g.arc[a].x] >= g.n ? (int64_t)g.cap[g.twin[a]] : 0;
 }
@@ -3205,7 +3213,7 @@ __global__ void __launch_bounds__(kBlock)
     k_batch_teams(const DevGraph *__restrict__ graphs, const int32_t *__restrict__ order, int count, LoopParams p,
                   const int32_t *__restrict__ kc, BatchResult *__restrict__ res, BatchCtl *ctl, int team) {
     __shared__ int s_rank, s_size;
-    const int xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & (kBatchXccs - 1));
+    const int xcc = xcd_id();
     if (threadIdx.x == 0) close_pool(&ctl->join[xcc], &ctl->size[xcc], p.team_want, p.join_ticks, &s_rank, &s_size);
     __syncthreads();
     if (s_rank < 0) return;
