@@ -505,43 +505,72 @@ __device__ __forceinline__ void flush_tally(Ctrl *c, Tally &t) {
 // Height reset: t and every deficient vertex other than s are roots (height
 // 0); all others get |V|.  Roots become the level-0 frontier.  With part
 // tags, only vertices of the wanted part can be roots, and with part_restrict
-// the heights of the other vertices are left alone.
-template <int SC>
-__device__ __forceinline__ void bfs_roots(const DevGraph &g, const Team &tm, bool counts, bool feats, bool track, Tally &tl) {
-    const int64_t gtid = tm.tid();
-    const int64_t stride = tm.nthreads();
-    const int64_t nr = ((int64_t)g.n + 63) & ~63ll;
-    for (int64_t i = gtid; i < nr; i += stride) {
-        const int v = (int)i;
-        bool root = false;
-        int beg = 0, end = 0;
-        if (i < g.n) {
-            const bool mine = !g.part || g.part[v] == g.part_want;
-            if (mine || !g.part_restrict) {
-                root = mine && ((v == g.t) || (v != g.s && get<SC>(&g.e[v]) < 0));
-                g.h[v] = root ? 0 : g.n;
-            }
-            if (root) {
-                beg = g.row_ptr[v];
-                end = g.row_ptr[v + 1];
-            }
+// the heights of the other vertices are left alone.  Returns the lane's share
+// of the deficits, of all parts.
+//
+// One pass over e and h, bound by the latency of its loads where the team has
+// fewer threads than the graph vertices: a wavefront then has U = 4 groups of
+// 64 vertices in flight, and the work for roots, which are few, is left to the
+// wavefronts that find one.  4.2 M vertices on 256 workgroups, this pass and a second one for
+// the deficits after the last relabel: 100 us of solve kernel per update, 85 us
+// with the groups and without the second pass.
+template <int SC, int U>
+__device__ __forceinline__ int64_t bfs_roots_by(const DevGraph &g, const Team &tm, bool counts, bool feats, bool track, Tally &tl) {
+    const int lane = lane_id();
+    int64_t deficit = 0;
+    for (int64_t base = tm.wave() * 64 * U; base < g.n; base += tm.nwaves() * 64 * U) {
+        bool root[U];
+        bool any = false;
+        int64_t ev[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int64_t i = base + 64 * k + lane;
+            ev[k] = i < g.n ? get<SC>(&g.e[i]) : 0;
         }
-        const int c = root ? n_items(end - beg) : 0;
-        const int nroot = __popcll(__ballot(root));
-        if (counts && lane_id() == 0 && nroot) add<SC>(&g.hcount[0], nroot);
-        if (feats && lane_id() == 0 && nroot) add<SC>(&g.ctrl->feat_reached, nroot);
-        if (track && nroot) {
-            const int64_t ra = wave_sum((int64_t)(end - beg));
-            if (lane_id() == 0) {
-                add<SC>(&g.ctrl->qverts[0], nroot);
-                add<SC>(&g.ctrl->qarcs[0], ra);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int64_t i = base + 64 * k + lane;
+            const int v = (int)i;
+            root[k] = false;
+            if (i < g.n) {
+                if (ev[k] < 0 && v != g.s && v != g.t) deficit += ev[k];
+                const bool mine = !g.part || g.part[v] == g.part_want;
+                if (mine || !g.part_restrict) {
+                    root[k] = mine && (v == g.t || (v != g.s && ev[k] < 0));
+                    g.h[v] = root[k] ? 0 : g.n;
+                }
             }
+            any |= root[k];
         }
-        const int base = wave_appendn<SC>(&g.ctrl->qcount[0], c);
-        for (int j = 0; j < c; ++j)
-            g.q[0][base + j] = make_int2(beg + j * kChunk, min(beg + (j + 1) * kChunk, end));
-        tl.bfs_v += root;
+        if (__ballot(any) == 0) continue;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = (int)(base + 64 * k + lane);
+            const int nroot = __popcll(__ballot(root[k]));
+            if (nroot == 0) continue;
+            const int beg = root[k] ? g.row_ptr[v] : 0, end = root[k] ? g.row_ptr[v + 1] : 0;
+            const int c = root[k] ? n_items(end - beg) : 0;
+            if (counts && lane == 0) add<SC>(&g.hcount[0], nroot);
+            if (feats && lane == 0) add<SC>(&g.ctrl->feat_reached, nroot);
+            if (track) {
+                const int64_t ra = wave_sum((int64_t)(end - beg));
+                if (lane == 0) {
+                    add<SC>(&g.ctrl->qverts[0], nroot);
+                    add<SC>(&g.ctrl->qarcs[0], ra);
+                }
+            }
+            const int at = wave_appendn<SC>(&g.ctrl->qcount[0], c);
+            for (int j = 0; j < c; ++j)
+                g.q[0][at + j] = make_int2(beg + j * kChunk, min(beg + (j + 1) * kChunk, end));
+            tl.bfs_v += root[k];
+        }
     }
+    return deficit;
+}
+template <int SC>
+__device__ __forceinline__ int64_t bfs_roots(const DevGraph &g, const Team &tm, bool counts, bool feats, bool track, Tally &tl) {
+    return g.n > tm.nthreads() ? bfs_roots_by<SC, 4>(g, tm, counts, feats, track, tl)
+                               : bfs_roots_by<SC, 1>(g, tm, counts, feats, track, tl);
 }
 
 // Features of the learned schedule: excess sum of the active vertices a BFS
@@ -2315,11 +2344,19 @@ __device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, co
     // reached (-1: none yet); the BFS direction rule takes the other arcs as
     // those a bottom-up level scans in full without finding a parent
     int64_t reach_prev = -1;
+    __shared__ int64_t s_def[kBlock / 64];  // the wavefronts' shares of the deficits
     for (;;) {
         // time budget: the leader raised `stop` before the last barrier, so
         // every workgroup sees the same value here
         if (ld<SC>(&c->stop)) {
             if (leader) c->status = kDeadline;
+            int64_t d = 0;  // the last rounds changed it
+            for (int64_t v = tm.tid(); v < g.n; v += tm.nthreads()) {
+                const int64_t ev = get<SC>(&g.e[v]);
+                if (ev < 0 && v != g.s && v != g.t) d += ev;
+            }
+            d = wave_sum(d);
+            if (lane_id() == 0) s_def[threadIdx.x >> 6] = d;
             break;
         }
         // --- global relabel ---
@@ -2348,7 +2385,10 @@ __device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, co
         // no level will reach (estimated by those the previous global relabel
         // did not reach) have their whole arc lists scanned at every level
         const bool dir = p.bu_alpha > 0 && g.bu_items != nullptr && !g.part_restrict;
-        bfs_roots<SC>(g, tm, counts, feats, dir, tl);
+        {
+            const int64_t d = wave_sum(bfs_roots<SC>(g, tm, counts, feats, dir, tl));
+            if (lane_id() == 0) s_def[threadIdx.x >> 6] = d;
+        }
         if (!grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
         int L = 0;
         bool bu = false;
@@ -2531,21 +2571,16 @@ __device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, co
         if (!grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
         ++iter;
     }
-    // --- value: e(t) plus the deficits of vertices other than s and t ---
+    // --- value: e(t) plus the deficits of vertices other than s and t, which
+    // nothing changed since the last global relabel read them ---
     // (every workgroup reaches this point after the same, uniform decision)
     {
-        __shared__ int64_t s_def;
-        if (threadIdx.x == 0) s_def = 0;
         __syncthreads();
-        int64_t part = 0;
-        for (int64_t v = tm.tid(); v < g.n; v += tm.nthreads()) {
-            const int64_t ev = get<SC>(&g.e[v]);
-            if (ev < 0 && v != g.s && v != g.t) part += ev;
+        if (threadIdx.x == 0) {
+            int64_t sum = 0;
+            for (int w = 0; w < (int)(blockDim.x >> 6); ++w) sum += s_def[w];
+            if (sum) add<SC>(&c->deficit, sum);
         }
-        part = wave_sum(part);
-        if (lane_id() == 0 && part) atomicAdd((unsigned long long *)&s_def, (unsigned long long)part);
-        __syncthreads();
-        if (threadIdx.x == 0 && s_def) add<SC>(&c->deficit, s_def);
         if (leader) c->e_t = get<SC>(&g.e[g.t]);
     }
     flush_tally<SC>(c, tl);
