@@ -207,11 +207,16 @@ void release(mf_handle_t *h) {
     if (h->own_stream) (void)hipStreamDestroy(h->own_stream);
 }
 
-// Read back the control block and wait for the call's GPU work.
-int finish_call(mf_handle_t *h) {
-    HIP_TRY(h, hipMemcpyAsync(h->h_ctrl, h->g.ctrl, sizeof(mf::Ctrl), hipMemcpyDeviceToHost, h->stream));
+// Wait for the call's GPU work, with the control block read back.  sent: the
+// solve kernel stores it to the host itself; one that left early did not, and
+// kNotSent is still there.
+constexpr int32_t kNotSent = -1;
+int finish_call(mf_handle_t *h, bool sent = false) {
+    if (!sent)
+        HIP_TRY(h, hipMemcpyAsync(h->h_ctrl, h->g.ctrl, sizeof(mf::Ctrl), hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipEventRecord(h->ev[3], h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (sent && h->h_ctrl->status == kNotSent) return finish_call(h);
     return MF_OK;
 }
 
@@ -298,8 +303,10 @@ void add_stats(mf_stats_t &s, const mf_stats_t &x) {
 
 // Launch the persistent loop on g (the handle's graph, or a part-restricted
 // view of it), read back, interpret the status.  prior: counters of earlier
-// launches of the same call, added to the call's statistics.
-int run_loop_and_finish(mf_handle_t *h, const mf::DevGraph *gsel = nullptr, const mf_stats_t *prior = nullptr) {
+// launches of the same call, added to the call's statistics.  b: the batch that
+// the kernel repairs first.
+int run_loop_and_finish(mf_handle_t *h, const mf::DevGraph *gsel = nullptr, const mf_stats_t *prior = nullptr,
+                        mf::Repair b = {}) {
     int rc = fresh_round_ids(h, h->g, h->seq);
     if (rc) return rc;
     const mf::DevGraph &g = gsel ? *gsel : h->g;
@@ -308,9 +315,11 @@ int run_loop_and_finish(mf_handle_t *h, const mf::DevGraph *gsel = nullptr, cons
     // again before every later global relabel); only the heuristic reads them
     if (h->use_gap) HIP_TRY(h, mf::launch_fill_i32(h->g.hcount, (int64_t)h->g.n + 1, 0, h->stream));
     HIP_TRY(h, hipEventRecord(h->ev[1], h->stream));
-    HIP_TRY(h, mf::launch_loop(g, p, h->grid, h->stream));
+    b.host = h->h_ctrl;
+    h->h_ctrl->status = kNotSent;
+    HIP_TRY(h, mf::launch_loop(g, p, b, h->grid, h->stream));
     HIP_TRY(h, hipEventRecord(h->ev[2], h->stream));
-    rc = finish_call(h);
+    rc = finish_call(h, true);
     if (rc) return rc;
     const mf::Ctrl &c = *h->h_ctrl;
     if (c.err) return MF_EINVAL;  // caller reports the message
@@ -332,6 +341,16 @@ int run_loop_and_finish(mf_handle_t *h, const mf::DevGraph *gsel = nullptr, cons
     return fail(h, MF_EDEVICE, "solve kernel aborted (grid barrier wait ran out)");
 }
 
+mf::Repair batch_of(const mf_handle_t *h, const int64_t *d_ids, const int32_t *d_caps, int64_t k) {
+    mf::Repair b;
+    b.ids = d_ids;
+    b.caps = d_caps;
+    b.k = k;
+    b.epoch = h->epoch;
+    b.cap_limit = h->cap_limit;
+    return b;
+}
+
 int update_error_text(mf_handle_t *h, int32_t err) {
     std::string msg = "invalid update batch:";
     if (err & 1) msg += " edge id out of range;";
@@ -349,8 +368,8 @@ int next_epoch(mf_handle_t *h) {
     return MF_OK;
 }
 
-// Upload a host batch through pinned staging (an upload from pageable memory
-// is staged by the runtime, synchronously).  A call that failed part-way may
+// Lay a host batch out in pinned staging, from where the call's first kernel
+// fetches it (begin_staged).  A call that failed part-way may
 // have left the previous copies queued, so the stream is drained before the
 // pinned buffers are written or freed (a no-op after a completed call).
 int stage_host_batch(mf_handle_t *h, const int64_t *ids, const int32_t *caps, int64_t k) {
@@ -383,9 +402,19 @@ int stage_host_batch(mf_handle_t *h, const int64_t *ids, const int32_t *caps, in
     if (k > 0) {
         std::memcpy(h->p_stage, ids, sizeof(int64_t) * k);
         std::memcpy(h->p_stage + sizeof(int64_t) * k, caps, sizeof(int32_t) * k);
-        HIP_TRY(h, hipMemcpyAsync(h->d_stage, h->p_stage, kPer * k, hipMemcpyHostToDevice, h->stream));
     }
     return MF_OK;
+}
+
+// Start of a call whose batch is in the pinned staging: a small batch is fetched
+// by the call's first kernel, a larger one copied (update of 100 k edges of
+// R-MAT 2^16: fetched 372 us, copied 307).
+hipError_t begin_staged(mf_handle_t *h, int64_t k) {
+    const int64_t words = 3 * k;
+    if (k <= mf::kRepairMax) return mf::launch_begin(h->g, h->p_stage, h->d_stage, words, h->stream);
+    const hipError_t e =
+        hipMemcpyAsync(h->d_stage, h->p_stage, sizeof(int32_t) * words, hipMemcpyHostToDevice, h->stream);
+    return e == hipSuccess ? mf::launch_reset_ctrl(h->g, h->stream) : e;
 }
 
 // Allocate the second view of the state (see mf_handle::views).
@@ -491,8 +520,8 @@ int run_two_views(mf_handle_t *h, const mf::DevGraph &a, mf::LoopParams pa, int3
             return hip_fail(h, le, "two-team launch");
         }
     } else {  // one workgroup (or a grid the two-team kernel cannot hold): one side after the other
-        HIP_TRY(h, mf::launch_loop(ga, pa, h->grid, h->stream));
-        HIP_TRY(h, mf::launch_loop(gb, pb, h->grid, h->stream));
+        HIP_TRY(h, mf::launch_loop(ga, pa, mf::Repair{}, h->grid, h->stream));
+        HIP_TRY(h, mf::launch_loop(gb, pb, mf::Repair{}, h->grid, h->stream));
     }
     HIP_TRY(h, hipMemcpyAsync(&h->h_vctrl[0], ga.ctrl, sizeof(mf::Ctrl), hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipMemcpyAsync(&h->h_vctrl[1], gb.ctrl, sizeof(mf::Ctrl), hipMemcpyDeviceToHost, h->stream));
@@ -591,8 +620,9 @@ int debug_check(mf_handle_t *h, int rc) {
     return fail(h, MF_EDEVICE, "debug check failed");
 }
 
-// Dynamic repair and re-solve with batch arrays already on the device.
-int apply_device(mf_handle_t *h, const int64_t *d_ids, const int32_t *d_caps, int64_t k) {
+// Dynamic repair and re-solve with batch arrays on the device (staged: once the
+// call's first kernel has fetched them).
+int apply_device(mf_handle_t *h, const int64_t *d_ids, const int32_t *d_caps, int64_t k, bool staged = false) {
     if (h->state != State::Solved && h->state != State::Partial)
         return fail(h, MF_ESTATE, "mf_apply_updates needs a flow: call mf_solve first");
     if (k < 0 || k > h->g.m) return fail(h, MF_EINVAL, "batch size k must be in [0, m]");
@@ -600,10 +630,18 @@ int apply_device(mf_handle_t *h, const int64_t *d_ids, const int32_t *d_caps, in
     int rc = next_epoch(h);
     if (rc) return rc;
     HIP_TRY(h, hipEventRecord(h->ev[0], h->stream));
-    HIP_TRY(h, mf::launch_reset_ctrl(h->g, h->stream));
-    HIP_TRY(h, mf::launch_validate_updates(h->g, d_ids, d_caps, k, h->epoch, h->cap_limit, h->stream));
-    HIP_TRY(h, mf::launch_apply_delta(h->g, d_ids, d_caps, k, h->stream));
-    HIP_TRY(h, mf::launch_clamp(h->g, d_ids, k, h->stream));
+    HIP_TRY(h, staged ? begin_staged(h, k) : mf::launch_reset_ctrl(h->g, h->stream));
+    mf::Repair b = batch_of(h, d_ids, d_caps, k);
+    // The solve kernel repairs a small batch itself; a larger one wants more of
+    // the chip than one workgroup (and, for its pulls, than one workgroup's
+    // team).  Updates of R-MAT 2^16, itself against kernels: 1000 edges 100 to
+    // 117 us, 3000 edges 150 to 130.
+    b.on = !h->push_pull && k <= (h->grid > 1 ? mf::kRepairMax : mf::kBlock);
+    if (!b.on) {
+        HIP_TRY(h, mf::launch_validate_updates(h->g, b, h->stream));
+        HIP_TRY(h, mf::launch_apply_delta(h->g, b, h->stream));
+        HIP_TRY(h, mf::launch_clamp(h->g, b, h->stream));
+    }
     h->batch_fraction = h->g.m > 0 ? (float)((double)k / (double)h->g.m) : 0.f;
     if (h->push_pull) {
         // the batch is checked before anything runs on the two sides
@@ -613,7 +651,7 @@ int apply_device(mf_handle_t *h, const int64_t *d_ids, const int32_t *d_caps, in
         h->state = State::Partial;
         rc = push_pull(h);
     } else {
-        HIP_TRY(h, mf::launch_saturate_source(h->g, h->stream));
+        if (!b.on) HIP_TRY(h, mf::launch_saturate_source(h->g, h->stream));
         // the local stage reads the cut of the last global relabel: only from
         // a solved state
         if (h->local_stage && h->state == State::Solved && k > 0) {
@@ -621,10 +659,13 @@ int apply_device(mf_handle_t *h, const int64_t *d_ids, const int32_t *d_caps, in
                 HIP_TRY(h, mf::launch_fill_i32(h->d_pmark, h->g.n, 0, h->stream));
                 h->ptag = 0;
             }
-            HIP_TRY(h, mf::launch_local_stage(h->g, d_ids, k, h->d_pmark, h->ptag + 1, kPullRounds, h->stream));
+            b.pulls = kPullRounds;
+            b.pmark = h->d_pmark;
+            b.tag = h->ptag + 2;
             h->ptag += kPullRounds + 1;
+            if (!b.on) HIP_TRY(h, mf::launch_local_stage(h->g, b, h->stream));
         }
-        rc = run_loop_and_finish(h);
+        rc = run_loop_and_finish(h, nullptr, nullptr, b);
     }
     if (rc == MF_EINVAL) return update_error_text(h, h->h_ctrl->err);
     return debug_check(h, rc);
@@ -986,7 +1027,7 @@ MF_API int mf_apply_updates(mf_handle_t *h, const int64_t *edge_ids, const int32
     HIP_TRY(h, hipSetDevice(h->device));
     int rc = stage_host_batch(h, edge_ids, new_caps, k);
     if (rc) return rc;
-    return apply_device(h, h->d_ids, h->d_caps, k);
+    return apply_device(h, h->d_ids, h->d_caps, k, true);
 }
 
 MF_API int mf_apply_updates_device(mf_handle_t *h, const int64_t *d_edge_ids, const int32_t *d_new_caps,
@@ -1029,9 +1070,10 @@ MF_API int mf_set_capacities(mf_handle_t *h, const int64_t *edge_ids, const int3
     rc = next_epoch(h);
     if (rc) return rc;
     HIP_TRY(h, hipEventRecord(h->ev[0], h->stream));
-    HIP_TRY(h, mf::launch_reset_ctrl(h->g, h->stream));
-    HIP_TRY(h, mf::launch_validate_updates(h->g, h->d_ids, h->d_caps, k, h->epoch, h->cap_limit, h->stream));
-    HIP_TRY(h, mf::launch_apply_delta(h->g, h->d_ids, h->d_caps, k, h->stream));
+    HIP_TRY(h, begin_staged(h, k));
+    const mf::Repair b = batch_of(h, h->d_ids, h->d_caps, k);
+    HIP_TRY(h, mf::launch_validate_updates(h->g, b, h->stream));
+    HIP_TRY(h, mf::launch_apply_delta(h->g, b, h->stream));
     rc = finish_call(h);
     if (rc) return rc;
     if (h->h_ctrl->err) return update_error_text(h, h->h_ctrl->err);

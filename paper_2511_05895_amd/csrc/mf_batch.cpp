@@ -762,8 +762,14 @@ MF_API int mf_batch_set_capacities(mf_batch_t *b, int32_t i, const int64_t *edge
         b->epoch = 1;
     }
     BHIP(b, mf::launch_reset_ctrl(g, b->stream));
-    BHIP(b, mf::launch_validate_updates(g, b->d_ids, b->d_caps, k, b->epoch, b->cap_limit[i], b->stream));
-    BHIP(b, mf::launch_apply_delta(g, b->d_ids, b->d_caps, k, b->stream));
+    mf::Repair up;
+    up.ids = b->d_ids;
+    up.caps = b->d_caps;
+    up.k = k;
+    up.epoch = b->epoch;
+    up.cap_limit = b->cap_limit[i];
+    BHIP(b, mf::launch_validate_updates(g, up, b->stream));
+    BHIP(b, mf::launch_apply_delta(g, up, b->stream));
     BHIP(b, hipMemcpyAsync(b->h_ctrl, g.ctrl, sizeof(mf::Ctrl), hipMemcpyDeviceToHost, b->stream));
     BHIP(b, hipStreamSynchronize(b->stream));
     b->solved = false;

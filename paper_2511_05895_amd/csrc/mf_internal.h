@@ -236,6 +236,29 @@ struct LoopParams {
                                // order and stops when the excess is gone (full scan only to relabel)
 };
 
+// Edges of a batch that the solve kernel repairs itself at most.
+constexpr int kRepairMax = 2 * kBlock;
+
+// A batch of capacity changes (device arrays), and what a solve kernel does
+// with it before its loop.
+struct Repair {
+    const int64_t *ids = nullptr;
+    const int32_t *caps = nullptr;
+    int64_t k = 0;
+    int32_t epoch = 0;        // stamp of the batch (duplicates)
+    int32_t cap_limit = 0;
+    int32_t on = 0;           // 1: the solve kernel repairs it
+    // Local stage (after the clamp and the source): saturate the updated arcs
+    // that cross the last cut from its source side to its sink side, then
+    // `pulls` rounds of pulls into the deficits at the batch's arc ends (the
+    // last round without handing deficits on).  0: no local stage.  Uses
+    // list[1], list[2] and ctrl->pull_cnt; pmark tags tag - 1 .. tag + pulls.
+    int32_t pulls = 0;
+    int32_t tag = 0;
+    int32_t *pmark = nullptr;
+    Ctrl *host = nullptr;     // pinned; its words from qcount on receive the control block
+};
+
 // Control words of a batch's team launch, cleared before it: the pools of
 // workgroups that form on each XCD, the next instance of the order, and every
 // team's barriers.
@@ -254,22 +277,19 @@ struct BatchResult {
 };
 
 // ---- launch wrappers (mf_kernels.hip) ----
-hipError_t launch_reset_ctrl(const DevGraph &g, hipStream_t st);
+// Clears the control block and copies `words` 4-byte words from pinned host
+// memory.
+hipError_t launch_begin(const DevGraph &g, const void *src, void *dst, int64_t words, hipStream_t st);
+inline hipError_t launch_reset_ctrl(const DevGraph &g, hipStream_t st) { return launch_begin(g, nullptr, nullptr, 0, st); }
 hipError_t launch_init_state(const DevGraph &g, hipStream_t st);
 hipError_t launch_saturate_source(const DevGraph &g, hipStream_t st);
-hipError_t launch_validate_updates(const DevGraph &g, const int64_t *ids, const int32_t *caps,
-                                   int64_t k, int32_t epoch, int32_t cap_limit, hipStream_t st);
-hipError_t launch_apply_delta(const DevGraph &g, const int64_t *ids, const int32_t *caps, int64_t k,
-                              hipStream_t st);
-hipError_t launch_clamp(const DevGraph &g, const int64_t *ids, int64_t k, hipStream_t st);
-// Local stage of a dynamic update (after the clamp and the source
-// re-saturation): saturate the updated arcs that cross the last cut from its
-// source side to its sink side, then `rounds` rounds of pulls into the
-// deficits at the batch's arc ends (the last round without handing deficits
-// on).  Uses list[1], list[2] and ctrl->pull_cnt; pmark tags tag0 .. tag0 + rounds.
-hipError_t launch_local_stage(const DevGraph &g, const int64_t *ids, int64_t k, int32_t *pmark, int32_t tag0,
-                              int rounds, hipStream_t st);
-hipError_t launch_loop(const DevGraph &g, const LoopParams &p, int grid, hipStream_t st);
+hipError_t launch_validate_updates(const DevGraph &g, const Repair &b, hipStream_t st);
+hipError_t launch_apply_delta(const DevGraph &g, const Repair &b, hipStream_t st);
+hipError_t launch_clamp(const DevGraph &g, const Repair &b, hipStream_t st);
+hipError_t launch_local_stage(const DevGraph &g, const Repair &b, hipStream_t st);
+// The solve kernel on a cleared control block.  b: the repair of an update
+// batch, made before the loop, and where the host wants the control block.
+hipError_t launch_loop(const DevGraph &g, const LoopParams &p, const Repair &b, int grid, hipStream_t st);
 // Source side (d_side: n bytes, in whole words, in the order of the caller's
 // ids; or null) and cut capacity (ctrl->cut); uses the frontier buffer q[0].
 hipError_t launch_min_cut(const DevGraph &g, const int32_t *new_of_old, uint8_t *d_side, hipStream_t st);

@@ -2312,15 +2312,14 @@ __device__ __forceinline__ void init_stages() {
 }
 
 template <int SC, bool WALK>
-__device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &p) {
+__device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, const LoopParams &p, uint32_t &bar_epoch) {
     Ctrl *c = g.ctrl;
     if (ld<SC>(&c->err)) return;  // update batch rejected: leave the state alone
     Tally tl;
     const bool leader = tm.rank == 0 && threadIdx.x == 0;
     const bool topology = p.mode == 1;
     int64_t iter = 0;
-    uint32_t bar_epoch = 0;  // barriers this launch has passed
-    uint32_t sum_epoch = 0;  // and summing barriers of its runs
+    uint32_t sum_epoch = 0;  // summing barriers of the launch's runs
     // Runs (frontier or list in LDS) are made by the whole team when it is one
     // workgroup or shares an XCD, and by the first workgroup alone otherwise.
     const Team run_team = SC == kAgent ? Team{0, 1} : tm;
@@ -2586,18 +2585,450 @@ __device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, co
     flush_tally<SC>(c, tl);
 }
 
+// ---------------------------------------------------------------------------
+// Source saturation and repair of a batch
+// ---------------------------------------------------------------------------
+
+// Saturate every residual arc out of s: c_f(s,u) -> 0, the twin gains it,
+// e(u) += d, e(s) -= d (Alg. 1 third loop; Alg. 4 lines 3-8, where the
+// remaining residual is pushed rather than e(u) overwritten).
+template <int SC>
+__device__ __forceinline__ void saturate_source(const DevGraph &g, const Team &tm) {
+    if (ld<SC>(&g.ctrl->err)) return;
+    __shared__ int64_t s_sum, s_cnt;
+    if (threadIdx.x == 0) {
+        s_sum = 0;
+        s_cnt = 0;
+    }
+    __syncthreads();
+    const int beg = g.row_ptr[g.s], end = g.row_ptr[g.s + 1];
+    int64_t sum = 0, cnt = 0;
+    for (int64_t a = beg + tm.tid(); a < end; a += tm.nthreads()) {
+        const int2 r = get<SC>(&g.arc[a]);
+        if (r.y > 0) {
+            g.arc[a].y = 0;
+            add<SC>(cf_ptr(g.arc, g.twin[a]), r.y);
+            add<SC>(&g.e[r.x], (int64_t)r.y);
+            sum += r.y;
+            cnt++;
+        }
+    }
+    sum = wave_sum(sum);
+    cnt = wave_sum(cnt);
+    if (lane_id() == 0 && sum) {
+        atomicAdd((unsigned long long *)&s_sum, (unsigned long long)sum);
+        atomicAdd((unsigned long long *)&s_cnt, (unsigned long long)cnt);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_sum) {
+        add<SC>(&g.e[g.s], -s_sum);
+        add<SC>(&g.ctrl->stat[kStSourcePushes], s_cnt);
+    }
+}
+
+__global__ void k_saturate_source(DevGraph g) {
+    saturate_source<kAgent>(g, Team{(int)blockIdx.x, (int)gridDim.x});
+}
+
+// Edges per thread of a batch that one workgroup repairs alone.
+constexpr int kAloneEdges = kRepairMax / kBlock;
+
+// Batch validation: ids in [0, m), capacities in [0, cap_limit], ids distinct
+// (a batch is a set).  Sets Ctrl::err; the rest of the call then leaves the
+// state alone.
+__global__ void k_validate_updates(DevGraph g, Repair b) {
+    const Team tm{(int)blockIdx.x, (int)gridDim.x};
+    for (int64_t i = tm.tid(); i < b.k; i += tm.nthreads()) {
+        const int64_t id = b.ids[i];
+        const int32_t cv = b.caps[i];
+        if (id < 0 || id >= g.m) {
+            atomicOr(&g.ctrl->err, 1);
+            continue;
+        }
+        if (cv < 0 || cv > b.cap_limit) atomicOr(&g.ctrl->err, 2);
+        if (atomicExch(&g.stamp[id], b.epoch) == b.epoch) atomicOr(&g.ctrl->err, 4);
+    }
+}
+
+// Alg. 5 first loop: c_f(u,v) += c' - c; the stored capacities follow.
+__global__ void k_apply_delta(DevGraph g, Repair b) {
+    if (ld<kAgent>(&g.ctrl->err)) return;
+    const Team tm{(int)blockIdx.x, (int)gridDim.x};
+    int64_t cnt = 0;
+    for (int64_t i = tm.tid(); i < b.k; i += tm.nthreads()) {
+        const int64_t id = b.ids[i];
+        const int32_t cv = b.caps[i];
+        const int32_t a = g.edge2arc[id];
+        const int32_t d = cv - g.ecap[id];
+        g.ecap[id] = cv;
+        if (a >= 0 && d != 0) {
+            add<kAgent>(&g.cap[a], d);
+            add<kAgent>(cf_ptr(g.arc, a), d);
+        }
+        cnt++;
+    }
+    cnt = wave_sum(cnt);
+    if (lane_id() == 0 && cnt) add<kAgent>(&g.ctrl->stat[kStUpdates], cnt);
+}
+
+// Alg. 5 second loop restricted to the updated arc pairs (only they can have
+// gone negative), with the excess change booked at once: the flow clamped by
+// o = -c_f(a) returns o units to the tail (e += o) and takes them from the
+// head (e -= o).  At most one arc of a pair can be negative (their residuals
+// sum to the pair's capacity); a compare-and-swap makes each clamp happen
+// once even when several updates share a pair.
+template <int SC>
+__device__ __forceinline__ int clamp_arc(const DevGraph &g, int x, int y, int32_t cv, int tail, int head) {
+    if (!cas<SC>(cf_ptr(g.arc, x), cv, 0)) return 0;
+    const int32_t o = -cv;
+    add<SC>(cf_ptr(g.arc, y), -o);
+    add<SC>(&g.e[tail], (int64_t)o);
+    add<SC>(&g.e[head], -(int64_t)o);
+    return 1;
+}
+__global__ void k_clamp(DevGraph g, Repair b) {
+    if (ld<kAgent>(&g.ctrl->err)) return;
+    const Team tm{(int)blockIdx.x, (int)gridDim.x};
+    int64_t cnt = 0;
+    for (int64_t i = tm.tid(); i < b.k; i += tm.nthreads()) {
+        const int32_t a0 = g.edge2arc[b.ids[i]];
+        if (a0 < 0) continue;
+        const int32_t a1 = g.twin[a0];
+        const int32_t r0 = ld<kAgent>(cf_ptr(g.arc, a0)), r1 = ld<kAgent>(cf_ptr(g.arc, a1));
+        if (r0 >= 0 && r1 >= 0) continue;
+        const int head = get<kAgent>(&g.arc[a0]).x, tail = get<kAgent>(&g.arc[a1]).x;
+        if (r0 < 0) cnt += clamp_arc<kAgent>(g, a0, a1, r0, tail, head);
+        if (r1 < 0) cnt += clamp_arc<kAgent>(g, a1, a0, r1, head, tail);
+    }
+    cnt = wave_sum(cnt);
+    if (lane_id() == 0 && cnt) add<kAgent>(&g.ctrl->stat[kStClamps], cnt);
+}
+
+// ---------------------------------------------------------------------------
+// Local stage of a dynamic update, between the batch repair (Alg. 5) and the
+// global loop: the updated arcs that now cross the last cut are saturated,
+// and the deficits the batch left are filled from excess nearby (the ideas of
+// Dynamic Push-Pull, Sec. 4.2 / Alg. 6 and 8, applied to the batch's own
+// arcs).  Every step is a push along a residual arc, so the global loop that
+// follows, with its unchanged termination test, still ends at a maximum flow;
+// the stage only saves it the work of letting every vertex that holds excess
+// on the source side chase a small deficit.
+// ---------------------------------------------------------------------------
+
+// Saturate every updated arc that is residual from the source side of the
+// last cut (height |V|) to its sink side (height < |V|).  A solved state has
+// no such arc, and only arcs whose capacity grew can have gained one: the
+// clamp and the source re-saturation only lower residuals across it.  The
+// flow moved becomes excess at the head and a deficit at the tail (Alg. 8,
+// "remove S to T edges", on the batch).  Heights are those of the last
+// global relabel.
+template <int SC>
+__device__ __forceinline__ void cut_arc_saturate(const DevGraph &g, int x, int y, int tail, int head) {
+    if (ld<SC>(cf_ptr(g.arc, x)) <= 0) return;
+    const int32_t c = xchg<SC>(cf_ptr(g.arc, x), 0);  // updates sharing the pair: one takes it
+    if (c > 0) {
+        add<SC>(cf_ptr(g.arc, y), c);
+        add<SC>(&g.e[tail], -(int64_t)c);
+        add<SC>(&g.e[head], (int64_t)c);
+    }
+}
+__global__ void k_cut_saturate(DevGraph g, Repair b) {
+    if (ld<kAgent>(&g.ctrl->err)) return;
+    const Team tm{(int)blockIdx.x, (int)gridDim.x};
+    for (int64_t i = tm.tid(); i < b.k; i += tm.nthreads()) {
+        const int32_t a0 = g.edge2arc[b.ids[i]];
+        if (a0 < 0) continue;
+        const int32_t a1 = g.twin[a0];
+        const int2 r0 = g.arc[a0], r1 = g.arc[a1];
+        const bool h0 = g.h[r0.x] >= g.n, h1 = g.h[r1.x] >= g.n;  // head of a0, and its tail
+        if (h1 && !h0) cut_arc_saturate<kAgent>(g, a0, a1, r1.x, r0.x);
+        if (h0 && !h1) cut_arc_saturate<kAgent>(g, a1, a0, r0.x, r1.x);
+    }
+}
+
+// One round of local pulls.  Every deficient vertex v of list `in` takes what
+// it lacks from its in-neighbours w (residual arc w -> v) that hold excess,
+// in arc order: d moves as a push from w to v (c_f(w,v) -= d, c_f(v,w) += d,
+// e(w) -= d, e(v) += d), as Alg. 6 pulls, here without heights.  With `out`,
+// what is still lacking is then taken from in-neighbours along their residual
+// arcs whatever their excess, which hands the deficit on to them; a giver
+// left with a deficit joins `out` (once, pmark tag).  s and t never give.  A
+// wavefront per vertex; v's own excess is touched by its wavefront only.
+// Each pass looks at no more than kPullScan arcs of v, the excess pass at the
+// front of v's list and the hand-on pass at its back (from the last chunk
+// backwards), so that a hub costs a bounded number of steps and the deficit
+// is handed on to the neighbours at the end of the list (the low-degree ones
+// when vertices are numbered by falling degree); what stays lacking is left
+// to the global loop.
+constexpr int kPullScan = 4096;
+// The first round takes its vertices from the batch itself (ids, k: both
+// ends of every updated arc pair, s and t left out, each deficient vertex
+// claimed once with tag - 1); the later ones from the list `in` of the round
+// before.  Marks only grow (pmark holds the largest tag given to a vertex,
+// tags rise from call to call), so a claim or an append takes a vertex only
+// if its mark is still below the tag: a vertex that round 0 already put on
+// the next round's list (tag) is not claimed again as a batch end (tag - 1)
+// while its first visit may still be running.  The list counters rotate over three words, cnt[r % 3] read and
+// cnt[(r + 1) % 3] appended to by round r, which clears cnt[(r + 2) % 3] for
+// round r + 1; they all start at zero with the call's control block.
+//
+// A wavefront looks its share of the batch up lane by lane and then visits the
+// deficient ends it found, one after another: what bounds a large batch is the
+// chain of lookups before a visit (the first round on 336 k ends of R-MAT 2^20:
+// 82 us with a wavefront per end, 18.5 us so).
+template <int SC>
+__device__ __forceinline__ void pull_round(const DevGraph &g, const Team &tm, const Repair &b, const int32_t *in,
+                                           int r, int32_t *out) {
+    const int lane = lane_id();
+    const int32_t tag = b.tag + r;
+    int32_t *cnt = g.ctrl->pull_cnt;
+    if (tm.rank == 0 && threadIdx.x == 0) cnt[(r + 2) % 3] = 0;
+    int32_t *out_cnt = &cnt[(r + 1) % 3];
+    const int64_t items = r == 0 ? 2 * b.k : (int64_t)ld<SC>(&cnt[r % 3]);
+    const int64_t nwaves = tm.nwaves();
+    const int share = (int)min((int64_t)64, (items + nwaves - 1) / nwaves);
+    for (int64_t base = tm.wave() * share; base < items; base += nwaves * share) {
+        const int64_t i = base + lane;
+        int mine = -1;
+        int64_t lacks = 0;
+        if (lane < share && i < items) {
+            int w;
+            if (r == 0) {
+                const int32_t a0 = g.edge2arc[b.ids[i >> 1]];
+                w = a0 < 0 ? -1 : get<SC>(&g.arc[(i & 1) ? g.twin[a0] : a0]).x;
+                if (w == g.s || w == g.t) w = -1;
+                if (w >= 0) {
+                    lacks = -ld<SC>(&g.e[w]);
+                    if (lacks > 0 && __hip_atomic_fetch_max(&b.pmark[w], tag - 1, __ATOMIC_RELAXED,
+                                                            __HIP_MEMORY_SCOPE_AGENT) < tag - 1)
+                        mine = w;
+                }
+            } else {
+                mine = get<SC>(&in[i]);
+                lacks = -ld<SC>(&g.e[mine]);
+            }
+        }
+        uint64_t todo = __ballot(mine >= 0 && lacks > 0);
+        while (todo) {
+            const int from = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            const int v = lane_value(mine, from);
+            const int64_t need = -uniform(ld<SC>(&g.e[v]));
+            if (need <= 0) continue;
+            const int beg = g.row_ptr[v], end = g.row_ptr[v + 1];
+            int64_t got = 0;
+            // chunks of 64 arcs aligned to the start of v's list in both passes,
+            // so that an arc the first pass pushed along is read again by the
+            // same lane (its own earlier atomic orders the read; another lane's
+            // would not)
+            const int nchunks = (end - beg + 63) / 64;
+            for (int hand_on = 0; hand_on < (out ? 2 : 1) && got < need; ++hand_on) {
+                const int lo = hand_on ? max(beg, end - kPullScan) : beg;
+                const int hi = hand_on ? end : min(end, beg + kPullScan);
+                const int c_first = hand_on ? nchunks - 1 : 0;
+                const int c_last = hand_on ? (lo - beg) / 64 : (hi - beg + 63) / 64 - 1;
+                for (int c = c_first; (hand_on ? c >= c_last : c <= c_last) && got < need; c += hand_on ? -1 : 1) {
+                    const int a = beg + 64 * c + lane;
+                    int64_t avail = 0;
+                    int w = -1, tw = 0;
+                    if (a >= lo && a < hi) {
+                        w = get<SC>(&g.arc[a]).x;
+                        tw = g.twin[a];
+                        if (w != g.s && w != g.t) {
+                            const int32_t r = ld<SC>(cf_ptr(g.arc, tw));
+                            if (r > 0) {
+                                if (hand_on) {
+                                    avail = r;
+                                } else {
+                                    const int64_t ew = ld<SC>(&g.e[w]);
+                                    if (ew > 0) avail = min((int64_t)r, ew);
+                                }
+                            }
+                        }
+                    }
+                    const int64_t incl = wave_incl_scan64(avail);
+                    const int64_t excl = incl - avail;
+                    const int64_t room = need - got;
+                    const int64_t d = (avail > 0 && excl < room) ? min(avail, room - excl) : 0;
+                    int64_t moved = 0;
+                    if (d > 0) {
+                        // The excess pass claims its share of w's excess first and
+                        // gives back what w no longer holds (other deficits may pull
+                        // from the same giver at once), so that it never overdraws a
+                        // giver: an overdrawn giver left after the last round is a
+                        // deficit that the global loop would reach from the whole
+                        // source side.  The hand-on pass takes along the residual
+                        // whatever w holds, and lists a giver it leaves in deficit.
+                        const int64_t old = fetch_add<SC>(&g.e[w], -d);
+                        moved = d;
+                        if (!hand_on) {
+                            moved = old >= d ? d : (old > 0 ? old : 0);
+                            if (moved < d) add<SC>(&g.e[w], d - moved);
+                        }
+                        if (moved > 0) {
+                            add<SC>(cf_ptr(g.arc, tw), -(int32_t)moved);
+                            add<SC>(cf_ptr(g.arc, a), (int32_t)moved);
+                        }
+                        if (out && hand_on && old - d < 0 &&
+                            __hip_atomic_fetch_max(&b.pmark[w], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < tag)
+                            out[fetch_add<SC>(out_cnt, 1)] = w;
+                    }
+                    got += wave_sum(moved);
+                }
+            }
+            if (lane == 0 && got > 0) add<SC>(&g.e[v], got);
+        }
+    }
+}
+
+__global__ void k_pull_round(DevGraph g, Repair b, const int32_t *in, int r, int32_t *out) {
+    if (ld<kAgent>(&g.ctrl->err)) return;
+    pull_round<kAgent>(g, Team{(int)blockIdx.x, (int)gridDim.x}, b, in, r, out);
+}
+
+// Repair of a batch of at most kRepairMax edges by one workgroup, up to the
+// pulls; the source only with `source`.  Everything that the steps look up
+// (ids, arcs, twins, ends, heights) is loaded once, at the validation, and
+// kept; a step then waits for its own atomics only.  Works as a team of one
+// XCD does, so that no stale line is left in the L1.
+__device__ __forceinline__ void repair_alone(const DevGraph &g, const Repair &b, bool source) {
+    constexpr int SC = kXcd, U = kAloneEdges;
+    int64_t id[U];
+    int32_t cv[U], a0[U], a1[U], d[U], head[U], tail[U];
+    bool mine[U], up[U], down[U];  // on the source side: tail only (of a0), head only
+    int bad = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t i = threadIdx.x + (int64_t)u * kBlock;
+        mine[u] = i < b.k;
+        id[u] = mine[u] ? b.ids[i] : 0;
+        cv[u] = mine[u] ? b.caps[i] : 0;
+        if (mine[u] && (cv[u] < 0 || cv[u] > b.cap_limit)) bad |= 2;
+        if (id[u] < 0 || id[u] >= g.m) {
+            bad |= 1;
+            mine[u] = false;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        a0[u] = mine[u] ? g.edge2arc[id[u]] : -1;
+        d[u] = mine[u] ? cv[u] - g.ecap[id[u]] : 0;
+        if (mine[u] && atomicExch(&g.stamp[id[u]], b.epoch) == b.epoch) bad |= 4;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) a1[u] = a0[u] >= 0 ? g.twin[a0[u]] : 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        head[u] = a0[u] >= 0 ? get<SC>(&g.arc[a0[u]]).x : 0;
+        tail[u] = a0[u] >= 0 ? get<SC>(&g.arc[a1[u]]).x : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool hs = g.h[head[u]] >= g.n, ts = g.h[tail[u]] >= g.n;
+        up[u] = ts && !hs;
+        down[u] = hs && !ts;
+    }
+    if (bad) atomicOr(&g.ctrl->err, bad);
+    if (__syncthreads_or(bad)) return;
+    int cnt = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (!mine[u]) continue;
+        g.ecap[id[u]] = cv[u];
+        if (a0[u] >= 0 && d[u] != 0) {
+            add<SC>(&g.cap[a0[u]], d[u]);
+            add<SC>(cf_ptr(g.arc, a0[u]), d[u]);
+        }
+        cnt++;
+    }
+    cnt = wave_sum(cnt);
+    if (lane_id() == 0 && cnt) add<SC>(&g.ctrl->stat[kStUpdates], (int64_t)cnt);
+    block_sync<SC>();
+    cnt = 0;
+    int32_t r0[U], r1[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        r0[u] = a0[u] >= 0 ? ld<SC>(cf_ptr(g.arc, a0[u])) : 0;
+        r1[u] = a0[u] >= 0 ? ld<SC>(cf_ptr(g.arc, a1[u])) : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (r0[u] < 0) cnt += clamp_arc<SC>(g, a0[u], a1[u], r0[u], tail[u], head[u]);
+        if (r1[u] < 0) cnt += clamp_arc<SC>(g, a1[u], a0[u], r1[u], head[u], tail[u]);
+    }
+    cnt = wave_sum(cnt);
+    if (lane_id() == 0 && cnt) add<SC>(&g.ctrl->stat[kStClamps], (int64_t)cnt);
+    block_sync<SC>();
+    // (the arcs out of s are the source saturation's, now or later)
+    if (b.pulls) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (a0[u] >= 0 && up[u] && tail[u] != g.s) cut_arc_saturate<SC>(g, a0[u], a1[u], tail[u], head[u]);
+            if (a0[u] >= 0 && down[u] && head[u] != g.s) cut_arc_saturate<SC>(g, a1[u], a0[u], head[u], tail[u]);
+        }
+    }
+    if (source) saturate_source<SC>(g, Team{0, 1});
+}
+
+// The repair of a dynamic update at the head of its solve kernel: validation,
+// capacity changes and clamps (Alg. 5), the source saturated again, and the
+// local stage.  As kernels of their own these were ten launches of 2 to 4 us
+// with 4 to 8 us between them; here a step of the team ends with its barrier
+// (1 us on one XCD, 4 to 5 all over the device), and the batch itself is the
+// first workgroup's alone (repair_alone), which has still cheaper barriers, as
+// is the source when its list is as short as a batch.  The pulls are made by the
+// whole team and stop at the first round that hands nothing on.  Returns false
+// when a barrier failed.  A whole update, kernels of their own against this:
+// 1 k vertices, 100 edges 95 -> 52 us; 20 k vertices, 1000 edges 112 -> 75;
+// R-MAT 2^20, 1000 edges 180 -> 140.
+template <int SC>
+__device__ __forceinline__ bool repair(const DevGraph &g, const Team &tm, const LoopParams &p, const Repair &b,
+                                       uint32_t &epoch) {
+    constexpr int PS = SC == kGroup ? kXcd : SC;  // scope of the pulls
+    const bool source_alone = SC == kGroup || g.row_ptr[g.s + 1] - g.row_ptr[g.s] <= kRepairMax;
+    if (tm.rank == 0) repair_alone(g, b, source_alone);
+    block_sync<PS>();
+    if (!grid_barrier<SC>(g.ctrl, tm, epoch, p.barrier_ticks)) return false;
+    if (ld<PS>(&g.ctrl->err)) return true;
+    if constexpr (SC != kGroup) {
+        if (!source_alone) {
+            saturate_source<SC>(g, tm);
+            if (!grid_barrier<SC>(g.ctrl, tm, epoch, p.barrier_ticks)) return false;
+        }
+    }
+    for (int r = 0; r < b.pulls; ++r) {
+        const bool last = r == b.pulls - 1;
+        pull_round<PS>(g, tm, b, (r & 1) ? g.list[2] : g.list[1], r, last ? nullptr : (r & 1) ? g.list[1] : g.list[2]);
+        block_sync<PS>();
+        if (!grid_barrier<SC>(g.ctrl, tm, epoch, p.barrier_ticks)) return false;
+        if (last || uniform(ld<PS>(&g.ctrl->pull_cnt[(r + 1) % 3])) == 0) break;
+    }
+    return true;
+}
+
 // The whole grid is one team (see join_team), or a single workgroup.
 // WALK: long arc lists are visited by the downhill walk (else scan first);
 // the two are separate instances, since both inlined side by side would spill.
 template <int BLOCK, int SC, bool WALK>
-__global__ void __launch_bounds__(BLOCK) k_loop(DevGraph g, LoopParams p) {
+__global__ void __launch_bounds__(BLOCK) k_loop(DevGraph g, LoopParams p, Repair b) {
     Team tm{0, 1};
+    uint32_t epoch = 0;  // barriers this launch has passed
     if constexpr (SC != kGroup) {
         tm = join_team<SC>(g.ctrl, p.team_want, p.join_ticks);
         if (tm.size == 0) return;
         init_stages();
     }
-    solve_loop<SC, WALK>(g, tm, p);
+    if (b.on && !repair<SC>(g, tm, p, b, epoch)) return;
+    solve_loop<SC, WALK>(g, tm, p, epoch);
+    // the control block to the host, which saves a copy's dispatch
+    block_sync<SC == kGroup ? kXcd : SC>();
+    if (!grid_barrier<SC>(g.ctrl, tm, epoch, p.barrier_ticks)) return;
+    if (b.host && tm.rank == 0) {
+        constexpr int from = (int)(offsetof(Ctrl, qcount) / sizeof(int)), words = (int)(sizeof(Ctrl) / sizeof(int));
+        const int *w = reinterpret_cast<const int *>(g.ctrl);
+        int *out = reinterpret_cast<int *>(b.host);
+        for (int i = from + threadIdx.x; i < words; i += BLOCK) out[i] = ld<SC == kGroup ? kXcd : SC>(&w[i]);
+    }
 }
 
 // A view read from a device table, its pointers read as pointers to global
@@ -2666,7 +3097,8 @@ __global__ void __launch_bounds__(BLOCK)
     const int side = (int)blockIdx.x < split ? 0 : 1;
     const Team tm = side == 0 ? Team{(int)blockIdx.x, split} : Team{(int)blockIdx.x - split, G - split};
     const LoopParams &p = params[side];
-    solve_loop<kAgent, WALK>(global_view(views[side]), tm, p);
+    uint32_t epoch = 0;
+    solve_loop<kAgent, WALK>(global_view(views[side]), tm, p, epoch);
 }
 
 // ---------------------------------------------------------------------------
@@ -2791,10 +3223,16 @@ __global__ void k_edge_flow(DevGraph g, int32_t *rem, int32_t *flow) {
 // Initialisation, source saturation and update repair
 // ---------------------------------------------------------------------------
 
-__global__ void k_reset_ctrl(Ctrl *c) {
-    int *w = reinterpret_cast<int *>(c);
-    const int words = (int)(sizeof(Ctrl) / sizeof(int));
-    for (int i = threadIdx.x; i < words; i += blockDim.x) w[i] = 0;
+// Start of a call: the control block is cleared, and a batch that waits in
+// pinned host memory is fetched (`words` words; read over the bus by the
+// kernel, which saves the copy's own dispatch).
+__global__ void k_begin(Ctrl *c, const int32_t *src, int32_t *dst, int64_t words) {
+    if (blockIdx.x == 0) {
+        int *w = reinterpret_cast<int *>(c);
+        for (int i = threadIdx.x; i < (int)(sizeof(Ctrl) / sizeof(int)); i += blockDim.x) w[i] = 0;
+    }
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += stride) dst[i] = src[i];
 }
 
 // Alg. 1 first loops: e = 0, h = 0, c_f = c.
@@ -2805,274 +3243,6 @@ __global__ void k_init_state(DevGraph g) {
     for (int64_t v = gtid; v < g.n; v += stride) {
         g.e[v] = 0;
         g.h[v] = 0;
-    }
-}
-
-// Saturate every residual arc out of s: c_f(s,u) -> 0, the twin gains it,
-// e(u) += d, e(s) -= d (Alg. 1 third loop; Alg. 4 lines 3-8, where the
-// remaining residual is pushed rather than e(u) overwritten).
-template <int SC>
-__device__ __forceinline__ void saturate_source(const DevGraph &g, const Team &tm) {
-    if (ld<SC>(&g.ctrl->err)) return;
-    __shared__ int64_t s_sum, s_cnt;
-    if (threadIdx.x == 0) {
-        s_sum = 0;
-        s_cnt = 0;
-    }
-    __syncthreads();
-    const int beg = g.row_ptr[g.s], end = g.row_ptr[g.s + 1];
-    int64_t sum = 0, cnt = 0;
-    for (int64_t a = beg + tm.tid(); a < end; a += tm.nthreads()) {
-        const int2 r = get<SC>(&g.arc[a]);
-        if (r.y > 0) {
-            g.arc[a].y = 0;
-            add<SC>(cf_ptr(g.arc, g.twin[a]), r.y);
-            add<SC>(&g.e[r.x], (int64_t)r.y);
-            sum += r.y;
-            cnt++;
-        }
-    }
-    sum = wave_sum(sum);
-    cnt = wave_sum(cnt);
-    if (lane_id() == 0 && sum) {
-        atomicAdd((unsigned long long *)&s_sum, (unsigned long long)sum);
-        atomicAdd((unsigned long long *)&s_cnt, (unsigned long long)cnt);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && s_sum) {
-        add<SC>(&g.e[g.s], -s_sum);
-        add<SC>(&g.ctrl->stat[kStSourcePushes], s_cnt);
-    }
-}
-
-__global__ void k_saturate_source(DevGraph g) {
-    saturate_source<kAgent>(g, Team{(int)blockIdx.x, (int)gridDim.x});
-}
-
-// Batch validation: ids in [0, m), capacities in [0, cap_limit], ids distinct
-// (a batch is a set).  Sets Ctrl::err; later kernels of the call then skip.
-__global__ void k_validate_updates(DevGraph g, const int64_t *ids, const int32_t *caps, int64_t k,
-                                   int32_t epoch, int32_t cap_limit) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t id = ids[i];
-        const int32_t cv = caps[i];
-        if (id < 0 || id >= g.m) {
-            atomicOr(&g.ctrl->err, 1);
-            continue;
-        }
-        if (cv < 0 || cv > cap_limit) atomicOr(&g.ctrl->err, 2);
-        if (atomicExch(&g.stamp[id], epoch) == epoch) atomicOr(&g.ctrl->err, 4);
-    }
-}
-
-// Alg. 5 first loop: c_f(u,v) += c' - c; the stored capacities follow.
-__global__ void k_apply_delta(DevGraph g, const int64_t *ids, const int32_t *caps, int64_t k) {
-    if (ld<kAgent>(&g.ctrl->err)) return;
-    int64_t cnt = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t id = ids[i];
-        const int32_t cv = caps[i];
-        const int32_t d = cv - g.ecap[id];
-        g.ecap[id] = cv;
-        const int32_t a = g.edge2arc[id];
-        if (a >= 0 && d != 0) {
-            add<kAgent>(&g.cap[a], d);
-            add<kAgent>(cf_ptr(g.arc, a), d);
-        }
-        cnt++;
-    }
-    cnt = wave_sum(cnt);
-    if (lane_id() == 0 && cnt) add<kAgent>(&g.ctrl->stat[kStUpdates], cnt);
-}
-
-// Alg. 5 second loop restricted to the updated arc pairs (only they can have
-// gone negative), with the excess change booked at once: the flow clamped by
-// o = -c_f(a) returns o units to the tail (e += o) and takes them from the
-// head (e -= o).  At most one arc of a pair can be negative (their residuals
-// sum to the pair's capacity); a compare-and-swap makes each clamp happen
-// once even when several updates share a pair.
-__global__ void k_clamp(DevGraph g, const int64_t *ids, int64_t k) {
-    if (ld<kAgent>(&g.ctrl->err)) return;
-    int64_t cnt = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t a0 = g.edge2arc[ids[i]];
-        if (a0 < 0) continue;
-        const int32_t a1 = g.twin[a0];
-        for (int side = 0; side < 2; ++side) {
-            const int32_t x = side ? a1 : a0;
-            const int32_t y = side ? a0 : a1;
-            int32_t *cfx = cf_ptr(g.arc, x);
-            const int32_t cv = ld<kAgent>(cfx);
-            if (cv < 0 && cas<kAgent>(cfx, cv, 0)) {
-                const int32_t o = -cv;
-                add<kAgent>(cf_ptr(g.arc, y), -o);
-                add<kAgent>(&g.e[g.arc[y].x], (int64_t)o);  // tail of x
-                add<kAgent>(&g.e[g.arc[x].x], -(int64_t)o); // head of x
-                cnt++;
-            }
-        }
-    }
-    cnt = wave_sum(cnt);
-    if (lane_id() == 0 && cnt) add<kAgent>(&g.ctrl->stat[kStClamps], cnt);
-}
-
-// ---------------------------------------------------------------------------
-// Local stage of a dynamic update, between the batch repair (Alg. 5) and the
-// global loop: the updated arcs that now cross the last cut are saturated,
-// and the deficits the batch left are filled from excess nearby (the ideas of
-// Dynamic Push-Pull, Sec. 4.2 / Alg. 6 and 8, applied to the batch's own
-// arcs).  Every step is a push along a residual arc, so the global loop that
-// follows, with its unchanged termination test, still ends at a maximum flow;
-// the stage only saves it the work of letting every vertex that holds excess
-// on the source side chase a small deficit.
-// ---------------------------------------------------------------------------
-
-// Saturate every updated arc that is residual from the source side of the
-// last cut (height |V|) to its sink side (height < |V|).  A solved state has
-// no such arc, and only arcs whose capacity grew can have gained one: the
-// clamp and the source re-saturation only lower residuals across it.  The
-// flow moved becomes excess at the head and a deficit at the tail (Alg. 8,
-// "remove S to T edges", on the batch).  Heights are those of the last
-// global relabel.
-__global__ void k_cut_saturate(DevGraph g, const int64_t *ids, int64_t k) {
-    if (ld<kAgent>(&g.ctrl->err)) return;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t a0 = g.edge2arc[ids[i]];
-        if (a0 < 0) continue;
-        const int32_t a1 = g.twin[a0];
-        for (int side = 0; side < 2; ++side) {
-            const int32_t x = side ? a1 : a0, y = side ? a0 : a1;
-            const int head = g.arc[x].x, tail = g.arc[y].x;
-            if (g.h[tail] < g.n || g.h[head] >= g.n) continue;
-            if (ld<kAgent>(cf_ptr(g.arc, x)) <= 0) continue;
-            const int32_t c = xchg<kAgent>(cf_ptr(g.arc, x), 0);  // updates sharing the pair: one takes it
-            if (c > 0) {
-                add<kAgent>(cf_ptr(g.arc, y), c);
-                add<kAgent>(&g.e[tail], -(int64_t)c);
-                add<kAgent>(&g.e[head], (int64_t)c);
-            }
-        }
-    }
-}
-
-// One round of local pulls.  Every deficient vertex v of list `in` takes what
-// it lacks from its in-neighbours w (residual arc w -> v) that hold excess,
-// in arc order: d moves as a push from w to v (c_f(w,v) -= d, c_f(v,w) += d,
-// e(w) -= d, e(v) += d), as Alg. 6 pulls, here without heights.  With `out`,
-// what is still lacking is then taken from in-neighbours along their residual
-// arcs whatever their excess, which hands the deficit on to them; a giver
-// left with a deficit joins `out` (once, pmark tag).  s and t never give.  A
-// wavefront per vertex; v's own excess is touched by its wavefront only.
-// Each pass looks at no more than kPullScan arcs of v, the excess pass at the
-// front of v's list and the hand-on pass at its back (from the last chunk
-// backwards), so that a hub costs a bounded number of steps and the deficit
-// is handed on to the neighbours at the end of the list (the low-degree ones
-// when vertices are numbered by falling degree); what stays lacking is left
-// to the global loop.
-constexpr int kPullScan = 4096;
-// The first round takes its vertices from the batch itself (ids, k: both
-// ends of every updated arc pair, s and t left out, each deficient vertex
-// claimed once with tag - 1); the later ones from the list `in` of the round
-// before.  Marks only grow (pmark holds the largest tag given to a vertex,
-// tags rise from call to call), so a claim or an append takes a vertex only
-// if its mark is still below the tag: a vertex that round 0 already put on
-// the next round's list (tag) is not claimed again as a batch end (tag - 1)
-// while its first visit may still be running.  The list counters rotate over three words, cnt[r % 3] read and
-// cnt[(r + 1) % 3] appended to by round r, which clears cnt[(r + 2) % 3] for
-// round r + 1; they all start at zero with the call's control block.
-__global__ void k_pull_round(DevGraph g, const int64_t *ids, int64_t k, const int32_t *in, int32_t *cnt, int r,
-                             int32_t *out, int32_t *pmark, int32_t tag) {
-    if (ld<kAgent>(&g.ctrl->err)) return;
-    const int lane = lane_id();
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    if (blockIdx.x == 0 && threadIdx.x == 0) cnt[(r + 2) % 3] = 0;
-    int32_t *out_cnt = &cnt[(r + 1) % 3];
-    const int64_t items = ids ? 2 * k : (int64_t)ld<kAgent>(&cnt[r % 3]);
-    for (int64_t i = wave; i < items; i += nwaves) {
-        int v = -1;
-        int64_t need = 0;
-        if (lane == 0) {
-            if (ids) {
-                const int32_t a0 = g.edge2arc[ids[i >> 1]];
-                const int w = a0 < 0 ? -1 : ((i & 1) ? g.arc[g.twin[a0]].x : g.arc[a0].x);
-                if (w >= 0 && w != g.s && w != g.t && ld<kAgent>(&g.e[w]) < 0 &&
-                    __hip_atomic_fetch_max(&pmark[w], tag - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < tag - 1)
-                    v = w;
-            } else {
-                v = in[i];
-            }
-            if (v >= 0) need = -ld<kAgent>(&g.e[v]);
-        }
-        v = lane_value(v, 0);
-        need = lane_value(need, 0);
-        if (need <= 0) continue;
-        const int beg = g.row_ptr[v], end = g.row_ptr[v + 1];
-        int64_t got = 0;
-        // chunks of 64 arcs aligned to the start of v's list in both passes,
-        // so that an arc the first pass pushed along is read again by the
-        // same lane (its own earlier atomic orders the read; another lane's
-        // would not)
-        const int nchunks = (end - beg + 63) / 64;
-        for (int hand_on = 0; hand_on < (out ? 2 : 1) && got < need; ++hand_on) {
-            const int lo = hand_on ? max(beg, end - kPullScan) : beg;
-            const int hi = hand_on ? end : min(end, beg + kPullScan);
-            const int c_first = hand_on ? nchunks - 1 : 0;
-            const int c_last = hand_on ? (lo - beg) / 64 : (hi - beg + 63) / 64 - 1;
-            for (int c = c_first; (hand_on ? c >= c_last : c <= c_last) && got < need; c += hand_on ? -1 : 1) {
-                const int a = beg + 64 * c + lane;
-                int64_t avail = 0;
-                int w = -1, tw = 0;
-                if (a >= lo && a < hi) {
-                    w = g.arc[a].x;
-                    tw = g.twin[a];
-                    if (w != g.s && w != g.t) {
-                        const int32_t r = ld<kAgent>(cf_ptr(g.arc, tw));
-                        if (r > 0) {
-                            if (hand_on) {
-                                avail = r;
-                            } else {
-                                const int64_t ew = ld<kAgent>(&g.e[w]);
-                                if (ew > 0) avail = min((int64_t)r, ew);
-                            }
-                        }
-                    }
-                }
-                const int64_t incl = wave_incl_scan64(avail);
-                const int64_t excl = incl - avail;
-                const int64_t room = need - got;
-                const int64_t d = (avail > 0 && excl < room) ? min(avail, room - excl) : 0;
-                int64_t moved = 0;
-                if (d > 0) {
-                    // The excess pass claims its share of w's excess first and
-                    // gives back what w no longer holds (other deficits may pull
-                    // from the same giver at once), so that it never overdraws a
-                    // giver: an overdrawn giver left after the last round is a
-                    // deficit that the global loop would reach from the whole
-                    // source side.  The hand-on pass takes along the residual
-                    // whatever w holds, and lists a giver it leaves in deficit.
-                    const int64_t old = fetch_add<kAgent>(&g.e[w], -d);
-                    moved = d;
-                    if (!hand_on) {
-                        moved = old >= d ? d : (old > 0 ? old : 0);
-                        if (moved < d) add<kAgent>(&g.e[w], d - moved);
-                    }
-                    if (moved > 0) {
-                        add<kAgent>(cf_ptr(g.arc, tw), -(int32_t)moved);
-                        add<kAgent>(cf_ptr(g.arc, a), (int32_t)moved);
-                    }
-                    if (out && hand_on && old - d < 0 &&
-                        __hip_atomic_fetch_max(&pmark[w], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < tag)
-                        out[fetch_add<kAgent>(out_cnt, 1)] = w;
-                }
-                got += wave_sum(moved);
-            }
-        }
-        if (lane == 0 && got > 0) add<kAgent>(&g.e[v], got);
     }
 }
 
@@ -3226,7 +3396,8 @@ __global__ void __launch_bounds__(BLOCK)
     LoopParams q = p;
     q.kc = kc[i];
     if (q.relabel_budget <= 0) q.relabel_budget = max((int64_t)1024, (int64_t)g.n / 16);
-    solve_loop<kGroup, false>(g, tm, q);
+    uint32_t epoch = 0;
+    solve_loop<kGroup, false>(g, tm, q, epoch);
     __syncthreads();
     if (threadIdx.x == 0) {
         BatchResult r;
@@ -3293,7 +3464,8 @@ __global__ void __launch_bounds__(kBlock)
         LoopParams q = p;
         q.kc = kc[i];
         if (q.relabel_budget <= 0) q.relabel_budget = max((int64_t)1024, (int64_t)g.n / 16);
-        solve_loop<kXcd, false>(g, tm, q);
+        uint32_t loop_epoch = 0;
+        solve_loop<kXcd, false>(g, tm, q, loop_epoch);
         block_sync<kXcd>();
         (void)team_sum<kXcd>(bar, tm, epoch, 0, p.barrier_ticks, &ok);
         if (!ok) return;
@@ -3325,8 +3497,9 @@ static int grid_for(int64_t work, int block, int cap) {
     return (int)b;
 }
 
-hipError_t launch_reset_ctrl(const DevGraph &g, hipStream_t st) {
-    hipLaunchKernelGGL(k_reset_ctrl, dim3(1), dim3(256), 0, st, g.ctrl);
+hipError_t launch_begin(const DevGraph &g, const void *src, void *dst, int64_t words, hipStream_t st) {
+    hipLaunchKernelGGL(k_begin, dim3(grid_for(words, 256, 512)), dim3(256), 0, st, g.ctrl,
+                       static_cast<const int32_t *>(src), static_cast<int32_t *>(dst), words);
     return hipGetLastError();
 }
 
@@ -3343,24 +3516,21 @@ hipError_t launch_saturate_source(const DevGraph &g, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_validate_updates(const DevGraph &g, const int64_t *ids, const int32_t *caps,
-                                   int64_t k, int32_t epoch, int32_t cap_limit, hipStream_t st) {
-    if (k <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_validate_updates, dim3(grid_for(k, 256)), dim3(256), 0, st, g, ids, caps, k,
-                       epoch, cap_limit);
+hipError_t launch_validate_updates(const DevGraph &g, const Repair &b, hipStream_t st) {
+    if (b.k <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_validate_updates, dim3(grid_for(b.k, 256)), dim3(256), 0, st, g, b);
     return hipGetLastError();
 }
 
-hipError_t launch_apply_delta(const DevGraph &g, const int64_t *ids, const int32_t *caps, int64_t k,
-                              hipStream_t st) {
-    if (k <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_apply_delta, dim3(grid_for(k, 256)), dim3(256), 0, st, g, ids, caps, k);
+hipError_t launch_apply_delta(const DevGraph &g, const Repair &b, hipStream_t st) {
+    if (b.k <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_apply_delta, dim3(grid_for(b.k, 256)), dim3(256), 0, st, g, b);
     return hipGetLastError();
 }
 
-hipError_t launch_clamp(const DevGraph &g, const int64_t *ids, int64_t k, hipStream_t st) {
-    if (k <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_clamp, dim3(grid_for(k, 256)), dim3(256), 0, st, g, ids, k);
+hipError_t launch_clamp(const DevGraph &g, const Repair &b, hipStream_t st) {
+    if (b.k <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_clamp, dim3(grid_for(b.k, 256)), dim3(256), 0, st, g, b);
     return hipGetLastError();
 }
 
@@ -3379,21 +3549,32 @@ hipError_t loop_max_coresident(int device, int *blocks) {
     return hipSuccess;
 }
 
-hipError_t launch_loop(const DevGraph &g, const LoopParams &p, int grid, hipStream_t st) {
+hipError_t launch_local_stage(const DevGraph &g, const Repair &b, hipStream_t st) {
+    if (b.k <= 0 || b.pulls == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_cut_saturate, dim3(grid_for(b.k, 256)), dim3(256), 0, st, g, b);
+    // at most 2k deficits in any list, a wavefront each
+    const dim3 blocks(grid_for(2 * b.k * 64, 256, 4096));
+    for (int r = 0; r < b.pulls; ++r)
+        hipLaunchKernelGGL(k_pull_round, blocks, dim3(256), 0, st, g, b, (r & 1) ? g.list[2] : g.list[1], r,
+                           r == b.pulls - 1 ? nullptr : (r & 1) ? g.list[1] : g.list[2]);
+    return hipGetLastError();
+}
+
+hipError_t launch_loop(const DevGraph &g, const LoopParams &p, const Repair &b, int grid, hipStream_t st) {
     if (grid <= 1) {
-        if (p.walk) hipLaunchKernelGGL((k_loop<kBlock, kGroup, true>), dim3(1), dim3(kBlock), 0, st, g, p);
-        else hipLaunchKernelGGL((k_loop<kBlock, kGroup, false>), dim3(1), dim3(kBlock), 0, st, g, p);
+        if (p.walk) hipLaunchKernelGGL((k_loop<kBlock, kGroup, true>), dim3(1), dim3(kBlock), 0, st, g, p, b);
+        else hipLaunchKernelGGL((k_loop<kBlock, kGroup, false>), dim3(1), dim3(kBlock), 0, st, g, p, b);
         return hipGetLastError();
     }
     LoopParams pa = p;
     pa.team_want = grid;
     if (p.xcd) {  // one workgroup in kXcds lands on the team's XCD, the others leave at once
         const dim3 blocks(grid * kXcds);
-        if (p.walk) hipLaunchKernelGGL((k_loop<kBlock, kXcd, true>), blocks, dim3(kBlock), 0, st, g, pa);
-        else hipLaunchKernelGGL((k_loop<kBlock, kXcd, false>), blocks, dim3(kBlock), 0, st, g, pa);
+        if (p.walk) hipLaunchKernelGGL((k_loop<kBlock, kXcd, true>), blocks, dim3(kBlock), 0, st, g, pa, b);
+        else hipLaunchKernelGGL((k_loop<kBlock, kXcd, false>), blocks, dim3(kBlock), 0, st, g, pa, b);
     } else {
-        if (p.walk) hipLaunchKernelGGL((k_loop<kBlock, kAgent, true>), dim3(grid), dim3(kBlock), 0, st, g, pa);
-        else hipLaunchKernelGGL((k_loop<kBlock, kAgent, false>), dim3(grid), dim3(kBlock), 0, st, g, pa);
+        if (p.walk) hipLaunchKernelGGL((k_loop<kBlock, kAgent, true>), dim3(grid), dim3(kBlock), 0, st, g, pa, b);
+        else hipLaunchKernelGGL((k_loop<kBlock, kAgent, false>), dim3(grid), dim3(kBlock), 0, st, g, pa, b);
     }
     return hipGetLastError();
 }
@@ -3490,24 +3671,6 @@ hipError_t launch_view_merge(const DevGraph &g, const int2 *varc, const int64_t 
 hipError_t launch_edge_flow(const DevGraph &g, const int2 *carc, int32_t *rem, int32_t *flow, hipStream_t st) {
     if (g.A > 0) hipLaunchKernelGGL(k_arc_flow, dim3(grid_for(g.A, 256)), dim3(256), 0, st, g, carc, rem);
     if (g.m > 0) hipLaunchKernelGGL(k_edge_flow, dim3(grid_for(g.m, 256)), dim3(256), 0, st, g, rem, flow);
-    return hipGetLastError();
-}
-
-hipError_t launch_local_stage(const DevGraph &g, const int64_t *ids, int64_t k, int32_t *pmark, int32_t tag0,
-                              int rounds, hipStream_t st) {
-    if (k <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cut_saturate, dim3(grid_for(k, 256)), dim3(256), 0, st, g, ids, k);
-    // the list counters (ctrl->pull_cnt) start at zero with the call's
-    // control block; at most 2k deficits in any list, a wavefront each
-    int32_t *cnt = g.ctrl->pull_cnt;
-    int32_t *lists[2] = {g.list[1], g.list[2]};
-    const int blocks = grid_for(2 * k * 64, 256, 4096);
-    for (int r = 0; r < rounds; ++r) {
-        const bool last = r == rounds - 1;
-        int32_t *out = last ? nullptr : lists[(r + 1) & 1];
-        hipLaunchKernelGGL(k_pull_round, dim3(blocks), dim3(256), 0, st, g, r == 0 ? ids : nullptr, k, lists[r & 1],
-                           cnt, r, out, pmark, tag0 + r + 1);
-    }
     return hipGetLastError();
 }
 
