@@ -10,7 +10,7 @@
 //  1. tail of every input edge (binary search in the input row pointers);
 //  2. two half-edges per edge that is not a self-loop, one owned by each end,
 //     keyed (owner, neighbour), compacted;
-//  3. a stable least-significant-digit radix sort of the keys (4-bit digits:
+//  3. a stable least-significant-digit radix sort of the keys (8-bit digits:
 //     per-tile digit counts, one exclusive scan over all tiles, a stable
 //     scatter that ranks each item within its tile);
 //  4. runs of equal keys are arcs: arc index by a scan of the run starts,
@@ -25,7 +25,8 @@ constexpr int kScanItems = 8;  // 2048 values per workgroup
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 16;  // 4096 items per tile
 constexpr int kSortTile = kSortThreads * kSortItems;
-constexpr int kDigits = 16;  // 4-bit digits
+constexpr int kDigitBits = 8;
+constexpr int kDigits = 1 << kDigitBits;
 
 __device__ __forceinline__ int lane_of() { return (int)__lane_id(); }
 
@@ -113,78 +114,106 @@ hipError_t scan_exclusive(int64_t *data, int64_t n, int64_t *tmp, hipStream_t st
 __global__ void __launch_bounds__(kSortThreads) k_rs_hist(const uint64_t *keys, int64_t n, int shift,
                                                           int64_t *hist, int64_t tiles) {
     __shared__ int s_cnt[kDigits];
-    if (threadIdx.x < kDigits) s_cnt[threadIdx.x] = 0;
+    static_assert(kDigits == kSortThreads, "a thread per digit");
+    s_cnt[threadIdx.x] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int j = threadIdx.x; j < kSortTile; j += kSortThreads) {
-        const int64_t i = base + j;
-        if (i < n) atomicAdd(&s_cnt[(int)((keys[i] >> shift) & (kDigits - 1))], 1);
+    uint64_t k[kSortItems];
+#pragma unroll
+    for (int j = 0; j < kSortItems; ++j) {
+        const int64_t i = base + j * kSortThreads + threadIdx.x;
+        k[j] = i < n ? keys[i] : 0;
     }
+#pragma unroll
+    for (int j = 0; j < kSortItems; ++j)
+        if (base + j * kSortThreads + threadIdx.x < n) atomicAdd(&s_cnt[(int)((k[j] >> shift) & (kDigits - 1))], 1);
     __syncthreads();
-    if (threadIdx.x < kDigits) hist[(int64_t)threadIdx.x * tiles + blockIdx.x] = s_cnt[threadIdx.x];
+    hist[(int64_t)threadIdx.x * tiles + blockIdx.x] = s_cnt[threadIdx.x];
 }
 
-// Stable scatter of one tile: thread t holds items [16t, 16t+16) of the tile
-// in order.  Its digit counts go to cnt[d][t]; an exclusive scan of cnt in
-// digit-major order gives, for (d, t), the items of the tile with a smaller
-// digit plus those with digit d in earlier threads.  Subtracting the first
-// (the tile's start of digit d) and adding the scanned tile offset of digit d
-// gives the global position of t's first item with digit d.
+// Stable scatter of one tile.  Wavefront w holds the items [1024 w, 1024 w +
+// 1024) of the tile, 64 consecutive ones per step.  An item's rank among those
+// of its digit: the lanes before it with the same digit (eight ballots find
+// them), the wavefront's earlier steps (a count per wavefront and digit in
+// LDS), then the earlier wavefronts and, for its place in the tile, the smaller
+// digits.  The tile is laid out in that order in LDS and stored from there, so
+// that a digit's items leave in runs of consecutive lanes.
+// Bound by the memory it moves, 24 bytes an item there and back: of 8 M items a
+// pass of 8 bits takes 60 us; one of 4 bits that ranked by thread and stored
+// from registers took 190.
 __global__ void __launch_bounds__(kSortThreads)
     k_rs_scatter(const uint64_t *keys, const uint32_t *vals, int64_t n, int shift, const int64_t *offs,
                  int64_t tiles, uint64_t *keys_out, uint32_t *vals_out) {
-    __shared__ int s_cnt[kDigits * kSortThreads];
-    const int t = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * kSortTile + (int64_t)t * kSortItems;
+    constexpr int kWaves = kSortThreads / 64;
+    __shared__ int s_cnt[kWaves][kDigits];
+    __shared__ int64_t s_to[kDigits];  // global position of a digit's first item, less its place in the tile
+    __shared__ uint64_t s_key[kSortTile];
+    __shared__ uint32_t s_val[kSortTile];
+    const int t = threadIdx.x, lane = lane_of(), w = t >> 6;
+    const int64_t tile0 = (int64_t)blockIdx.x * kSortTile;
+    const int here = (int)min((int64_t)kSortTile, n - tile0);
+    const int at0 = w * (kSortTile / kWaves) + lane;
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) s_cnt[k][t] = 0;
     uint64_t k[kSortItems];
     uint32_t v[kSortItems];
-    int dg[kSortItems];
-    int c[kDigits];
-#pragma unroll
-    for (int d = 0; d < kDigits; ++d) c[d] = 0;
+    int rank[kSortItems];
 #pragma unroll
     for (int j = 0; j < kSortItems; ++j) {
-        const bool ok = base + j < n;
-        k[j] = ok ? keys[base + j] : 0;
-        v[j] = ok ? vals[base + j] : 0;
-        dg[j] = ok ? (int)((k[j] >> shift) & (kDigits - 1)) : -1;
-#pragma unroll
-        for (int d = 0; d < kDigits; ++d) c[d] += dg[j] == d;
+        const bool ok = at0 + 64 * j < here;
+        k[j] = ok ? keys[tile0 + at0 + 64 * j] : 0;
+        v[j] = ok ? vals[tile0 + at0 + 64 * j] : 0;
     }
-#pragma unroll
-    for (int d = 0; d < kDigits; ++d) s_cnt[d * kSortThreads + t] = c[d];
     __syncthreads();
-    // exclusive scan of the 4096 counts, 16 consecutive entries per thread
-    int loc[kDigits];
+#pragma unroll
+    for (int j = 0; j < kSortItems; ++j) {
+        const bool ok = at0 + 64 * j < here;
+        const int d = (int)((k[j] >> shift) & (kDigits - 1));
+        uint64_t same = __ballot(ok);
+#pragma unroll
+        for (int bit = 0; bit < kDigitBits; ++bit) {
+            const uint64_t ones = __ballot((d >> bit) & 1);
+            same &= ((d >> bit) & 1) ? ones : ~ones;
+        }
+        const int before = __popcll(same & ((1ull << lane) - 1));
+        const int base = ok ? s_cnt[w][d] : 0;
+        rank[j] = base + before;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (ok && before == 0) s_cnt[w][d] = base + __popcll(same);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __syncthreads();
+    // thread t: digit t's items in the tile, and per wavefront where they begin
+    int64_t tot = 0;
     int sum = 0;
 #pragma unroll
-    for (int j = 0; j < kDigits; ++j) {
-        loc[j] = s_cnt[t * kDigits + j];
-        sum += loc[j];
-    }
-    int64_t tot = 0;
+    for (int k = 0; k < kWaves; ++k) sum += s_cnt[k][t];
     int run = (int)block_excl_scan<kSortThreads>((int64_t)sum, &tot);
-    __syncthreads();
+    s_to[t] = offs[(int64_t)t * tiles + blockIdx.x] - run;
 #pragma unroll
-    for (int j = 0; j < kDigits; ++j) {
-        s_cnt[t * kDigits + j] = run;
-        run += loc[j];
+    for (int k = 0; k < kWaves; ++k) {
+        const int c = s_cnt[k][t];
+        s_cnt[k][t] = run;
+        run += c;
     }
     __syncthreads();
-    int64_t pos[kDigits];
-#pragma unroll
-    for (int d = 0; d < kDigits; ++d)
-        pos[d] = offs[(int64_t)d * tiles + blockIdx.x] + (s_cnt[d * kSortThreads + t] - s_cnt[d * kSortThreads]);
 #pragma unroll
     for (int j = 0; j < kSortItems; ++j) {
-        if (dg[j] < 0) continue;
-        int64_t p = -1;
+        if (at0 + 64 * j >= here) continue;
+        const int p = s_cnt[w][(int)((k[j] >> shift) & (kDigits - 1))] + rank[j];
+        s_key[p] = k[j];
+        s_val[p] = v[j];
+    }
+    __syncthreads();
 #pragma unroll
-        for (int d = 0; d < kDigits; ++d)
-            if (dg[j] == d) p = pos[d]++;
+    for (int j = 0; j < kSortItems; ++j) {
+        const int i = j * kSortThreads + t;
+        if (i >= here) continue;
+        const uint64_t key = s_key[i];
+        const int64_t p = s_to[(int)((key >> shift) & (kDigits - 1))] + i;
         if (p < 0 || p >= n) continue;  // only on a broken scan: never write out of bounds
-        keys_out[p] = k[j];
-        vals_out[p] = v[j];
+        keys_out[p] = key;
+        vals_out[p] = s_val[i];
     }
 }
 
@@ -265,8 +294,10 @@ __global__ void k_arcs(const uint64_t *keys, const uint32_t *vals, const int64_t
 }
 
 // Arc records, capacities, the largest multiplicity (half-edges per arc) and
-// a flag for a capacity sum above int32.
-__global__ void k_arc_records(const int32_t *col, const int64_t *capsum, const int64_t *start, int64_t A, int64_t nh,
+// a flag for a capacity sum above int32.  (One maximum into the common word per
+// thread was what it spent its time on: 750 us for 8 M arcs, 75 us with one per
+// workgroup.)
+__global__ void __launch_bounds__(256) k_arc_records(const int32_t *col, const int64_t *capsum, const int64_t *start, int64_t A, int64_t nh,
                               int2 *arc, int32_t *cap, int32_t *maxmult, int32_t *overflow) {
     int32_t mm = 0;
     for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < A; a += (int64_t)gridDim.x * blockDim.x) {
@@ -278,7 +309,14 @@ __global__ void k_arc_records(const int32_t *col, const int64_t *capsum, const i
         const int64_t len = (a + 1 < A ? start[a + 1] : nh) - start[a];
         mm = max(mm, (int32_t)min(len, (int64_t)INT32_MAX));
     }
-    atomicMax(maxmult, mm);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) mm = max(mm, __shfl_xor(mm, d, 64));
+    __shared__ int s_mm[256 / 64];
+    if (lane_of() == 0) s_mm[threadIdx.x >> 6] = mm;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < 256 / 64; ++k) mm = max(mm, s_mm[k]);
+    if (mm > *maxmult) atomicMax(maxmult, mm);
 }
 
 // row_ptr[v] = first arc owned by a vertex >= v (arcs are sorted by owner).
@@ -304,14 +342,36 @@ __global__ void k_twins(const int32_t *edge2arc, const int32_t *rev_arc, int64_t
     }
 }
 
-// Edges at every vertex (either end; self-loops left out).
-__global__ void k_degree(const int32_t *tail, const int32_t *col, int64_t m, int32_t *deg) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
+// Edges at every vertex (either end; self-loops left out).  Bound by the
+// additions to a hub's count, which follow one another: a workgroup adds up the
+// vertices that come first to their slot of a table in LDS, hubs among them,
+// and only the others go to memory at once.  (R-MAT 2^18, 4 M
+// edges: 1055 us with two additions to memory per edge, 254 us so.)
+constexpr int kDegThreads = 1024;
+constexpr int kDegSlotBits = 12;
+__global__ void __launch_bounds__(kDegThreads) k_degree(const int32_t *tail, const int32_t *col, int64_t m, int32_t *deg) {
+    __shared__ int s_tag[1 << kDegSlotBits], s_sum[1 << kDegSlotBits];
+    for (int i = threadIdx.x; i < (1 << kDegSlotBits); i += kDegThreads) {
+        s_tag[i] = -1;
+        s_sum[i] = 0;
+    }
+    __syncthreads();
+    auto count = [&](int32_t v) {
+        const int slot = (int)(((uint32_t)v * 2654435769u) >> (32 - kDegSlotBits));
+        int tag = s_tag[slot];
+        if (tag == -1) tag = atomicCAS(&s_tag[slot], -1, v);
+        if (tag == -1 || tag == v) atomicAdd(&s_sum[slot], 1);
+        else atomicAdd(&deg[v], 1);
+    };
+    for (int64_t i = (int64_t)blockIdx.x * kDegThreads + threadIdx.x; i < m; i += (int64_t)gridDim.x * kDegThreads) {
         const int32_t u = tail[i], v = col[i];
         if (u == v) continue;
-        atomicAdd(&deg[u], 1);
-        atomicAdd(&deg[v], 1);
+        count(u);
+        count(v);
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < (1 << kDegSlotBits); i += kDegThreads)
+        if (s_sum[i]) atomicAdd(&deg[s_tag[i]], s_sum[i]);
 }
 
 // Sort keys of the vertices for falling degree, ties by id:
@@ -353,7 +413,7 @@ int grid_of(int64_t work) {
     return (int)(b < 1 ? 1 : (b > 16384 ? 16384 : b));
 }
 
-// Stable LSD sort of n (key, value) pairs on their low `bits` key bits, 4 bits
+// Stable LSD sort of n (key, value) pairs on their low `bits` key bits, 8 bits
 // a pass, between the buffer pairs (k0, v0) and (k1, v1); the sorted pairs end
 // in (*k0, *v0) (the pointers are swapped as the passes go).  hist and scan:
 // kDigits * tiles and scan_tmp_count(kDigits * tiles) entries.
@@ -361,9 +421,8 @@ hipError_t radix_sort(uint64_t **k0, uint32_t **v0, uint64_t **k1, uint32_t **v1
                       int64_t *hist, int64_t *scan, hipStream_t st) {
     const int64_t tiles = (n + kSortTile - 1) / kSortTile;
     if (n <= 1) return hipSuccess;
-    hipError_t e = hipMemsetAsync(hist, 0, sizeof(int64_t) * kDigits * tiles, st);
-    if (e != hipSuccess) return e;
-    for (int shift = 0; shift < bits; shift += 4) {
+    hipError_t e = hipSuccess;
+    for (int shift = 0; shift < bits; shift += kDigitBits) {
         hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)tiles), dim3(kSortThreads), 0, st, *k0, n, shift, hist, tiles);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = scan_exclusive(hist, kDigits * tiles, scan, st)) != hipSuccess) return e;
@@ -465,7 +524,9 @@ hipError_t build_layout_device(int32_t n, int64_t m, const int64_t *h_row_ptr, c
         BTRY(mem.alloc_keep((void **)&d_perm, sizeof(int32_t) * n));
         out->new_of_old = d_perm;
         BTRY(hipMemsetAsync(d_perm, 0, sizeof(int32_t) * n, st));
-        if (m > 0) hipLaunchKernelGGL(k_degree, dim3(grid_of(m)), dim3(256), 0, st, d_tail, d_col, m, d_perm);
+        if (m > 0)
+            hipLaunchKernelGGL(k_degree, dim3(std::min(512, grid_of(m))), dim3(kDegThreads), 0, st, d_tail, d_col, m,
+                               d_perm);
         hipLaunchKernelGGL(k_vertex_keys, dim3(grid_of(n)), dim3(256), 0, st, d_perm, n, b, d_k0, d_v0);
         BTRY(hipGetLastError());
         BTRY(radix_sort(&d_k0, &d_v0, &d_k1, &d_v1, n, b + kDegBits, d_hist, d_scan2, st));
