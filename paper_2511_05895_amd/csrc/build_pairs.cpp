@@ -16,7 +16,7 @@
 namespace mf {
 
 int check_graph(int32_t n, int64_t m, const int64_t *row_ptr, const int32_t *col, const int32_t *cap,
-                int32_t s, int32_t t, std::string *err) {
+                int32_t s, int32_t t, std::string *err, int32_t *cap_most) {
     auto bad = [&](const char *why) {
         *err = why;
         return -1;
@@ -29,10 +29,22 @@ int check_graph(int32_t n, int64_t m, const int64_t *row_ptr, const int32_t *col
     if (row_ptr[0] != 0 || row_ptr[n] != m) return bad("row_ptr must run from 0 to m");
     for (int32_t v = 0; v < n; ++v)
         if (row_ptr[v + 1] < row_ptr[v]) return bad("row_ptr not non-decreasing");
+    // one pass without branches; the first fault is looked up only if one is there
+    uint32_t col_most = 0;
+    int32_t least = 0, most = 0;
     for (int64_t i = 0; i < m; ++i) {
-        if (col[i] < 0 || col[i] >= n) return bad("col out of range");
-        if (cap[i] < 0) return bad("negative capacity");
+        const uint32_t c = (uint32_t)col[i];
+        col_most = c > col_most ? c : col_most;
+        least = cap[i] < least ? cap[i] : least;
+        most = cap[i] > most ? cap[i] : most;
     }
+    if (m > 0 && (col_most >= (uint32_t)n || least < 0)) {
+        for (int64_t i = 0; i < m; ++i) {
+            if (col[i] < 0 || col[i] >= n) return bad("col out of range");
+            if (cap[i] < 0) return bad("negative capacity");
+        }
+    }
+    if (cap_most) *cap_most = most;
     return 0;
 }
 

@@ -22,9 +22,9 @@ struct HostPairs {
 
 // Argument checks of one graph: n >= 2, s and t distinct and in range,
 // row_ptr non-decreasing from 0 to m < 2^31-1, col in [0, n), cap >= 0.
-// Returns 0, or -1 with *err set.
+// Returns 0, or -1 with *err set.  *cap_most: the largest capacity (or 0).
 int check_graph(int32_t n, int64_t m, const int64_t *row_ptr, const int32_t *col, const int32_t *cap,
-                int32_t s, int32_t t, std::string *err);
+                int32_t s, int32_t t, std::string *err, int32_t *cap_most = nullptr);
 
 // Per-edge capacity limit of a layout whose busiest arc pair merges `mult`
 // input edges: after the deltas of one batch land, an arc's residual is at

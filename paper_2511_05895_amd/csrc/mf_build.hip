@@ -448,11 +448,6 @@ hipError_t build_layout_device(int32_t n, int64_t m, const int64_t *h_row_ptr, c
                                DeviceLayout *out, std::vector<int32_t> *h_row_ptr_out,
                                std::vector<int32_t> *h_new_of_old, std::string *err) {
     std::vector<void *> tmp;
-    auto talloc = [&](void **p, size_t bytes) -> hipError_t {
-        hipError_t e = mem.alloc(p, bytes < 256 ? 256 : bytes);
-        if (e == hipSuccess) tmp.push_back(*p);
-        return e;
-    };
     auto cleanup = [&]() {
         (void)hipStreamSynchronize(st);
         for (void *p : tmp) mem.release(p);
@@ -469,21 +464,20 @@ hipError_t build_layout_device(int32_t n, int64_t m, const int64_t *h_row_ptr, c
     } while (0)
     int64_t *d_rp = nullptr, *d_flag = nullptr, *d_scan = nullptr, *d_hist = nullptr;
     int32_t *d_tail = nullptr, *d_col = nullptr, *d_ecap = nullptr, *d_info = nullptr;
-    BTRY(talloc((void **)&d_rp, sizeof(int64_t) * (n + 1)));
-    BTRY(talloc((void **)&d_col, sizeof(int32_t) * (m > 0 ? m : 1)));
-    BTRY(talloc((void **)&d_tail, sizeof(int32_t) * (m > 0 ? m : 1)));
-    BTRY(talloc((void **)&d_info, sizeof(int32_t) * 4));
-    // the edge capacities stay with the handle (ecap)
-    BTRY(mem.alloc_keep((void **)&d_ecap, sizeof(int32_t) * (m > 0 ? m : 1)));
+    int32_t *d_perm = nullptr;
+    const int64_t mm = m > 0 ? m : 1;
+    BTRY(mem.alloc({want(&d_rp, (int64_t)n + 1), want(&d_col, m), want(&d_tail, m), want(&d_info, 4),
+                    want(&d_flag, mm + 1), want(&d_scan, scan_tmp_count(2 * mm + 1))},
+                   &tmp));
+    // the edge capacities stay with the handle (ecap), and so does the numbering
+    if (renumber && n > 0) BTRY(mem.keep({want(&d_ecap, m), want(&d_perm, n)}));
+    else BTRY(mem.keep({want(&d_ecap, m)}));
     BTRY(hipMemcpyAsync(d_rp, h_row_ptr, sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, st));
     if (m > 0) {
         BTRY(hipMemcpyAsync(d_col, h_col, sizeof(int32_t) * m, hipMemcpyHostToDevice, st));
         BTRY(hipMemcpyAsync(d_ecap, h_cap, sizeof(int32_t) * m, hipMemcpyHostToDevice, st));
     }
     // 1-2: tails, non-loop positions, half-edges
-    const int64_t mm = m > 0 ? m : 1;
-    BTRY(talloc((void **)&d_flag, sizeof(int64_t) * (mm + 1)));
-    BTRY(talloc((void **)&d_scan, sizeof(int64_t) * scan_tmp_count(2 * mm + 1)));
     int64_t nonloop = 0;
     if (m > 0) {
         hipLaunchKernelGGL(k_tails, dim3(grid_of(m)), dim3(256), 0, st, d_rp, n, m, d_tail);
@@ -508,20 +502,16 @@ hipError_t build_layout_device(int32_t n, int64_t m, const int64_t *h_row_ptr, c
     uint64_t *d_k0 = nullptr, *d_k1 = nullptr;
     uint32_t *d_v0 = nullptr, *d_v1 = nullptr;
     const int64_t nhh = std::max<int64_t>(nh > 0 ? nh : 1, renumber ? n : 1);
-    BTRY(talloc((void **)&d_k0, sizeof(uint64_t) * nhh));
-    BTRY(talloc((void **)&d_k1, sizeof(uint64_t) * nhh));
-    BTRY(talloc((void **)&d_v0, sizeof(uint32_t) * nhh));
-    BTRY(talloc((void **)&d_v1, sizeof(uint32_t) * nhh));
     const int64_t tiles = (nhh + kSortTile - 1) / kSortTile;
-    int64_t *d_scan2 = nullptr;
-    BTRY(talloc((void **)&d_hist, sizeof(int64_t) * kDigits * tiles));
-    BTRY(talloc((void **)&d_scan2, sizeof(int64_t) * scan_tmp_count(kDigits * tiles)));
+    int64_t *d_scan2 = nullptr, *d_idx = nullptr;
+    BTRY(mem.alloc({want(&d_k0, nhh), want(&d_k1, nhh), want(&d_v0, nhh), want(&d_v1, nhh),
+                    want(&d_hist, kDigits * tiles), want(&d_scan2, scan_tmp_count(kDigits * tiles)),
+                    want(&d_idx, nhh + 1)},
+                   &tmp));
     // 2b: the handle's vertex order: falling degree (ties by id), so that the
     // hubs' heights, excesses and row bounds share a few cache lines and
     // every arc list starts with its hub neighbours
-    int32_t *d_perm = nullptr;
     if (renumber && n > 0) {
-        BTRY(mem.alloc_keep((void **)&d_perm, sizeof(int32_t) * n));
         out->new_of_old = d_perm;
         BTRY(hipMemsetAsync(d_perm, 0, sizeof(int32_t) * n, st));
         if (m > 0)
@@ -546,8 +536,6 @@ hipError_t build_layout_device(int32_t n, int64_t m, const int64_t *h_row_ptr, c
     BTRY(radix_sort(&d_k0, &d_v0, &d_k1, &d_v1, nh, 2 * b, d_hist, d_scan2, st));
     // 4: arcs
     int64_t A = 0;
-    int64_t *d_idx = nullptr;
-    BTRY(talloc((void **)&d_idx, sizeof(int64_t) * (nhh + 1)));
     if (nh > 0) {
         hipLaunchKernelGGL(k_run_starts, dim3(grid_of(nh)), dim3(256), 0, st, d_k0, nh, d_idx);
         BTRY(hipGetLastError());
@@ -567,17 +555,11 @@ hipError_t build_layout_device(int32_t n, int64_t m, const int64_t *h_row_ptr, c
     const int64_t AA = A > 0 ? A : 1;
     int32_t *d_colA = nullptr, *d_owner = nullptr, *d_rev = nullptr;
     int64_t *d_start = nullptr, *d_capsum = nullptr;
-    BTRY(talloc((void **)&d_colA, sizeof(int32_t) * AA));
-    BTRY(talloc((void **)&d_owner, sizeof(int32_t) * AA));
-    BTRY(talloc((void **)&d_start, sizeof(int64_t) * AA));
-    BTRY(talloc((void **)&d_capsum, sizeof(int64_t) * AA));
-    BTRY(talloc((void **)&d_rev, sizeof(int32_t) * mm));
+    BTRY(mem.alloc({want(&d_colA, AA), want(&d_owner, AA), want(&d_start, AA), want(&d_capsum, AA), want(&d_rev, mm)},
+                   &tmp));
     // the handle's arrays
-    BTRY(mem.alloc_keep((void **)&out->row_ptr, sizeof(int32_t) * (n + 1)));
-    BTRY(mem.alloc_keep((void **)&out->arc, sizeof(int2) * AA));
-    BTRY(mem.alloc_keep((void **)&out->twin, sizeof(int32_t) * AA));
-    BTRY(mem.alloc_keep((void **)&out->cap, sizeof(int32_t) * AA));
-    BTRY(mem.alloc_keep((void **)&out->edge2arc, sizeof(int32_t) * mm));
+    BTRY(mem.keep({want(&out->row_ptr, (int64_t)n + 1), want(&out->arc, AA), want(&out->twin, AA),
+                   want(&out->cap, AA), want(&out->edge2arc, mm)}));
     out->ecap = d_ecap;
     BTRY(hipMemsetAsync(d_capsum, 0, sizeof(int64_t) * AA, st));
     BTRY(hipMemsetAsync(d_info, 0, sizeof(int32_t) * 4, st));
@@ -612,11 +594,6 @@ hipError_t caller_arc_order(int32_t n, int64_t A, const int2 *arc, const int32_t
                             const std::vector<int32_t> &old_of_new, const BuildAlloc &mem, hipStream_t st,
                             std::vector<int32_t> *h_caller_of_arc) {
     std::vector<void *> tmp;
-    auto talloc = [&](void **p, size_t bytes) -> hipError_t {
-        hipError_t e = mem.alloc(p, bytes < 256 ? 256 : bytes);
-        if (e == hipSuccess) tmp.push_back(*p);
-        return e;
-    };
     hipError_t e = hipSuccess;
     auto done = [&](hipError_t r) {
         (void)hipStreamSynchronize(st);
@@ -629,15 +606,10 @@ hipError_t caller_arc_order(int32_t n, int64_t A, const int2 *arc, const int32_t
     uint32_t *v0 = nullptr, *v1 = nullptr;
     int32_t *d_old = nullptr, *d_rank = nullptr;
     int64_t *hist = nullptr, *scan = nullptr;
-    if ((e = talloc((void **)&k0, sizeof(uint64_t) * AA)) != hipSuccess ||
-        (e = talloc((void **)&k1, sizeof(uint64_t) * AA)) != hipSuccess ||
-        (e = talloc((void **)&v0, sizeof(uint32_t) * AA)) != hipSuccess ||
-        (e = talloc((void **)&v1, sizeof(uint32_t) * AA)) != hipSuccess ||
-        (e = talloc((void **)&d_old, sizeof(int32_t) * (n > 0 ? n : 1))) != hipSuccess ||
-        (e = talloc((void **)&d_rank, sizeof(int32_t) * AA)) != hipSuccess ||
-        (e = talloc((void **)&hist, sizeof(int64_t) * kDigits * tiles)) != hipSuccess ||
-        (e = talloc((void **)&scan, sizeof(int64_t) * scan_tmp_count(kDigits * tiles))) != hipSuccess)
-        return done(e);
+    e = mem.alloc({want(&k0, AA), want(&k1, AA), want(&v0, AA), want(&v1, AA), want(&d_old, n), want(&d_rank, AA),
+                   want(&hist, kDigits * tiles), want(&scan, scan_tmp_count(kDigits * tiles))},
+                  &tmp);
+    if (e != hipSuccess) return done(e);
     if (n > 0 && (e = hipMemcpyAsync(d_old, old_of_new.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, st)) !=
                      hipSuccess)
         return done(e);

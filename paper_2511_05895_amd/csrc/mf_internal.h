@@ -5,7 +5,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <functional>
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -351,13 +353,24 @@ constexpr int64_t kNoAllocCapsBytes = kNoAllocMaxUpdates * (int64_t)sizeof(int32
 hipError_t noalloc_scratch_setup(int device);
 void *noalloc_scratch(int device);
 
+// An array that is wanted: where its address goes, and its bytes.
+struct Want {
+    void **p;
+    size_t bytes;
+};
+template <typename T>
+Want want(T **p, int64_t count) {
+    return {reinterpret_cast<void **>(p), sizeof(T) * (size_t)std::max<int64_t>(count, 1)};
+}
+
 // Device build of the merged arc-pair layout (mf_build.hip).  alloc /
-// release: temporary device memory of the build; alloc_keep: memory the
-// handle keeps (and frees with itself).
+// release: temporary device memory of the build, a group of arrays at a time
+// (what has to be released goes to the vector, also of a group that failed);
+// keep: memory the handle keeps (and frees with itself).
 struct BuildAlloc {
-    std::function<hipError_t(void **, size_t)> alloc;
+    std::function<hipError_t(std::initializer_list<Want>, std::vector<void *> *)> alloc;
     std::function<void(void *)> release;
-    std::function<hipError_t(void **, size_t)> alloc_keep;
+    std::function<hipError_t(std::initializer_list<Want>)> keep;
 };
 struct DeviceLayout {
     int32_t A = 0;
