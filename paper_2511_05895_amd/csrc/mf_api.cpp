@@ -48,6 +48,8 @@ struct mf_handle {
     mf::DevGraph g{};
     std::vector<void *> allocs;
     mf::Ctrl *h_ctrl = nullptr;  // pinned read-back of the control block
+    uint8_t *h_side = nullptr;   // pinned cut side behind it (at most kHostSide vertices), or null
+    bool long_lists = false;     // some vertex has more than kChunk arcs
     // staging of host update batches: one device buffer and its pinned host
     // copy, ids then capacities back to back, so that one copy uploads both;
     // d_ids / d_caps point into it for the current call
@@ -147,6 +149,10 @@ constexpr int64_t kXcdMaxArcs = 1 << 22;
 // Rounds of local pulls into the deficits a batch leaves (the last one
 // without handing deficits on).
 constexpr int kPullRounds = 4;
+// Vertices up to which the cut's side is stored to the host by the kernel, copy
+// against this: 20 k vertices 38 to 17 us, 200 k 42 to 30, 2^20 118 to 106 (it is
+// pinned memory of every handle, so no more than 1 MB).
+constexpr int32_t kHostSide = 1 << 20;
 
 int fail(mf_handle_t *h, int code, const std::string &msg) {
     if (h) h->err = msg;
@@ -825,8 +831,10 @@ MF_API int mf_create(const mf_csr_t *g, const int32_t *cap, int32_t s, int32_t t
     for (auto &ev : h->ev)
         if ((e = hipEventCreate(&ev)) != hipSuccess)
             return bail(MF_EDEVICE, std::string("hipEventCreate: ") + hipGetErrorString(e));
-    if ((e = hipHostMalloc((void **)&h->h_ctrl, sizeof(mf::Ctrl), hipHostMallocDefault)) != hipSuccess)
+    const size_t side_bytes = n <= kHostSide ? ((size_t)n + 3) & ~(size_t)3 : 0;
+    if ((e = hipHostMalloc((void **)&h->h_ctrl, sizeof(mf::Ctrl) + side_bytes, hipHostMallocDefault)) != hipSuccess)
         return bail(MF_ENOMEM, "pinned control block");
+    if (side_bytes) h->h_side = reinterpret_cast<uint8_t *>(h->h_ctrl + 1);
 
     // a0: the merged arc-pair layout, built on the device (mf_build.hip); the
     // arc row pointers come back for the host-side lists below
@@ -877,6 +885,7 @@ MF_API int mf_create(const mf_csr_t *g, const int32_t *cap, int32_t s, int32_t t
         const int32_t deg = hrow[v + 1] - hrow[v];
         if (v != s && v != t && deg > mf::kLightMaxDeg) heavy.push_back(v);
         if (v != s && v != t && deg > mf::kHugeDeg) nhuge++;
+        if (deg > mf::kChunk) h->long_lists = true;
     }
     // vertices of huge degree draw pushes from many others at once: add them
     // up per workgroup first
@@ -1146,11 +1155,14 @@ MF_API int mf_min_cut(mf_handle_t *h, uint8_t *side_out, int64_t *cut_cap_out) {
     if (!h) return fail(nullptr, MF_EINVAL, "null handle");
     if (h->state != State::Solved) return fail(h, MF_ESTATE, "not solved");
     HIP_TRY(h, hipSetDevice(h->device));
-    HIP_TRY(h, mf::launch_min_cut(h->g, h->d_new_of_old, side_out ? h->d_side : nullptr, h->stream));
-    HIP_TRY(h, hipMemcpyAsync(&h->h_ctrl->cut, &h->g.ctrl->cut, sizeof(int64_t), hipMemcpyDeviceToHost, h->stream));
-    if (side_out)
+    // a short side goes to pinned memory straight from the kernel: a copy to
+    // pageable memory takes longer to start than the whole cut
+    uint8_t *side = !side_out ? nullptr : h->h_side ? h->h_side : h->d_side;
+    HIP_TRY(h, mf::launch_min_cut(h->g, h->d_new_of_old, side, h->long_lists, &h->h_ctrl->cut, h->stream));
+    if (side_out && !h->h_side)
         HIP_TRY(h, hipMemcpyAsync(side_out, h->d_side, (size_t)h->g.n, hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (side_out && h->h_side) std::memcpy(side_out, h->h_side, (size_t)h->g.n);
     if (cut_cap_out) *cut_cap_out = h->h_ctrl->cut;
     return MF_OK;
 }

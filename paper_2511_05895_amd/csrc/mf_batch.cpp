@@ -726,9 +726,8 @@ MF_API int mf_batch_min_cut(mf_batch_t *b, int32_t i, uint8_t *side, int64_t *cu
     if (!b->solved) return bfail(b, MF_ESTATE, "not solved");
     const mf::DevGraph &g = b->g[i];
     BHIP(b, hipSetDevice(b->device));
-    BHIP(b, mf::launch_min_cut(g, nullptr, side ? b->d_side : nullptr, b->stream));
+    BHIP(b, mf::launch_min_cut(g, nullptr, side ? b->d_side : nullptr, g.A > mf::kChunk, &b->h_ctrl->cut, b->stream));
     if (side) BHIP(b, hipMemcpyAsync(side, b->d_side, g.n, hipMemcpyDeviceToHost, b->stream));
-    BHIP(b, hipMemcpyAsync(b->h_ctrl, g.ctrl, sizeof(mf::Ctrl), hipMemcpyDeviceToHost, b->stream));
     BHIP(b, hipStreamSynchronize(b->stream));
     if (cut_cap) *cut_cap = b->h_ctrl->cut;
     return MF_OK;

@@ -144,7 +144,7 @@ struct Ctrl : BarWords {
     int64_t e_t;        // e(t) at termination
     int64_t cut;        // cut capacity
     int32_t cut_items;  // pieces of long arc lists still to be summed into it
-    int32_t cut_pad;
+    int32_t cut_done;   // workgroups that added their share
     // state of the rounds a workgroup ran alone, handed to the others
     int64_t run_arcs;   // arcs of the vertices that BFS runs discovered (this launch)
     int32_t solo_r, solo_done, solo_reason, solo_last_change;
@@ -292,9 +292,12 @@ hipError_t launch_local_stage(const DevGraph &g, const Repair &b, hipStream_t st
 // The solve kernel on a cleared control block.  b: the repair of an update
 // batch, made before the loop, and where the host wants the control block.
 hipError_t launch_loop(const DevGraph &g, const LoopParams &p, const Repair &b, int grid, hipStream_t st);
-// Source side (d_side: n bytes, in whole words, in the order of the caller's
-// ids; or null) and cut capacity (ctrl->cut); uses the frontier buffer q[0].
-hipError_t launch_min_cut(const DevGraph &g, const int32_t *new_of_old, uint8_t *d_side, hipStream_t st);
+// Source side (side: n bytes, in whole words, in the order of the caller's
+// ids; or null) and cut capacity (*cut), both to the device or to pinned host
+// memory; uses the frontier buffer q[0].  long_lists: some vertex may have more
+// than kChunk arcs.  ctrl->cut, cut_items and cut_done are zero before and after.
+hipError_t launch_min_cut(const DevGraph &g, const int32_t *new_of_old, uint8_t *side, bool long_lists, int64_t *cut,
+                          hipStream_t st);
 // Invariant check of the state into ctrl->check (cleared first): 1 c_f < 0,
 // 2 pair sum broken, 4 excess != residual change, and when solved 8 active
 // vertex left, 16 residual arc from the source side to the sink side.

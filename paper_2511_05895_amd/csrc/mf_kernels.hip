@@ -3255,12 +3255,26 @@ __global__ void k_init_state(DevGraph g) {
 // kChunk arcs go to k_cut_items in items, so a hub is split over the device.
 // Bound by the read of the heights when the sink side is small.  R-MAT 2^22 x
 // 16: 5.1 ms (scanning the source side, the numbering undone on the host) ->
-// 0.36 ms; 2^20: 1.12 -> 0.12 ms; a 512 x 512 grid: 175 -> 101 us.
+// 0.36 ms; 2^20: 1.12 -> 0.11 ms; a 512 x 512 grid: 175 -> 112 us; 20 k vertices:
+// 62 -> 17 us, one launch (without lists to split) and no copy.
 __device__ __forceinline__ int64_t cut_arc(const DevGraph &g, int a) {
     return g.h[g.arc[a].x] >= g.n ? (int64_t)g.cap[g.twin[a]] : 0;
 }
 
-__global__ void k_cut_side(DevGraph g, const int32_t *new_of_old, uint8_t *side) {
+// The last workgroup of the launch hands the sum out and leaves the words at
+// zero for the next cut.  Every thread calls it.
+__device__ __forceinline__ void cut_finish(Ctrl *c, int64_t *cut) {
+    block_sync<kXcd>();  // the workgroup's additions have been made
+    if (threadIdx.x != 0) return;
+    const int last = (int)gridDim.x - 1;
+    if (__hip_atomic_fetch_add(&c->cut_done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != last) return;
+    *cut = __hip_atomic_exchange(&c->cut, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    c->cut_items = 0;
+    c->cut_done = 0;
+}
+
+// cut: where the sum goes, or null if k_cut_items follows.
+__global__ void k_cut_side(DevGraph g, const int32_t *new_of_old, uint8_t *side, int64_t *cut) {
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     if (side) {  // four vertices a word (side is allocated in whole words)
@@ -3307,9 +3321,10 @@ __global__ void k_cut_side(DevGraph g, const int32_t *new_of_old, uint8_t *side)
     }
     part = wave_sum(part);
     if (lane == 0 && part) add<kAgent>(&g.ctrl->cut, part);
+    if (cut) cut_finish(g.ctrl, cut);
 }
 
-__global__ void k_cut_items(DevGraph g) {
+__global__ void k_cut_items(DevGraph g, int64_t *cut) {
     const int lane = lane_id();
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -3321,6 +3336,7 @@ __global__ void k_cut_items(DevGraph g) {
     }
     part = wave_sum(part);
     if (lane == 0 && part) add<kAgent>(&g.ctrl->cut, part);
+    cut_finish(g.ctrl, cut);
 }
 
 __global__ void k_fill_i32(int32_t *p, int64_t count, int32_t value) {
@@ -3674,13 +3690,12 @@ hipError_t launch_edge_flow(const DevGraph &g, const int2 *carc, int32_t *rem, i
     return hipGetLastError();
 }
 
-hipError_t launch_min_cut(const DevGraph &g, const int32_t *new_of_old, uint8_t *d_side, hipStream_t st) {
-    static_assert(offsetof(Ctrl, cut_items) == offsetof(Ctrl, cut) + 8, "cut and cut_items are cleared together");
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, reinterpret_cast<int32_t *>(&g.ctrl->cut), (int64_t)3, 0);
-    const int blocks = grid_for(g.n, 256, 2048);
-    hipLaunchKernelGGL(k_cut_side, dim3(blocks), dim3(256), 0, st, g, new_of_old, d_side);
-    // items only where a list is longer than one
-    if (g.A > kChunk) hipLaunchKernelGGL(k_cut_items, dim3(grid_for(g.A / kChunk, 4, 1024)), dim3(256), 0, st, g);
+hipError_t launch_min_cut(const DevGraph &g, const int32_t *new_of_old, uint8_t *side, bool long_lists, int64_t *cut,
+                          hipStream_t st) {
+    hipLaunchKernelGGL(k_cut_side, dim3(grid_for(g.n, 256, 2048)), dim3(256), 0, st, g, new_of_old, side,
+                       long_lists ? nullptr : cut);
+    if (long_lists)
+        hipLaunchKernelGGL(k_cut_items, dim3(grid_for(g.A / kChunk, 4, 1024)), dim3(256), 0, st, g, cut);
     return hipGetLastError();
 }
 
