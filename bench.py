@@ -132,8 +132,8 @@ def cpu_baseline(g, cap0, batches, A, max_seconds):
 
 
 def run_batch(args):
-    """C4: one batched solve of 256 independent instances (one workgroup per
-    instance, size classes autotuned, hipGraph replay) per step, against 256
+    """C4: one batched solve of 256 independent instances (a workgroup or a team
+    of one XCD per instance, size classes autotuned, hipGraph replay) per step, against 256
     sequential solves on single handles and against the same handles driven
     from 16 host threads (one stream per handle)."""
     import concurrent.futures as cf
@@ -220,7 +220,7 @@ def run_batch(args):
         "speedup_vs_sequential": float(np.median(seq) / np.percentile(wall, 50)),
         "speedup_vs_stream_per_instance": float(np.median(par) / np.percentile(wall, 50)),
         "exact": "batched values == single-handle values (sequential and concurrent) on every step",
-        "roofline": {"kernel": "k_batch (one workgroup per instance)", "bound": "hbm", "achieved": achieved,
+        "roofline": {"kernel": "k_batch and k_batch_teams (a workgroup or an XCD's team per instance)", "bound": "hbm", "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": None, "alg_bytes_per_launch": alg,
                      "avg_launch_ms": float(kern.mean())},

@@ -387,11 +387,13 @@ MF_API int mf_set_stream(mf_handle_t *h, void *stream);
  * scratch (the static method of Alg. 1: saturate the source, then global
  * relabel / push-relabel / RemoveInvalidEdges until no active vertex is
  * left).  The instances are packed block-diagonally into one set of device
- * arrays and each is solved by ONE workgroup of a persistent launch, so no
- * grid barrier is involved and workgroups never wait for each other.
+ * arrays and each is solved by one workgroup of a persistent launch, or, in
+ * classes of 1024-thread workgroups, by a team of them on one XCD when the
+ * batch ends sooner that way; instances never wait for each other.
  * Instances are grouped by their number of residual arcs into size classes;
- * each class is one launch with its own workgroup size and KERNELCYCLES,
- * instances ordered largest first inside it; the classes run side by side.
+ * each class is one launch with its own workgroup size and KERNELCYCLES
+ * (neighbouring classes solved by teams share a launch), instances ordered
+ * largest first inside it; the classes run side by side.
  * With use_graph the launches are captured into a hipGraph on the first solve
  * after a configuration change and that graph is replayed by later solves.
  * Values and cuts follow the same definitions as for a single handle.

@@ -1,11 +1,12 @@
 // Batched solve of many independent max-flow instances (mf_batch_* in
 // include/mf.h).  The instances are packed block-diagonally into one set of
-// device arrays; every instance is solved from scratch by one workgroup of a
-// persistent launch (no grid barrier: a workgroup barrier separates the steps
-// of its instance).  Instances are grouped into size classes by arc count;
-// each class is one launch with its own workgroup size and KERNELCYCLES, the
-// classes run side by side on forked streams, and the whole fork/join is
-// captured once into a hipGraph that later solves replay.
+// device arrays; every instance is solved from scratch by one workgroup, or, in
+// the classes of 1024-thread workgroups, by a team of workgroups of one XCD
+// where that ends the batch sooner (team_size).  Instances are grouped into
+// size classes by arc count; each class is one launch with its own workgroup
+// size and KERNELCYCLES (classes of teams share one), the launches run side by
+// side on forked streams, and the whole fork/join is captured once into a
+// hipGraph that later solves replay.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -109,7 +109,7 @@ struct BarWords {
 };
 
 // Device control block: barrier words, then loop counters.  Reset by
-// k_reset_ctrl before every solving call.
+// k_begin before every solving call.
 struct Ctrl : BarWords {
     PaddedU32 join;       // workgroups that registered for the launch's team (top bit: closed)
     PaddedU32 team_size;  // its size once closed

@@ -2773,9 +2773,10 @@ constexpr int kPullScan = 4096;
 // tags rise from call to call), so a claim or an append takes a vertex only
 // if its mark is still below the tag: a vertex that round 0 already put on
 // the next round's list (tag) is not claimed again as a batch end (tag - 1)
-// while its first visit may still be running.  The list counters rotate over three words, cnt[r % 3] read and
-// cnt[(r + 1) % 3] appended to by round r, which clears cnt[(r + 2) % 3] for
-// round r + 1; they all start at zero with the call's control block.
+// while its first visit may still be running.  The list counters rotate over
+// three words, cnt[r % 3] read and cnt[(r + 1) % 3] appended to by round r,
+// which clears cnt[(r + 2) % 3] for round r + 1; they all start at zero with
+// the call's control block.
 //
 // A wavefront looks its share of the batch up lane by lane and then visits the
 // deficient ends it found, one after another: what bounds a large batch is the
@@ -3383,7 +3384,7 @@ hipError_t launch_check_state(const DevGraph &g, int solved, hipStream_t st) {
 
 
 // ---------------------------------------------------------------------------
-// Batched solve: one workgroup per instance
+// Batched solve: one workgroup per instance, or a team of one XCD
 // ---------------------------------------------------------------------------
 
 // order[blockIdx.x] names the instance.  Its workgroup clears the control

@@ -14,10 +14,10 @@
 //   after that commit.
 // * Several workers drive different graphs at the same time; each graph's
 //   handle has its own stream, so their kernels overlap on the device.  A
-//   graph's persistent solve kernel is a cooperative grid whose workgroups
-//   must all be resident at once; a commit starts only while the grids in
-//   flight leave room for its grid (workgroup slots of the device), so
-//   concurrent tenants never starve one another's grid barriers.
+//   graph's persistent solve kernel is run by the workgroups that are resident
+//   when its team forms; a commit starts only while the grids in flight leave
+//   room for its grid (workgroup slots of the device), so that concurrent
+//   tenants' teams reach their full size.
 // * Requests are admitted by memory: the queued requests' bytes stay within
 //   max_pending_bytes (else MF_EBUSY, nothing queued), and a request may not
 //   exceed the edges one commit stages (max_group_edges), so the staging
