@@ -2910,7 +2910,7 @@ __device__ __forceinline__ void repair_alone(const DevGraph &g, const Repair &b,
         id[u] = mine[u] ? b.ids[i] : 0;
         cv[u] = mine[u] ? b.caps[i] : 0;
         if (mine[u] && (cv[u] < 0 || cv[u] > b.cap_limit)) bad |= 2;
-        if (id[u] < 0 || id[u] >= g.m) {
+        if (mine[u] && (id[u] < 0 || id[u] >= g.m)) {
             bad |= 1;
             mine[u] = false;
         }
