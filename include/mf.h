@@ -289,8 +289,9 @@ MF_API int mf_set_capacities(mf_handle_t *h, const int64_t *edge_ids, const int3
                              int64_t k);
 
 /* Continue the loop from the current state after MF_ETIMEOUT (or after a
- * call made with max_iterations == 0).  MF_ESTATE if the flow was never
- * initialised. */
+ * call made with max_iterations == 0), after an aborted launch (MF_EDEVICE,
+ * barrier wait) or from an imported state; residual capacity left on arcs out
+ * of s is pushed first.  MF_ESTATE if the flow was never initialised. */
 MF_API int mf_resume(mf_handle_t *h);
 
 /* Maximum-flow value of the current capacities: e(t) plus the (negative)

@@ -1031,6 +1031,11 @@ MF_API int mf_resume(mf_handle_t *h) {
     HIP_TRY(h, hipSetDevice(h->device));
     HIP_TRY(h, hipEventRecord(h->ev[0], h->stream));
     HIP_TRY(h, mf::launch_reset_ctrl(h->g, h->stream));
+    // The loop ends at a maximum flow only if no residual arc leaves s.  A
+    // solve kernel that left while it repaired a batch (a barrier wait ran out)
+    // may not have come to the source, and an imported state need not have; one
+    // that is saturated is not changed.
+    HIP_TRY(h, mf::launch_saturate_source(h->g, h->stream));
     return debug_check(h, run_loop_and_finish(h));
 }
 
