@@ -361,7 +361,8 @@ struct RunStage {
     int32_t deliv;     // this round delivered excess
     int32_t base[4];
     int64_t acc[4];    // of the run: excess into t, relabels, pushes, deliveries into deficits
-    int64_t arcs;      // arcs of the vertices a BFS run discovered
+    int64_t arcs;      // arcs of the vertices that a BFS run discovered, its last level left out
+    int32_t last_items, last_arcs;  // frontier items and arcs of its last level
     uint64_t total;    // sum of the last team_sum
     int32_t ok;
 };
@@ -956,7 +957,7 @@ __device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const 
             rs->found = 0;
             rs->act = 0;
             rs->arcs = 0;
-            rs->larcs = 0;
+            rs->larcs = rs->last_arcs = 0;
         }
     }
     __syncthreads();
@@ -1110,12 +1111,13 @@ __device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const 
         uint64_t mine = 0;
         if (t == 0) {
             const bool late = (it & 15) == 0 && (int64_t)(wall_clock64() - ts) > p.barrier_ticks / 4;
-            const int got = min(rs->found, kRunItems);
-            rs->icnt[nxt] = got;
+            rs->arcs += rs->last_arcs;
+            rs->last_items = rs->found;
+            rs->last_arcs = rs->larcs;
+            rs->icnt[nxt] = min(rs->found, kRunItems);
             rs->found = 0;
-            mine = (uint64_t)rs->larcs | ((uint64_t)(rs->spill || late) << 48);
-            rs->arcs += rs->larcs;
             rs->larcs = 0;
+            mine = (uint64_t)rs->last_arcs | ((uint64_t)(rs->spill || late) << 48);
         }
         const uint64_t sum = team_sum<SC>(c, tm, epoch, mine, p.barrier_ticks, ok);
         if (!*ok) return L;
@@ -1131,7 +1133,10 @@ __device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const 
     if (t == 0) {
         if (nq) {
             rs->base[0] = fetch_add<SC>(&c->qcount[L % 3], nq);
-            if (dir) add<SC>(&c->qverts[L % 3], nq);  // the direction rule takes an item for a vertex here
+            if (dir) {  // the level's, spilled items too; the direction rule takes an item for a vertex here
+                add<SC>(&c->qverts[L % 3], rs->last_items);
+                add<SC>(&c->qarcs[L % 3], (int64_t)rs->last_arcs);
+            }
         }
         if (nl | nh) {
             const int64_t b = fetch_add<SC>(reinterpret_cast<int64_t *>(&c->lst[0]), ((int64_t)nh << 32) | (int64_t)nl);
@@ -1141,18 +1146,9 @@ __device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const 
     }
     __syncthreads();
     if (dir && t == 0 && rs->arcs) add<SC>(&c->run_arcs, rs->arcs);
-    int64_t qa = 0;
-    for (int i = t; i < nq; i += blockDim.x) {
-        const int2 item = items[cur * kRunItems + i];
-        frontier(g, L)[rs->base[0] + i] = item;
-        qa += item.y - item.x;
-    }
+    for (int i = t; i < nq; i += blockDim.x) frontier(g, L)[rs->base[0] + i] = items[cur * kRunItems + i];
     for (int i = t; i < nl; i += blockDim.x) g.list[0][rs->base[1] + i] = rs->aux[i];
     for (int i = t; i < nh; i += blockDim.x) g.list[0][n - 1 - (rs->base[2] + i)] = rs->aux[kStageCap + i];
-    if (dir && nq) {
-        qa = wave_sum(qa);
-        if (lane == 0 && qa) add<SC>(&c->qarcs[L % 3], qa);
-    }
     __syncthreads();  // the stage is free again
     return L;
 }
@@ -2396,7 +2392,7 @@ __device__ __forceinline__ void solve_loop(const DevGraph &g, const Team &tm, co
         if (!grid_barrier<SC>(c, tm, bar_epoch, p.barrier_ticks)) return;
         int L = 0;
         bool bu = false;
-        int64_t seen_arcs = 0;  // arcs of the vertices reached so far
+        int64_t seen_arcs = 0;  // arcs of the vertices reached so far (a run's last level by qarcs)
         for (;;) {
             // the level's counters are loaded together: one round trip after
             // the barrier, not one per counter
