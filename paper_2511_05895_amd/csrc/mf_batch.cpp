@@ -162,28 +162,30 @@ int class_of(const mf_batch_opts_t &o, int64_t a) {
     return o.n_classes - 1;
 }
 
+// What a team of t workgroups of 1024 threads needs for an instance of `arcs`
+// arcs, up to a factor: its steps, and its work per step over the team.
+double team_time(int64_t arcs, double t) { return std::sqrt((double)arcs) * (1 + (double)arcs / (160e3 * t)); }
+
 // Workgroups of 1024 threads per instance: the size with the shortest schedule
-// of order[0, cnt), each instance taken by the first team that is free.  A team
-// of t needs about sqrt(A) (1 + A / (160000 t)) for an instance of A arcs
-// (its steps, and its work per step over the team): by teams of 1, 2, 4, 8, 16
+// of order[0, cnt) on `cus` compute units, each instance taken by the first team
+// that is free.  (team_time: by teams of 1, 2, 4, 8, 16
 // and 32, a grid of 64 k arcs took 17 15 13 11 11 10 ms, one of 499 k arcs 90 59
 // 40 33 27 25, R-MAT of 427 k arcs 8.2 5.2 3.5 2.3 1.9 1.6.  Batches, at the
 // sizes chosen and beside them: 24 grids of 499 k, 8: 53 ms (4: 66, 16: 67); 128
-// of 135 k, 2: 32 (one workgroup each 46, 4: 49); 300 of 80 k, 1: 43 (2: 47).
-int team_size(const mf_batch_t *b, const int32_t *order, int32_t cnt) {
+// of 135 k, 2: 32 (one workgroup each 46, 4: 49); 300 of 80 k, 1: 43 (2: 47).)
+int team_size(const mf_batch_t *b, const int32_t *order, int32_t cnt, int cus) {
     int best = 1;
     double best_span = 0;
     for (int t = 1; t <= b->blocks / mf::kXcds; t *= 2) {
         std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
         double span = 0;
         for (int32_t j = 0; j < cnt; ++j) {
-            const double a = (double)b->arcs[order[j]];
             double at = 0;
-            if ((int)busy.size() == b->blocks / t) {
+            if ((int)busy.size() == std::max(1, cus / t)) {
                 at = busy.top();
                 busy.pop();
             }
-            at += std::sqrt(a) * (1 + a / (160e3 * t));
+            at += team_time(b->arcs[order[j]], t);
             busy.push(at);
             span = std::max(span, at);
         }
@@ -211,19 +213,32 @@ int apply_config(mf_batch_t *b) {
     b->class_begin.assign(o.n_classes + 1, 0);
     for (int32_t i = 0; i < b->count; ++i) b->class_begin[cls[i] + 1]++;
     for (int c = 0; c < o.n_classes; ++c) b->class_begin[c + 1] += b->class_begin[c];
+    // Compute units for the classes of 1024-thread workgroups, which run beside
+    // the smaller ones: in proportion to the work, at least what those cannot
+    // fill.  Teams that take them all only wait for one another's: 1000 random
+    // graphs of 100 to 2100 vertices, 26 of them in such a class, teams of 8
+    // against one workgroup each: 2.66 and 2.2 ms.
+    double small = 0, large = 0, wide = 0;
+    for (int32_t i = 0; i < b->count; ++i) {
+        const int block = o.block[cls[i]];
+        const double share = block == 256 ? 1. / 3 : 1;  // workgroups resident per unit
+        if (block == mf::kBlock) large += team_time(b->arcs[i], 1);
+        else small += share * team_time(b->arcs[i], (double)block / mf::kBlock), wide += share;
+    }
+    const int cus = b->blocks - (int)std::min(wide, large > 0 ? b->blocks * small / (small + large) : 0.);
     // Classes of 1024-thread workgroups next to each other share one launch and
     // its queue, largest first, when teams solve them.
     std::vector<int32_t> teams(b->order);
     for (int c = 0, end = 0; c < o.n_classes; c = end) {
         for (end = c; end < o.n_classes && o.block[end] == mf::kBlock; ++end) {
             const int32_t beg = b->class_begin[end];
-            b->team_alone[end] = team_size(b, b->order.data() + beg, b->class_begin[end + 1] - beg);
+            b->team_alone[end] = team_size(b, b->order.data() + beg, b->class_begin[end + 1] - beg, b->blocks);
         }
         if (end > c) {
             const int32_t beg = b->class_begin[c], cnt = b->class_begin[end] - beg;
             std::stable_sort(teams.begin() + beg, teams.begin() + beg + cnt,
                              [&](int32_t x, int32_t y) { return b->arcs[x] > b->arcs[y]; });
-            b->team[c] = team_size(b, teams.data() + beg, cnt);
+            b->team[c] = team_size(b, teams.data() + beg, cnt, cus);
             if (b->team[c] > 1) {
                 b->launch_end[c] = end;
                 continue;
@@ -267,7 +282,7 @@ hipError_t launch_classes(mf_batch_t *b, int first, int end, int team, hipStream
 // All classes side by side: fork from the main stream, one class per side
 // stream, join back.  Recorded into a graph when the main stream captures.
 hipError_t enqueue_all(mf_batch_t *b) {
-    hipError_t e = mf::launch_batch_reset(b->d_ctl, MF_BATCH_MAX_CLASSES, b->d_res, b->count, b->stream);
+    hipError_t e = mf::launch_batch_reset(b->d_ctl, b->opts.n_classes, b->d_res, b->count, b->stream);
     if (e != hipSuccess) return e;
     if ((e = hipEventRecord(b->fork_ev, b->stream)) != hipSuccess) return e;
     for (int c = 0, end = 0; c < b->opts.n_classes; c = end) {
@@ -632,7 +647,7 @@ MF_API int mf_batch_solve_class(mf_batch_t *b, int32_t c, double *kernel_ms) {
     if (!b) return bfail(nullptr, MF_EINVAL, "null batch");
     if (c < 0 || c >= b->opts.n_classes) return bfail(b, MF_EINVAL, "class out of range");
     BHIP(b, hipSetDevice(b->device));
-    BHIP(b, mf::launch_batch_reset(b->d_ctl, MF_BATCH_MAX_CLASSES, b->d_res, b->count, b->stream));
+    BHIP(b, mf::launch_batch_reset(b->d_ctl, b->opts.n_classes, b->d_res, b->count, b->stream));
     BHIP(b, hipEventRecord(b->ev[0], b->stream));
     BHIP(b, launch_classes(b, c, c + 1, b->team_alone[c], b->stream));
     BHIP(b, hipEventRecord(b->ev[1], b->stream));

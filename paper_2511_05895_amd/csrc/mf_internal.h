@@ -261,13 +261,14 @@ struct Repair {
     Ctrl *host = nullptr;     // pinned; its words from qcount on receive the control block
 };
 
-// Control words of a batch's team launch, cleared before it: the pools of
-// workgroups that form on each XCD, the next instance of the order, and every
-// team's barriers.
-constexpr int kBatchTeams = 16; // teams per XCD
+// Control words of a batch's team launch, cleared before it: the team that is
+// forming on each XCD, the sizes of its closed teams, the instances taken from
+// the front of the order (low half) and from its back, and every team's barriers.
+constexpr int kBatchTeams = 32; // teams per XCD
 struct BatchCtl {
-    PaddedU32 join[kXccIds], size[kXccIds];
-    PaddedU32 next;
+    PaddedU32 open[kXccIds];
+    PaddedU64 next;
+    uint32_t size[kXccIds][kBatchTeams];
     BarWords team[kXccIds * kBatchTeams];
 };
 

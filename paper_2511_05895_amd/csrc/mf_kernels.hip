@@ -3426,32 +3426,87 @@ __global__ void __launch_bounds__(BLOCK)
     }
 }
 
+// A team under three quarters of the size that was meant.
+__device__ __forceinline__ bool team_is_short(int members, int want) { return 4 * members < 3 * want; }
+
+// Join the team that is forming on this XCD (one thread calls it).  *open holds
+// its number times 256 plus its members so far; whoever completes it opens the
+// next one, so workgroups that get a compute unit late, behind other classes or
+// tenants, still make teams.  A team's first member closes it short after `limit`
+// ticks if it has half its members, and after ten times that with any number (a
+// member or two would hold up the batch with a large instance).  sizes[team] is
+// set once the team is closed.  *team is -1 beyond kBatchTeams.
+// Batches beside a class of small instances, with one pool per XCD that closed
+// after `limit` against this: 1000 grids of side 10 to 69, 62 against 23 ms; 600
+// of side 10 to 39 and four of 250, 76 against 35; 256 instances of up to 524 k
+// arcs 35 against 33.
+__device__ __forceinline__ void join_batch_team(PaddedU32 *open, uint32_t *sizes, int want, int64_t limit, int *team,
+                                                int *rank, int *size) {
+    uint32_t seen = __hip_atomic_load(&open->v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), next;
+    do {
+        if ((seen >> 8) >= (uint32_t)kBatchTeams) {
+            *team = -1;
+            return;
+        }
+        next = (int)(seen & 255u) + 1 == want ? (seen & ~255u) + 256u : seen + 1u;
+    } while (!__hip_atomic_compare_exchange_strong(&open->v, &seen, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT));
+    const uint32_t id = seen >> 8;
+    uint32_t n = 0;
+    if ((next >> 8) != id) {
+        n = (uint32_t)want;
+        __hip_atomic_store(&sizes[id], n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        const uint64_t t0 = wall_clock64();
+        while ((n = __hip_atomic_load(&sizes[id], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
+            __builtin_amdgcn_s_sleep(1);
+            const int64_t waited = (int64_t)(wall_clock64() - t0);
+            if ((seen & 255u) != 0 || waited < limit) continue;
+            uint32_t now = __hip_atomic_load(&open->v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t members = now & 255u;
+            if ((now >> 8) != id ||  // complete: its last member is about to set the size
+                (team_is_short((int)members, want) && waited < 10 * limit) ||
+                !__hip_atomic_compare_exchange_strong(&open->v, &now, (id + 1u) << 8, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT))
+                continue;
+            __hip_atomic_store(&sizes[id], members, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    *team = (int)id;
+    *rank = (int)(seen & 255u);
+    *size = (int)n;
+}
+
 // The larger instances of a batch: a workgroup alone is bound by what one
 // compute unit issues and gathers, and the batch ends with its largest
-// instance.  So the workgroups of each XCD form teams of `team` (whoever is
-// running when the XCD's pool closes, see join_team), and the teams take
-// instances from the order, largest first.  A team never waits for another.
+// instance.  So the workgroups of each XCD form teams of `team` (as they get
+// compute units, see join_batch_team), and the teams take instances from the
+// order, largest first.  A team never waits for another.
 // Measured, 64 grids and random graphs of up to 524 k arcs: 72 ms with one
 // workgroup each, 24 ms by teams (the largest alone: 21.4 ms).
 __global__ void __launch_bounds__(kBlock)
     k_batch_teams(const DevGraph *__restrict__ graphs, const int32_t *__restrict__ order, int count, LoopParams p,
                   const int32_t *__restrict__ kc, BatchResult *__restrict__ res, BatchCtl *ctl, int team) {
-    __shared__ int s_rank, s_size;
+    __shared__ int s_team, s_rank, s_size;
     const int xcc = xcd_id();
-    if (threadIdx.x == 0) close_pool(&ctl->join[xcc], &ctl->size[xcc], p.team_want, p.join_ticks, &s_rank, &s_size);
+    if (threadIdx.x == 0)
+        join_batch_team(&ctl->open[xcc], ctl->size[xcc], team, p.join_ticks, &s_team, &s_rank, &s_size);
     __syncthreads();
-    if (s_rank < 0) return;
-    const int id = s_rank / team;
-    if (id >= kBatchTeams) return;
-    const Team tm{s_rank - id * team, min(team, s_size - id * team)};
-    BarWords *bar = &ctl->team[xcc * kBatchTeams + id];
+    if (s_team < 0) return;
+    const Team tm{s_rank, s_size};
+    BarWords *bar = &ctl->team[xcc * kBatchTeams + s_team];
     init_stages();
     uint32_t epoch = 0;
     bool ok = true;
+    const bool back = team_is_short(tm.size, team);
     for (;;) {
         uint64_t mine = 0;
-        if (threadIdx.x == 0 && tm.rank == 0)
-            mine = 1u + __hip_atomic_fetch_add(&ctl->next.v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0 && tm.rank == 0) {
+            const uint64_t taken = __hip_atomic_fetch_add(&ctl->next.v, back ? 1ull << 32 : 1ull, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT);
+            const int front = (int)(uint32_t)taken, behind = (int)(taken >> 32);
+            mine = 1u + (uint32_t)(front + behind >= count ? count : back ? count - 1 - behind : front);
+        }
         block_sync<kXcd>();
         const int idx = (int)team_sum<kXcd>(bar, tm, epoch, mine, p.barrier_ticks, &ok) - 1;
         if (!ok || idx >= count) return;
@@ -3620,9 +3675,7 @@ hipError_t launch_batch_teams(const DevGraph *graphs, const int32_t *order, int 
                               const int32_t *kc, BatchResult *res, BatchCtl *ctl, int team, int blocks,
                               hipStream_t st) {
     if (count <= 0) return hipSuccess;
-    LoopParams pa = p;
-    pa.team_want = blocks / kXcds;
-    hipLaunchKernelGGL(k_batch_teams, dim3(blocks), dim3(kBlock), 0, st, graphs, order, count, pa, kc, res, ctl, team);
+    hipLaunchKernelGGL(k_batch_teams, dim3(blocks), dim3(kBlock), 0, st, graphs, order, count, p, kc, res, ctl, team);
     return hipGetLastError();
 }
 
