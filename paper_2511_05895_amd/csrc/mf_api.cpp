@@ -144,6 +144,12 @@ constexpr int32_t kBuBeta = 24;
 // workgroups all over the device: R-MAT 2^16 (1.8 M arcs) 1.30 against 1.81 ms,
 // grid 720^2 (4.1 M arcs) 79 against 105 ms, R-MAT 2^17 (3.7 M arcs) 2.1 against
 // 2.3 ms, R-MAT 2^18 (7.6 M arcs) 3.6 against 2.6 ms.
+// Two vertices count as an arc, which matters where most vertices have none:
+// every relabel reads and writes them all.  Updates of 50 edges of 2 k to 8 k
+// arcs, one workgroup against one XCD: 32 k vertices 58 to 104 against 61 to 118
+// us, 65 k 68 to 114 against 64 to 117, 1 M 394 to 445 against 76 to 137; one
+// XCD against 256 workgroups: 1 M 76 against 84, 4 M 105 against 90, 16 M 298
+// against 174.
 constexpr int64_t kOneMaxArcs = 1 << 14;
 constexpr int64_t kXcdMaxArcs = 1 << 22;
 // Rounds of local pulls into the deficits a batch leaves (the last one
@@ -937,20 +943,20 @@ MF_API int mf_create(const mf_csr_t *g, const int32_t *cap, int32_t s, int32_t t
         return bail(MF_EDEVICE, std::string("occupancy query: ") + hipGetErrorString(e));
     // one workgroup for small graphs, the workgroups of one XCD for larger
     // ones (kOneMaxArcs, kXcdMaxArcs); otherwise about one 1024-thread
-    // workgroup per 64K arcs, at most one per compute unit: a barrier of
-    // workgroups on several XCDs costs roughly 60 ns per workgroup
+    // workgroup per 64K arcs, at most one per compute unit
+    const int64_t size = std::max<int64_t>(A, n / 2);
     int cus = 0;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, o.device);
     int grid = o.grid_blocks;
     if (grid == 0) {
-        if (A <= kOneMaxArcs) grid = 1;
+        if (size <= kOneMaxArcs) grid = 1;
         else grid = (int)std::min<int64_t>(std::min(maxb, std::max(cus, 1)),
-                                           std::max<int64_t>(8, (A + 65535) / 65536));
+                                           std::max<int64_t>(8, (size + 65535) / 65536));
         // Graphs of up to kXcdMaxArcs arcs run on the compute units of one XCD
         // (see kXcd in the kernels): their steps are chains of dependent
         // loads, and one L2 without invalidations answers those sooner than
         // eight with.  Larger ones need every compute unit's bandwidth.
-        if (grid > 1 && A <= kXcdMaxArcs) {
+        if (grid > 1 && size <= kXcdMaxArcs) {
             h->xcd = 1;
             grid = std::max(2, std::max(cus, 1) / mf::kXcds);
         }
