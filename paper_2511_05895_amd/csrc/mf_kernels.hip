@@ -351,10 +351,11 @@ struct RunStage {
     // BFS: active vertices found, rounds: vertices for RemoveInvalidEdges;
     // short lists, then long ones
     int32_t aux[2 * kStageCap];
-    int32_t icnt[2], lcnt[2], hcnt[2], rcnt[2];
-    int32_t found;  // BFS: frontier items found in this level,
-    uint64_t act;   // short (low half) and long active vertices found in this run
-    int32_t larcs;     // BFS: arcs of the vertices discovered in this level
+    int32_t lcnt[2], hcnt[2], rcnt[2];
+    // BFS, of the two levels in buf: frontier items (spilled ones too) and the
+    // arcs of the vertices discovered (0 for those that the run starts with)
+    int32_t found[2], larcs[2];
+    uint64_t act;   // BFS: short (low half) and long active vertices found in this run
     int32_t spill;     // something did not fit and went to the global lists
     int32_t firsts;    // rounds: vertices relabelled for the first time in the phase
     int32_t relabels;  // of this round
@@ -362,7 +363,6 @@ struct RunStage {
     int32_t base[4];
     int64_t acc[4];    // of the run: excess into t, relabels, pushes, deliveries into deficits
     int64_t arcs;      // arcs of the vertices that a BFS run discovered, its last level left out
-    int32_t last_items, last_arcs;  // frontier items and arcs of its last level
     uint64_t total;    // sum of the last team_sum
     int32_t ok;
 };
@@ -944,6 +944,7 @@ __device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const 
                        bool counts, bool dir, uint32_t &epoch, Tally &tl, bool *ok) {
     RunStage *rs = run_stage();
     const int t = threadIdx.x, lane = lane_id(), w = uniform(t >> 6), nw = blockDim.x >> 6;
+    const int nw_bits = 31 - __clz(nw);  // a power of two
     const int n = g.n;
     Ctrl *c = g.ctrl;
     int2 *items = reinterpret_cast<int2 *>(rs->buf);
@@ -952,12 +953,12 @@ __device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const 
         const int mine = (cnt - tm.rank + tm.size - 1) / tm.size;
         for (int i = t; i < mine; i += blockDim.x) items[i] = get<SC>(&q[tm.rank + i * tm.size]);
         if (t == 0) {
-            rs->icnt[0] = mine;
+            rs->found[0] = mine;
+            rs->found[1] = 0;
+            rs->larcs[0] = rs->larcs[1] = 0;
             rs->spill = 0;
-            rs->found = 0;
             rs->act = 0;
             rs->arcs = 0;
-            rs->larcs = rs->last_arcs = 0;
         }
     }
     __syncthreads();
@@ -972,14 +973,21 @@ __device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const 
             c->qverts[(L + 2) % 3] = 0;
             c->qarcs[(L + 2) % 3] = 0;
         }
-        const int m = rs->icnt[cur], nxt = cur ^ 1;
+        const int m = min(rs->found[cur], kRunItems), nxt = cur ^ 1;
         const int2 *in = items + cur * kRunItems;
         int found_arcs = 0;
         // a wavefront takes 8 items at a time: 8 lanes each when none is long,
-        // otherwise all lanes over the items' arcs in turn
-        for (int base = w * G; base < m; base += nw * G) {
+        // otherwise all lanes over the items' arcs in turn.  Items that are long on
+        // average (a hub's list), and those that the run starts with, are dealt out
+        // one by one when there are not enough for all wavefronts; short ones are
+        // not, a step of a wavefront costs the same with 8 as with 1.  (edge_flow of
+        // a 40 x 40 grid, whose t has 1600 arcs: 308 us with 8 at a time, 195 us dealt
+        // out; all items dealt out, solve of a 256 x 256 grid: 25.6 -> 31 ms.)
+        const bool deal = it == 1 || rs->larcs[cur] > m * 4 * G;
+        const int q = uniform(deal ? min(G, (m + nw - 1) >> nw_bits) : G);
+        for (int base = w * q; base < m; base += nw * q) {
             int beg = 0, len = 0;
-            if (base + lane / G < m) {
+            if (lane / G < q && base + lane / G < m) {
                 const int2 item = in[base + lane / G];
                 beg = item.x;
                 len = item.y - item.x;
@@ -1048,7 +1056,7 @@ __device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const 
                 int ib = 0;
                 uint64_t ab = 0;
                 if (lane == 0) {
-                    ib = atomicAdd(&rs->found, ntot);
+                    ib = atomicAdd(&rs->found[nxt], ntot);
                     if (nl | nh)
                         ab = atomicAdd(reinterpret_cast<unsigned long long *>(&rs->act),
                                        ((unsigned long long)nh << 32) | (unsigned long long)nl);
@@ -1103,21 +1111,17 @@ __device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const 
                 }
             }
         }
-        if (w * G < m) {
+        if (w * q < m) {
             const int fa = wave_sum(found_arcs);  // below A < 2^31
-            if (lane == 0 && fa) atomicAdd(&rs->larcs, fa);
+            if (lane == 0 && fa) atomicAdd(&rs->larcs[nxt], fa);
         }
         block_sync<SC>();
         uint64_t mine = 0;
         if (t == 0) {
             const bool late = (it & 15) == 0 && (int64_t)(wall_clock64() - ts) > p.barrier_ticks / 4;
-            rs->arcs += rs->last_arcs;
-            rs->last_items = rs->found;
-            rs->last_arcs = rs->larcs;
-            rs->icnt[nxt] = min(rs->found, kRunItems);
-            rs->found = 0;
-            rs->larcs = 0;
-            mine = (uint64_t)rs->last_arcs | ((uint64_t)(rs->spill || late) << 48);
+            mine = (uint64_t)rs->larcs[nxt] | ((uint64_t)(rs->spill || late) << 48);
+            atomicAdd(reinterpret_cast<unsigned long long *>(&rs->arcs), (unsigned long long)rs->larcs[cur]);
+            rs->found[cur] = rs->larcs[cur] = 0;
         }
         const uint64_t sum = team_sum<SC>(c, tm, epoch, mine, p.barrier_ticks, ok);
         if (!*ok) return L;
@@ -1128,14 +1132,14 @@ __device__ __forceinline__ int bfs_run(const DevGraph &g, const Team &tm, const 
     }
     // the active vertices found (and the items, when the run ends early) go
     // to the global lists, one reservation each
-    const int nq = dump ? rs->icnt[cur] : 0;
+    const int nq = dump ? min(rs->found[cur], kRunItems) : 0;
     const int nl = min((int)(uint32_t)rs->act, kStageCap), nh = min((int)(rs->act >> 32), kStageCap);
     if (t == 0) {
         if (nq) {
             rs->base[0] = fetch_add<SC>(&c->qcount[L % 3], nq);
             if (dir) {  // the level's, spilled items too; the direction rule takes an item for a vertex here
-                add<SC>(&c->qverts[L % 3], rs->last_items);
-                add<SC>(&c->qarcs[L % 3], (int64_t)rs->last_arcs);
+                add<SC>(&c->qverts[L % 3], rs->found[cur]);
+                add<SC>(&c->qarcs[L % 3], (int64_t)rs->larcs[cur]);
             }
         }
         if (nl | nh) {
