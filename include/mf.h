@@ -91,14 +91,18 @@ typedef struct {
                                downhill to a root within L rounds);
                                0 = 3, < 0 = no such rule                     */
     int32_t solo_items;     /* a BFS level whose frontier holds at most this
-                               many items (arc ranges of up to 256 arcs), and
+                               many items (arc ranges of up to 256 arcs;
+                               levels of more than 4096 arcs are left to
+                               everyone while the bottom-up rule is on), and
                                a push/relabel round whose list holds at most
                                this many vertices (none of more than 4096
                                arcs), is run by one workgroup alone, with
                                workgroup barriers between its levels or
                                rounds, while the others wait (solves whose
                                workgroups share one XCD keep small levels and
-                               rounds among themselves instead); 0 = 128,
+                               rounds among themselves instead); what the
+                               workgroup's LDS holds bounds it: more than 512
+                               count as 512; 0 = 128,
                                < 0 = never                                   */
     int32_t lazy_items;     /* a BFS level whose frontier holds at least this
                                many items reads the residual of an arc's
@@ -202,7 +206,9 @@ typedef struct {
     int64_t source_pushes;    /* arcs out of s saturated                      */
     int64_t rounds;           /* push/relabel rounds                          */
     int64_t loop_launches;    /* launches of the persistent solve kernel      */
-    int64_t grid_blocks;      /* workgroups of that kernel                    */
+    int64_t grid_blocks;      /* workgroups it is meant for; those that run when
+                                 it starts form its team, fewer if other work
+                                 holds the device.  1 for a batch's instances */
     double bfs_ms;            /* device wall time in global relabels          */
     double pr_ms;             /* ... in push/relabel rounds                   */
     double rie_ms;            /* ... in RemoveInvalidEdges                    */

@@ -1691,10 +1691,6 @@ __device__ __forceinline__ int discharge_walk(const DevGraph &g, int u, int kc, 
     return lane == 0 ? relabels : 0;
 }
 
-// Lanes per vertex with a short arc list (at most kLightMaxDeg arcs): the
-// arcs of a typical vertex load in one step instead of one after another.
-constexpr int kLightGroup = 8;
-
 // A whole workgroup visits vertex u (more than kHugeDeg arcs).  Each
 // wavefront owns a contiguous chunk of u's arcs and finds, in one pass, its
 // lowest residual neighbour height and the residual capacity toward it; the
