@@ -3268,8 +3268,13 @@ __global__ void k_init_state(DevGraph g) {
 // the sink side, taken from the sink side's lists (the twins of its arcs whose
 // head is on the source side).  The sink side is usually the smaller one by
 // far, and a list of it is read in order with one height gather per arc; only
-// a crossing arc reads its twin and that arc's capacity.  Lists of more than
-// kChunk arcs go to k_cut_items in items, so a hub is split over the device.
+// a crossing arc reads its twin and that arc's capacity.  If some list has more
+// than kChunk arcs, those of more than kCutList go to k_cut_items in items: hubs
+// are split over the device, and vertices of many arcs, which are neighbours in
+// the degree order, do not end up with one wavefront (up to 64 x 256 arcs, one
+// step after another).  A small graph's vertices go to more wavefronts for the
+// same reason.  With the cut at s, all lists of the sink side: R-MAT 2^14 142 us,
+// 43 so, 2^16 177 and 84, 2^18 245 and 132; 100 vertices of 180 arcs 61 and 19.
 // Bound by the read of the heights when the sink side is small.  R-MAT 2^22 x
 // 16: 5.1 ms (scanning the source side, the numbering undone on the host) ->
 // 0.36 ms; 2^20: 1.12 -> 0.11 ms; a 512 x 512 grid: 175 -> 112 us; 20 k vertices:
@@ -3290,8 +3295,10 @@ __device__ __forceinline__ void cut_finish(Ctrl *c, int64_t *cut) {
     c->cut_done = 0;
 }
 
-// cut: where the sum goes, or null if k_cut_items follows.
-__global__ void k_cut_side(DevGraph g, const int32_t *new_of_old, uint8_t *side, int64_t *cut) {
+// cut: where the sum goes, or null if k_cut_items follows.  per: vertices of a
+// wavefront at a time.
+constexpr int kCutList = 16;  // arcs of a list that its wavefront reads itself
+__global__ void k_cut_side(DevGraph g, const int32_t *new_of_old, uint8_t *side, int64_t *cut, int per) {
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     if (side) {  // four vertices a word (side is allocated in whole words)
@@ -3306,16 +3313,17 @@ __global__ void k_cut_side(DevGraph g, const int32_t *new_of_old, uint8_t *side,
         }
     }
     const int lane = lane_id();
+    const int longest = cut ? INT32_MAX : kCutList;
     int64_t part = 0;
-    for (int64_t base = gtid - lane; base < g.n; base += stride) {
+    for (int64_t base = (gtid >> 6) * per; base < g.n; base += (stride >> 6) * per) {
         const int64_t v = base + lane;
         int beg = 0, len = 0;
-        if (v < g.n && g.h[v] < g.n) {
+        if (lane < per && v < g.n && g.h[v] < g.n) {
             beg = g.row_ptr[v];
             len = g.row_ptr[v + 1] - beg;
         }
         if (__ballot(len > 0) == 0) continue;
-        const int ni = len > kChunk ? n_items(len) : 0;
+        const int ni = len > longest ? n_items(len) : 0;
         const int slot = wave_appendn<kAgent>(&g.ctrl->cut_items, ni);
         for (int k = 0; k < ni; ++k)
             g.q[0][slot + k] = make_int2(beg + k * kChunk, min(beg + (k + 1) * kChunk, beg + len));
@@ -3767,8 +3775,9 @@ hipError_t launch_edge_flow(const DevGraph &g, const int2 *carc, int32_t *rem, i
 
 hipError_t launch_min_cut(const DevGraph &g, const int32_t *new_of_old, uint8_t *side, bool long_lists, int64_t *cut,
                           hipStream_t st) {
-    hipLaunchKernelGGL(k_cut_side, dim3(grid_for(g.n, 256, 2048)), dim3(256), 0, st, g, new_of_old, side,
-                       long_lists ? nullptr : cut);
+    const int per = max(4, min(64, g.n / 512));  // up to 32 k vertices, about 512 wavefronts
+    hipLaunchKernelGGL(k_cut_side, dim3(grid_for(((int64_t)g.n + per - 1) / per, 4, 2048)), dim3(256), 0, st, g,
+                       new_of_old, side, long_lists ? nullptr : cut, per);
     if (long_lists)
         hipLaunchKernelGGL(k_cut_items, dim3(grid_for(g.A / kChunk, 4, 1024)), dim3(256), 0, st, g, cut);
     return hipGetLastError();
