@@ -413,8 +413,8 @@ int next_epoch(mf_handle_t *h) {
     return MF_OK;
 }
 
-// Lay a host batch out in pinned staging, from where the call's first kernel
-// fetches it (begin_staged).  A call that failed part-way may
+// Lay a host batch out in pinned staging, from where it is copied or fetched
+// (begin_staged).  A call that failed part-way may
 // have left the previous copies queued, so the stream is drained before the
 // pinned buffers are written or freed (a no-op after a completed call).
 int stage_host_batch(mf_handle_t *h, const int64_t *ids, const int32_t *caps, int64_t k) {
@@ -447,19 +447,18 @@ int stage_host_batch(mf_handle_t *h, const int64_t *ids, const int32_t *caps, in
     if (k > 0) {
         std::memcpy(h->p_stage, ids, sizeof(int64_t) * k);
         std::memcpy(h->p_stage + sizeof(int64_t) * k, caps, sizeof(int32_t) * k);
+        // a small batch is fetched by the call's first kernel, a larger one copied,
+        // at once, while the host prepares the rest (update of 100 k edges of R-MAT
+        // 2^16: fetched 372 us, copied 307)
+        if (k > mf::kRepairMax)
+            HIP_TRY(h, hipMemcpyAsync(h->d_stage, h->p_stage, kPer * k, hipMemcpyHostToDevice, h->stream));
     }
     return MF_OK;
 }
 
-// Start of a call whose batch is in the pinned staging: a small batch is fetched
-// by the call's first kernel, a larger one copied (update of 100 k edges of
-// R-MAT 2^16: fetched 372 us, copied 307).
+// First kernel of a call whose batch was staged.
 hipError_t begin_staged(mf_handle_t *h, int64_t k) {
-    const int64_t words = 3 * k;
-    if (k <= mf::kRepairMax) return mf::launch_begin(h->g, h->p_stage, h->d_stage, words, h->stream);
-    const hipError_t e =
-        hipMemcpyAsync(h->d_stage, h->p_stage, sizeof(int32_t) * words, hipMemcpyHostToDevice, h->stream);
-    return e == hipSuccess ? mf::launch_reset_ctrl(h->g, h->stream) : e;
+    return mf::launch_begin(h->g, h->p_stage, h->d_stage, k <= mf::kRepairMax ? 3 * k : 0, h->stream);
 }
 
 // Allocate the second view of the state (see mf_handle::views).
