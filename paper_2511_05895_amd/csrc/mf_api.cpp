@@ -137,7 +137,7 @@ constexpr int32_t kLazyItems = 1024;
 constexpr int32_t kBuAlpha = 14;
 constexpr int32_t kBuBeta = 24;
 // Arcs up to which one workgroup solves alone, and up to which the solve
-// kernel's team stays on one XCD (32 workgroups).  Static solves, one workgroup
+// kernel's team stays on one XCD (28 workgroups; figures with 32).  Static solves, one workgroup
 // against one XCD: 20 x 20 grid (2,880 arcs) 0.67 against 0.70 ms, random graph
 // of 1,000 vertices (16 k arcs) 0.45 against 0.48 ms, R-MAT 2^10 (24 k arcs) 0.50
 // against 0.25 ms, grid 64^2 (32 k arcs) 5.1 against 3.9 ms.  One XCD against
@@ -961,7 +961,7 @@ MF_API int mf_create(const mf_csr_t *g, const int32_t *cap, int32_t s, int32_t t
         // eight with.  Larger ones need every compute unit's bandwidth.
         if (grid > 1 && size <= kXcdMaxArcs) {
             h->xcd = 1;
-            grid = std::max(2, std::max(cus, 1) / mf::kXcds);
+            grid = std::max(2, std::max(cus, 1) / mf::kXcds - mf::kXcdSpare);
         }
     }
     if (grid > 1 && grid > maxb)

@@ -23,6 +23,17 @@ constexpr int kHugeDeg = 4096;
 constexpr int kChunk = 256;
 // XCDs of the device; consecutive workgroups of a launch go to them in turn.
 constexpr int kXcds = 8;
+// Compute units of its XCD that a one-XCD team leaves to others.  A workgroup of
+// the solve kernel fills the registers of its unit, so without them everything
+// else that has a workgroup bound for that XCD, also one that would only leave,
+// waits for the team's solve to end.  Four, one for each of the XCD's shader
+// engines, to which workgroups go in turn: with two it waits all the same.
+// Updates of 100 edges beside solves of a 512 x 512 grid (45 ms), none / two /
+// four left: 3 k vertices 41 / 44 / 0.15 ms, 20 k vertices 42 / 43 / 0.20; two and
+// four 200 x 200 grids at once 30 and 32 ms with none left, 20 and 20 with four.
+// The team of 28 solves as fast as one of 32 (200 x 200 to 320 x 320 grids, R-MAT
+// 2^14 and 2^16, random graphs of 5 k and 20 k vertices: within 2 %).
+constexpr int kXcdSpare = 4;
 // Threads per workgroup of the persistent solve kernel.
 constexpr int kBlock = 1024;
 

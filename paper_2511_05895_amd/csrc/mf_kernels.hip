@@ -430,58 +430,83 @@ __device__ __forceinline__ uint64_t team_sum(BarWords *c, const Team &tm, uint32
     return (uint64_t)uniform((int64_t)rs->total);
 }
 
-// Register with a pool of workgroups (one thread calls it): the first arrival
-// closes the pool once `want` have registered or `limit` ticks have passed and
-// publishes its size, the others wait for that (the first is running, so it
-// comes).  *rank is -1 for whoever arrives later.
+// Waits until `want` workgroups have registered in *joined or `limit` ticks have
+// passed, closes it and publishes the team's size (the first of them calls it).
 constexpr uint32_t kTeamClosed = 0x80000000u;
-__device__ __forceinline__ void close_pool(PaddedU32 *join, PaddedU32 *closed, int want, int64_t limit, int *rank,
-                                           int *size) {
-    *rank = -1;
-    *size = 0;
-    const uint32_t old = __hip_atomic_fetch_add(&join->v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old & kTeamClosed) return;
-    *rank = (int)old;
-    uint32_t n = 0;
-    if (old == 0) {
-        const uint64_t t0 = wall_clock64();
-        while ((int)__hip_atomic_load(&join->v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want &&
-               (int64_t)(wall_clock64() - t0) < limit) {
-        }
-        n = __hip_atomic_fetch_or(&join->v, kTeamClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&closed->v, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        while ((n = __hip_atomic_load(&closed->v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0)
-            __builtin_amdgcn_s_sleep(1);
+__device__ __forceinline__ uint32_t close_team(uint32_t *joined, uint32_t *size, int want, int64_t limit) {
+    const uint64_t t0 = wall_clock64();
+    while ((int)__hip_atomic_load(joined, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want &&
+           (int64_t)(wall_clock64() - t0) < limit) {
     }
-    *size = (int)n;
+    const uint32_t n = __hip_atomic_fetch_or(joined, kTeamClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(size, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return n;
 }
 
-// The team of a launch forms itself: the workgroups that arrive register in
-// Ctrl::join, the first of them closes the team once `want` have registered or
-// `limit` ticks have passed, and whoever arrives later leaves the kernel.  A
+// The team of a launch forms itself: the workgroups that arrive register, the
+// first of them closes the team once `want` have registered or `limit` ticks
+// have passed, and whoever arrives later leaves the kernel.  A
 // team is thus made of workgroups that are running already, whatever else
 // occupies the device, so its barriers need no co-residency promise (and no
 // cooperative launch, whose host call costs several times a plain one's).
-// With kXcd only workgroups on the XCD of the first arrival register.  Returns
-// size 0 to a workgroup that is not in the team.  Every thread calls it once,
-// before any grid barrier, on a cleared control block.
+//
+// With kXcd the launch has `want` workgroups for every XCD.  Each registers on
+// its own, and the first XCD to have them all is the team's; the others' leave.
+// If none is complete after a quarter of `limit` (other work holds units of
+// them all, perhaps another launch of this kind that waits in the same way), it
+// is the one with the most, ties broken differently for different handles; what
+// leaves the others then makes room for its rest.
+//
+// Returns size 0 to a workgroup that is not in the team.  Every thread calls it
+// once, before any grid barrier, on a cleared control block.
 template <int SC>
 __device__ __forceinline__ Team join_team(Ctrl *c, int want, int64_t limit) {
     __shared__ int s_rank, s_size;
     if (threadIdx.x == 0) {
-        int rank = -1, size = 0;
-        bool in = true;
+        uint32_t *joined = &c->join.v;
+        const uint32_t me = (uint32_t)xcd_id() + 1u;
+        if constexpr (SC == kXcd) joined = &c->bar_xcd[me - 1u].v;  // (such a team's barrier does not use it)
+        const uint32_t rank = __hip_atomic_fetch_add(joined, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool in = rank < (uint32_t)want;
         if constexpr (SC == kXcd) {
-            const uint32_t me = (uint32_t)xcd_id() + 1u;
-            uint32_t first = 0;
-            in = __hip_atomic_compare_exchange_strong(&c->xcd_pick.v, &first, me, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT) ||
-                 first == me;
+            if (in) {
+                uint32_t pick = 0, none = 0;
+                if (rank + 1u == (uint32_t)want)
+                    __hip_atomic_compare_exchange_strong(&c->xcd_pick.v, &none, me, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);
+                const uint64_t t0 = wall_clock64();
+                while ((pick = __hip_atomic_load(&c->xcd_pick.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
+                    __builtin_amdgcn_s_sleep(1);
+                    if ((int64_t)(wall_clock64() - t0) < limit / 4) continue;
+                    const uint32_t from = ((uint32_t)(reinterpret_cast<uint64_t>(c) >> 8) * 2654435761u) >> 29;
+                    uint32_t most = 0, at = 0;
+                    for (uint32_t k = 0; k < (uint32_t)kXccIds; ++k) {
+                        const uint32_t x = (from + k) & (kXccIds - 1);
+                        const uint32_t n = __hip_atomic_load(&c->bar_xcd[x].v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (n > most) {
+                            most = n;
+                            at = x + 1u;
+                        }
+                    }
+                    none = 0;
+                    __hip_atomic_compare_exchange_strong(&c->xcd_pick.v, &none, at, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);
+                }
+                in = pick == me;
+            }
         }
-        if (in) close_pool(&c->join, &c->team_size, want, limit, &rank, &size);
-        s_rank = rank;
-        s_size = size;
+        uint32_t size = 0;
+        if (in) {
+            if (rank == 0) {
+                size = close_team(joined, &c->team_size.v, want, limit);
+            } else {
+                while ((size = __hip_atomic_load(&c->team_size.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0)
+                    __builtin_amdgcn_s_sleep(1);
+            }
+            if (SC == kXcd && size > (uint32_t)want) size = (uint32_t)want;
+        }
+        s_rank = (int)rank;
+        s_size = (int)size;
     }
     __syncthreads();
     return Team{s_rank, s_size};
@@ -3669,7 +3694,7 @@ hipError_t launch_loop(const DevGraph &g, const LoopParams &p, const Repair &b, 
     }
     LoopParams pa = p;
     pa.team_want = grid;
-    if (p.xcd) {  // one workgroup in kXcds lands on the team's XCD, the others leave at once
+    if (p.xcd) {  // `grid` for every XCD, one of which is the team
         const dim3 blocks(grid * kXcds);
         if (p.walk) hipLaunchKernelGGL((k_loop<kBlock, kXcd, true>), blocks, dim3(kBlock), 0, st, g, pa, b);
         else hipLaunchKernelGGL((k_loop<kBlock, kXcd, false>), blocks, dim3(kBlock), 0, st, g, pa, b);

@@ -17,12 +17,9 @@
 //   graph's persistent solve kernel is run by the workgroups that are resident
 //   when its team forms, and its result does not depend on how many those are.
 //   A commit starts only while the grids in flight leave room for its grid
-//   (workgroup slots of the device).  That does not keep tenants apart: the
-//   count is over the device, and a team of one XCD wants its workgroups there;
-//   where another tenant is, it forms smaller or elsewhere.  And a solve kernel
-//   fills the compute units it has, so a kernel with workgroups bound for them,
-//   also workgroups that only leave, ends after it (100 edges of 20 k vertices:
-//   0.18 ms alone, 50 ms beside solves of a 512 x 512 grid of 50 ms each).
+//   (workgroup slots of the device).  Teams of one XCD form on different XCDs and
+//   leave room on theirs for others' workgroups to pass; a team all over the
+//   device leaves none, and commits beside it end after it.
 // * Requests are admitted by memory: the queued requests' bytes stay within
 //   max_pending_bytes (else MF_EBUSY, nothing queued), and a request may not
 //   exceed the edges one commit stages (max_group_edges), so the staging

@@ -1,5 +1,5 @@
 """Which workgroups solve a graph by default: one up to 2^14 arcs, those of one
-XCD up to 2^22, one per 2^16 arcs beyond, where two vertices count as an arc at
+XCD but four up to 2^22, one per 2^16 arcs beyond, where two vertices count as an arc at
 least.  Graphs at the edges of the rule, against the oracle."""
 import numpy as np
 import pytest
@@ -43,7 +43,7 @@ def test_default_team(name):
     from paper_2511_05895_amd import mf
     n, pairs, used, blocks = CASES[name]
     if blocks == "x":
-        blocks = torch.cuda.get_device_properties(0).multi_processor_count // 8
+        blocks = torch.cuda.get_device_properties(0).multi_processor_count // 8 - 4
     g = distinct_pairs(n, pairs, 55, used)
     cap = g.cap.copy()
     with mf.MaxFlow(g) as F:
